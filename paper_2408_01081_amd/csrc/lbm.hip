@@ -46,16 +46,15 @@ constexpr int RED_THREADS = 256;
 // Device kernels
 // ---------------------------------------------------------------------------
 
+template <int SRC>
 __global__ __launch_bounds__(256) void k_init(const double* __restrict__ v0,
                                               const double* __restrict__ s0,
                                               const double* __restrict__ grad,
                                               float* __restrict__ dst, Grid g, InitConst k,
                                               Force F) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)g.nx * g.ny;
-  if (id >= n) return;
-  const int y = (int)(id / g.nx), x = (int)(id - (int64_t)y * g.nx);
-  init_node<double>(v0, s0, grad, dst, g, k, x, y, F);
+  int x, y;
+  if (!field_node(g, x, y)) return;
+  init_node<SRC, double>(v0, s0, grad, dst, g, k, x, y, F);
 }
 
 // U_num(t_n) of a node from its stored post-collision populations:
@@ -76,10 +75,9 @@ __global__ __launch_bounds__(256) void k_init_disp(const float* __restrict__ src
                                                    const double* __restrict__ u0,
                                                    double* __restrict__ D, Grid g, Force F,
                                                    double half_dt) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)g.nx * g.ny;
-  if (id >= n) return;
-  const int y = (int)(id / g.nx), x = (int)(id - (int64_t)y * g.nx);
+  int x, y;
+  if (!field_node(g, x, y)) return;
+  const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC], U[NC];
   for (int q = 0; q < NQ; ++q)
     for (int c = 0; c < NC; ++c) f[q][c] = src[pidx(g, q * NC + c, y, x)];
@@ -92,10 +90,9 @@ __global__ __launch_bounds__(256) void k_displacement(const float* __restrict__ 
                                                       const double* __restrict__ D,
                                                       float* __restrict__ out, Grid g, Force F,
                                                       double half_dt) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)g.nx * g.ny;
-  if (id >= n) return;
-  const int y = (int)(id / g.nx), x = (int)(id - (int64_t)y * g.nx);
+  int x, y;
+  if (!field_node(g, x, y)) return;
+  const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC], U[NC];
   for (int q = 0; q < NQ; ++q)
     for (int c = 0; c < NC; ++c) f[q][c] = src[pidx(g, q * NC + c, y, x)];
@@ -107,10 +104,9 @@ __global__ __launch_bounds__(256) void k_displacement(const float* __restrict__ 
 __global__ __launch_bounds__(256) void k_set_populations(const float* __restrict__ fin,
                                                          float* __restrict__ dst, Grid g,
                                                          float kK, float km, Force F) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)g.nx * g.ny;
-  if (id >= n) return;
-  const int y = (int)(id / g.nx), x = (int)(id - (int64_t)y * g.nx);
+  int x, y;
+  if (!field_node(g, x, y)) return;
+  const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC];
   for (int q = 0; q < NQ; ++q)
     for (int c = 0; c < NC; ++c) f[q][c] = fin[(q * NC + c) * n + id];
@@ -138,10 +134,9 @@ struct MomConst {
 __global__ __launch_bounds__(256) void k_moments(const float* __restrict__ src,
                                                  float* __restrict__ out, Grid g, MomConst m,
                                                  Force F) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)g.nx * g.ny;
-  if (id >= n) return;
-  const int y = (int)(id / g.nx), x = (int)(id - (int64_t)y * g.nx);
+  int x, y;
+  if (!field_node(g, x, y)) return;
+  const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC];
   for (int q = 0; q < NQ; ++q)
     for (int c = 0; c < NC; ++c) f[q][c] = src[pidx(g, q * NC + c, y, x)];
@@ -639,10 +634,11 @@ lbm_status lbm_lattice_constants(const lbm_ctx* c, double* kK, double* km, doubl
 
 static lbm_status init_from(lbm_ctx* c, const double* d_v0, const double* d_s0,
                             const double* d_grad, int src) {
-  const int64_t n = (int64_t)c->g.nx * c->g.ny;
-  InitConst k{c->kK, c->km, c->cK, c->cmu, c->p.rho, c->p.dx, c->p.bc, src};
-  hipLaunchKernelGGL(k_init, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, d_v0,
-                     d_s0, d_grad, c->buf[0], c->g, k, force_at(c, 0));
+  const InitConst k = init_const(c->kK, c->km, c->cK, c->cmu, c->p.rho, c->p.dx, c->p.bc);
+  hipLaunchKernelGGL(src == INIT_FROM_STRESS ? &k_init<INIT_FROM_STRESS>
+                                             : &k_init<INIT_FROM_GRADIENT>,
+                     dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream, d_v0, d_s0,
+                     d_grad, c->buf[0], c->g, k, force_at(c, 0));
   lbm_status s = launch_check("k_init launch");
   if (s) return s;
   c->cur = 0;
@@ -685,8 +681,7 @@ lbm_status lbm_init_displacement(lbm_ctx* c, const double* d_u0) {
   if (!c->disp) return fail(LBM_E_STATE, "context created without LBM_F_DISPLACEMENT");
   if (!c->initialised || c->nstep != 0)
     return fail(LBM_E_STATE, "lbm_init_displacement needs a freshly initialised lattice");
-  const int64_t n = (int64_t)c->g.nx * c->g.ny;
-  hipLaunchKernelGGL(k_init_disp, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+  hipLaunchKernelGGL(k_init_disp, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
                      (const float*)c->buf[c->cur], d_u0, c->disp, c->g, force_at(c, 0),
                      0.5 * c->p.dt);
   lbm_status s = launch_check("k_init_disp launch");
@@ -699,8 +694,7 @@ lbm_status lbm_displacement(lbm_ctx* c, float* d_u) {
   if (!c || !d_u) return fail(LBM_E_ARG, "null argument");
   if (!c->disp || !c->disp_ready)
     return fail(LBM_E_STATE, "no displacement: LBM_F_DISPLACEMENT and lbm_init_displacement");
-  const int64_t n = (int64_t)c->g.nx * c->g.ny;
-  hipLaunchKernelGGL(k_displacement, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+  hipLaunchKernelGGL(k_displacement, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
                      (const float*)c->buf[c->cur], (const double*)c->disp, d_u, c->g,
                      force_at(c, c->nstep), 0.5 * c->p.dt);
   return launch_check("k_displacement launch");
@@ -749,8 +743,7 @@ lbm_status lbm_error_sums(lbm_ctx* c, double* h_out) {
 
 lbm_status lbm_set_populations(lbm_ctx* c, const float* d_f) {
   if (!c || !d_f) return fail(LBM_E_ARG, "null argument");
-  const int64_t n = (int64_t)c->g.nx * c->g.ny;
-  hipLaunchKernelGGL(k_set_populations, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
+  hipLaunchKernelGGL(k_set_populations, dim3((unsigned)field_tiles(c->g)), dim3(256), 0,
                      c->stream, d_f, c->buf[0], c->g, (float)c->kK, (float)c->km,
                      force_at(c, 0));
   lbm_status s = launch_check("k_set_populations launch");
@@ -1615,9 +1608,8 @@ lbm_status lbm_time_step_config(lbm_ctx* c, int32_t index, int32_t reps, double*
 static lbm_status moments_mode(lbm_ctx* c, float* out, int mode) {
   if (!c || !out) return fail(LBM_E_ARG, "null argument");
   if (!c->initialised) return fail(LBM_E_STATE, "not initialised");
-  const int64_t n = (int64_t)c->g.nx * c->g.ny;
   MomConst m{(float)c->cK, (float)c->cmu, (float)c->p.rho, (float)c->kK, (float)c->km, mode};
-  hipLaunchKernelGGL(k_moments, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+  hipLaunchKernelGGL(k_moments, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
                      c->buf[c->cur], out, c->g, m, force_at(c, c->nstep));
   return launch_check("k_moments launch");
 }

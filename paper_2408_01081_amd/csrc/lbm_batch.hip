@@ -70,6 +70,27 @@ __device__ inline int find_instance(const InstDesc* __restrict__ d, int n, int64
   return lo;
 }
 
+// fn(instance, x, y) for this thread's node of the packed node range: a block
+// of BT consecutive nodes lies in one instance, or in a run of them, which the
+// whole block walks together, so the descriptors come through scalar loads
+// and no thread searches for its own (128 instances of 128 rows, 3.3 M nodes:
+// FP64 initialisation 237 -> 81 us with the form of init_node above).
+template <typename FN>
+__device__ inline void for_block_instances(const InstDesc* __restrict__ descs, int n, FN fn) {
+  const int64_t first = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BT;
+  const int64_t node = first + threadIdx.x;
+  for (int i = find_instance(descs, n, first); i < n; ++i) {
+    const InstDesc& d = descs[i];
+    if (d.node0 >= first + BT) break;
+    const int64_t loc = node - d.node0;
+    if (loc < 0 || loc >= (int64_t)d.g.nx * d.g.ny) continue;
+    // (instances whose node count fits 31 bits: a 32-bit division)
+    const int y = (int64_t)d.g.nx * d.g.ny <= 0x7fffffff ? (int)((unsigned)loc / (unsigned)d.g.nx)
+                                                          : (int)(loc / d.g.nx);
+    fn(d, (int)(loc - (int64_t)y * d.g.nx), y);
+  }
+}
+
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_batch_step(const float* __restrict__ pool_src,
                                                         float* __restrict__ pool_dst,
@@ -182,45 +203,38 @@ template <typename T>
 __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
                                                    const T* __restrict__ s0, int packed,
                                                    float* __restrict__ pool,
-                                                   const InstDesc* __restrict__ descs, int n,
-                                                   int64_t total) {
-  const int64_t node = (int64_t)blockIdx.x * BT + threadIdx.x;
-  if (node >= total) return;
-  const InstDesc& d = descs[find_instance(descs, n, node)];
-  const int64_t loc = node - d.node0;
-  const int64_t ni = (int64_t)d.g.nx * d.g.ny;
-  const int y = (int)(loc / d.g.nx), x = (int)(loc - (int64_t)y * d.g.nx);
-  const T* v = packed ? s0 + 5 * d.node0 : v0 + 2 * d.node0;
-  const T* s = packed ? s0 + 5 * d.node0 + 2 * ni : s0 + 3 * d.node0;
-  init_node<T>(v, s, nullptr, pool + d.off, d.g, d.ic, x, y);
+                                                   const InstDesc* __restrict__ descs, int n) {
+  for_block_instances(descs, n, [&](const InstDesc& d, int x, int y) {
+    const int64_t ni = (int64_t)d.g.nx * d.g.ny;
+    const T* v = packed ? s0 + 5 * d.node0 : v0 + 2 * d.node0;
+    const T* s = packed ? s0 + 5 * d.node0 + 2 * ni : s0 + 3 * d.node0;
+    init_node<INIT_FROM_STRESS, T>(v, s, nullptr, pool + d.off, d.g, d.ic, x, y);
+  });
 }
 
 // mode 0: physical (v, sigma_bar); 1: U
 __global__ __launch_bounds__(BT) void k_batch_moments(const float* __restrict__ pool,
                                                       float* __restrict__ out,
                                                       const InstDesc* __restrict__ descs, int n,
-                                                      int64_t total, int mode) {
-  const int64_t node = (int64_t)blockIdx.x * BT + threadIdx.x;
-  if (node >= total) return;
-  const InstDesc& d = descs[find_instance(descs, n, node)];
-  const int64_t loc = node - d.node0;
-  const int64_t ni = (int64_t)d.g.nx * d.g.ny;
-  const int y = (int)(loc / d.g.nx), x = (int)(loc - (int64_t)y * d.g.nx);
-  const float* src = pool + d.off;
-  float f[NQ][NC], U[NC];
-  for (int q = 0; q < NQ; ++q)
-    for (int c = 0; c < NC; ++c) f[q][c] = src[pidx(d.g, q * NC + c, y, x)];
-  moment0(f, U);  // the single lattice's summation order
-  float* o = out + 5 * d.node0 + loc;
-  if (mode == 1) {
-    for (int c = 0; c < NC; ++c) o[c * ni] = U[c];
-    return;
-  }
-  o[0] = U[0];
-  o[ni] = U[1];
-  o[2 * ni] = -d.rho * (d.cK * U[2] + d.cmu * U[3]);
-  o[3 * ni] = -d.rho * (d.cK * U[2] - d.cmu * U[3]);
-  o[4 * ni] = -d.rho * (d.cmu * U[4]);
+                                                      int mode) {
+  for_block_instances(descs, n, [&](const InstDesc& d, int x, int y) {
+    const int64_t ni = (int64_t)d.g.nx * d.g.ny;
+    const float* src = pool + d.off;
+    float f[NQ][NC], U[NC];
+    for (int q = 0; q < NQ; ++q)
+      for (int c = 0; c < NC; ++c) f[q][c] = src[pidx(d.g, q * NC + c, y, x)];
+    moment0(f, U);  // the single lattice's summation order
+    float* o = out + 5 * d.node0 + (int64_t)y * d.g.nx + x;
+    if (mode == 1) {
+      for (int c = 0; c < NC; ++c) o[c * ni] = U[c];
+      return;
+    }
+    o[0] = U[0];
+    o[ni] = U[1];
+    o[2 * ni] = -d.rho * (d.cK * U[2] + d.cmu * U[3]);
+    o[3 * ni] = -d.rho * (d.cK * U[2] - d.cmu * U[3]);
+    o[4 * ni] = -d.rho * (d.cmu * U[4]);
+  });
 }
 
 __device__ inline double wg_sum(double v, double* sh) {
@@ -384,7 +398,7 @@ lbm_status plan(int32_t n, const lbm_params* params, Layout* L) {
     d.cK = (float)dv.cK;
     d.cmu = (float)dv.cmu;
     d.rho = (float)params[i].rho;
-    d.ic = InitConst{dv.kK, dv.km, dv.cK, dv.cmu, params[i].rho, params[i].dx, params[i].bc};
+    d.ic = init_const(dv.kK, dv.km, dv.cK, dv.cmu, params[i].rho, params[i].dx, params[i].bc);
     if (!norm_weights(dv.kK, dv.km, d.kw)) return fail(LBM_E_CFL, "g_ij not positive definite");
     if (d.bc == LBM_DIRICHLET) {
       const int links = 2 * (d.g.nx + d.g.ny);
@@ -746,11 +760,11 @@ static lbm_status batch_init_any(lbm_batch* b, const void* v0, const void* s0, i
   if (f32)
     hipLaunchKernelGGL(k_batch_init<float>, dim3(grid), dim3(BT), 0, b->stream,
                        (const float*)v0, (const float*)s0, packed, b->pool[0],
-                       (const InstDesc*)b->d_desc, b->n, total);
+                       (const InstDesc*)b->d_desc, b->n);
   else
     hipLaunchKernelGGL(k_batch_init<double>, dim3(grid), dim3(BT), 0, b->stream,
                        (const double*)v0, (const double*)s0, packed, b->pool[0],
-                       (const InstDesc*)b->d_desc, b->n, total);
+                       (const InstDesc*)b->d_desc, b->n);
   lbm_status s = launch_check("batch init launch");
   if (s) return s;
   b->cur = 0;
@@ -927,7 +941,7 @@ static lbm_status batch_moments(lbm_batch* b, float* out, int mode) {
   const int64_t total = b->L.total_nodes;
   hipLaunchKernelGGL(k_batch_moments, dim3((unsigned)((total + BT - 1) / BT)), dim3(BT), 0,
                      b->stream, (const float*)b->pool[b->cur], out, (const InstDesc*)b->d_desc,
-                     b->n, total, mode);
+                     b->n, mode);
   return launch_check("batch moments launch");
 }
 

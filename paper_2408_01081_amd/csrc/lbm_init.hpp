@@ -17,10 +17,18 @@ constexpr int INIT_FROM_STRESS = 0;
 constexpr int INIT_FROM_GRADIENT = 1;
 
 struct InitConst {
-  double kK, km, cK, cmu, rho, dx;
+  double kK, km, cK, cmu, dx;
+  // Cauchy stress -> j (inverse of Eq. sigma_num): 1 / (2 rho c_K),
+  // 1 / (2 rho c_mu), 1 / (rho c_mu) (the last two unused for c_mu = 0, which
+  // starts from the displacement gradient)
+  double js, jd, jxy;
   int bc;
-  int src = INIT_FROM_STRESS;
 };
+
+inline InitConst init_const(double kK, double km, double cK, double cmu, double rho, double dx,
+                            int bc) {
+  return InitConst{kK, km, cK, cmu, dx, 0.5 / (rho * cK), 0.5 / (rho * cmu), 1.0 / (rho * cmu), bc};
+}
 
 // Phi_x(V)/c and Phi_y(V)/c in double precision
 __device__ inline void flux_x(const InitConst& k, const double V[NC], double o[NC]) {
@@ -41,19 +49,13 @@ __device__ inline void flux_y(const InitConst& k, const double V[NC], double o[N
 // U = (v, j) from velocity and Cauchy stress at a node (inverse of Eq. sigma_num)
 __device__ inline void to_U(const InitConst& k, double vx, double vy, double sxx, double syy,
                             double sxy, double U[NC]) {
-  const double r = 1.0 / k.rho;
   U[0] = vx;
   U[1] = vy;
-  U[2] = -(sxx + syy) * r / (2.0 * k.cK);
-  U[3] = -(sxx - syy) * r / (2.0 * k.cmu);
-  U[4] = -sxy * r / k.cmu;
+  U[2] = -k.js * (sxx + syy);
+  U[3] = -k.jd * (sxx - syy);
+  U[4] = -k.jxy * sxy;
 }
 
-// U0 at a node from the initial data: with INIT_FROM_STRESS s0 is the Cauchy
-// stress [3][ny][nx]; with INIT_FROM_GRADIENT it is the displacement
-// gradient [4][ny][nx] (du_x/dx, du_x/dy, du_y/dx, du_y/dy) and U0 follows
-// Eq. ic_vector directly, j = -c (derivatives of u0), with no division by
-// c_mu (so c_mu = 0 is allowed)
 // Eq. ic_vector: U from v and the displacement gradient (uxx = du_x/dx,
 // uxy = du_x/dy, uyx = du_y/dx, uyy = du_y/dy); linear, so it also maps
 // derivatives of these fields to derivatives of U
@@ -66,50 +68,56 @@ __device__ inline void from_gradient(const InitConst& k, double vx, double vy, d
   U[4] = -k.cmu * (uyx + uxy);
 }
 
-template <typename T>
-__device__ inline void node_U(const InitConst& k, const T* v0, const T* s0, int64_t n, int64_t id,
-                              double U[NC]) {
-  if (k.src == INIT_FROM_GRADIENT) {
-    from_gradient(k, v0[id], v0[n + id], s0[id], s0[n + id], s0[2 * n + id], s0[3 * n + id], U);
-    return;
-  }
-  to_U(k, (double)v0[id], (double)v0[n + id], (double)s0[id], (double)s0[n + id],
-       (double)s0[2 * n + id], U);
+// The initial data of a node: v0 and, with SRC = INIT_FROM_STRESS, the Cauchy
+// stress [3][ny][nx], with INIT_FROM_GRADIENT the displacement gradient
+// [4][ny][nx] (du_x/dx, du_x/dy, du_y/dx, du_y/dy)
+constexpr int NRAW = 6;
+
+template <int SRC, typename T>
+__device__ inline void load_raw(const T* __restrict__ v0, const T* __restrict__ s0, int64_t n,
+                                int64_t id, double r[NRAW]) {
+  r[0] = (double)v0[id];
+  r[1] = (double)v0[n + id];
+  r[2] = (double)s0[id];
+  r[3] = (double)s0[n + id];
+  r[4] = (double)s0[2 * n + id];
+  r[5] = SRC == INIT_FROM_GRADIENT ? (double)s0[3 * n + id] : 0.0;
 }
 
-// lattice derivative dx * dU/dx along one axis by central differences
-template <typename T>
-__device__ inline void lattice_grad(const InitConst& k, const T* v0, const T* s0,
-                                    int nx, int ny, int x, int y, int axis, double G[NC]) {
-  const int64_t n = (int64_t)nx * ny;
-  const int m = axis == 0 ? x : y, len = axis == 0 ? nx : ny;
-  auto id_of = [&](int mm) -> int64_t {
-    return axis == 0 ? (int64_t)y * nx + mm : (int64_t)mm * nx + x;
-  };
-  double A[NC], B[NC], C[NC];
-  if (len == 1) {
-    for (int c = 0; c < NC; ++c) G[c] = 0.0;
-    return;
-  }
-  if (k.bc == LBM_PERIODIC || (m > 0 && m < len - 1)) {
-    const int mp = m + 1 == len ? 0 : m + 1, mm = m == 0 ? len - 1 : m - 1;
-    node_U(k, v0, s0, n, id_of(mp), A);
-    node_U(k, v0, s0, n, id_of(mm), B);
-    for (int c = 0; c < NC; ++c) G[c] = 0.5 * (A[c] - B[c]);
-    return;
-  }
-  if (len == 2) {
-    node_U(k, v0, s0, n, id_of(1), A);
-    node_U(k, v0, s0, n, id_of(0), B);
-    for (int c = 0; c < NC; ++c) G[c] = A[c] - B[c];
-    return;
-  }
-  // one-sided second order at a wall
-  const int s = m == 0 ? 1 : -1;
-  node_U(k, v0, s0, n, id_of(m), A);
-  node_U(k, v0, s0, n, id_of(m + s), B);
-  node_U(k, v0, s0, n, id_of(m + 2 * s), C);
-  for (int c = 0; c < NC; ++c) G[c] = s * 0.5 * (-3.0 * A[c] + 4.0 * B[c] - C[c]);
+// U0 from those data.  Linear, so it also maps their derivatives to those of
+// U0.  The gradient route (j = -c (derivatives of u0)) divides by no c_mu, so
+// c_mu = 0 is allowed there.
+template <int SRC>
+__device__ inline void raw_U(const InitConst& k, const double r[NRAW], double U[NC]) {
+  if (SRC == INIT_FROM_GRADIENT)
+    from_gradient(k, r[0], r[1], r[2], r[3], r[4], r[5], U);
+  else
+    to_U(k, r[0], r[1], r[2], r[3], r[4], U);
+}
+
+// Lattice derivative (dx d/dx) at position m of an axis of n nodes as
+// wa F[a] + wb F[b] + wm F[m]: central differences, at walls the one-sided
+// second-order formula (first order on two nodes, zero on one).  The weights
+// are selected, not branched on, so that a node's loads along both axes are
+// all in flight together.
+struct Diff {
+  int a, b;
+  double wa, wb, wm;
+};
+
+__device__ inline Diff lattice_diff(int bc, int m, int n) {
+  Diff d;
+  const bool lo = m == 0, hi = m == n - 1;
+  const bool wall = bc != LBM_PERIODIC && (lo || hi);
+  const double s = lo ? 1.0 : -1.0;  // inward
+  const int i = lo ? 1 : -1;
+  if (n < 2) return Diff{m, m, 0.0, 0.0, 0.0};
+  d.a = wall ? m + i : (hi ? 0 : m + 1);
+  d.b = wall ? (n == 2 ? m : m + 2 * i) : (lo ? n - 1 : m - 1);
+  d.wa = wall ? (n == 2 ? s : 2.0 * s) : 0.5;
+  d.wb = wall ? (n == 2 ? 0.0 : -0.5 * s) : -0.5;
+  d.wm = wall ? (n == 2 ? -s : -1.5 * s) : 0.0;
+  return d;
 }
 
 // B_hat(x, y, t_0) = (dt / rho) b_bar in FP64 from the separable tables (zero
@@ -128,86 +136,106 @@ __device__ inline void body_hat0(const Force& F, int x, int y, double& bx, doubl
 
 // Populations f*(0) of one node (x, y): Eq. ic_second in FP64 followed by the
 // first omega = 2 collision, rounded once to FP32.  v0 [2][ny][nx] and s0
-// (Cauchy stress [3][ny][nx], or the displacement gradient [4][ny][nx] with
-// INIT_FROM_GRADIENT) are the instance's fields (double or float); grad is
-// nullable FP64 physical derivatives d/dx, d/dy of the input fields:
-// [2][5][ny][nx] of (v, sigma_bar), or [2][6][ny][nx] of (v, grad u0) with
-// INIT_FROM_GRADIENT; F the body load at t_0 (rank 0: none).
-template <typename T>
+// (load_raw) are the instance's fields (double or float); grad is nullable
+// FP64 physical derivatives d/dx, d/dy of the input fields: [2][5][ny][nx] of
+// (v, sigma_bar), or [2][6][ny][nx] of (v, grad u0) with INIT_FROM_GRADIENT;
+// F the body load at t_0 (rank 0: none).
+//
+// Eq. ic_second in lattice units (c dt = dx absorbed into UX, UY) is
+//   f_q = 1/4 [U + 2 C_q U]
+//     - 1/8 { B + 2 C_q B + i UX + (2i^2-1) X(UX) - 2 C_q X(UX)
+//             + j UY + (2j^2-1) Y(UY) - 2 C_q Y(UY) },  B = (B_hat_x, B_hat_y, 0, 0, 0),
+// whose sum is U - B/2, so the first collision's U_num is U.  With
+// P = X(UX) - Y(UY), S = X(UX) + Y(UY) (X and Y linear, C_q = i X + j Y) the
+// collided populations f* = U/2 + C_q U - f pair up by axis:
+//   f*_(+-1,0) = U/4 + (B + P)/8 +- [X(U)/2 + (2 X(B) + UX - 2 X(S))/8],
+//   f*_(0,+-1) = U/4 + (B - P)/8 +- [Y(U)/2 + (2 Y(B) + UY - 2 Y(S))/8].
+// The pass is bound by memory (120 B per node).  Written out per direction,
+// with FP64 divisions in the conversion of all five nodes and its loads behind
+// the branches of the boundary rule, it took 789 us on 4096 x 4096 and 92 us
+// on 2048 x 1024; in this form with plain stores 536 and 38 us, with
+// nontemporal ones (the state is not read back before the whole pass has
+// ended) 515 and 37 us (3.9 and 6.9 TB/s).
+template <int SRC, typename T>
 __device__ inline void init_node(const T* __restrict__ v0, const T* __restrict__ s0,
                                  const double* __restrict__ grad, float* __restrict__ dst,
                                  const Grid& g, const InitConst& k, int x, int y,
                                  const Force& F = Force{}) {
   const int64_t n = (int64_t)g.nx * g.ny;
   const int64_t id = (int64_t)y * g.nx + x;
-  double U[NC], UX[NC], UY[NC];
-  node_U(k, v0, s0, n, id, U);
+  double U[NC], UX[NC], UY[NC], r[NRAW];
   if (grad) {
     // physical derivatives of the input fields -> lattice derivatives of U
-    if (k.src == INIT_FROM_GRADIENT) {
-      const double* gx = grad;
-      const double* gy = grad + 6 * n;
-      from_gradient(k, gx[id], gx[n + id], gx[2 * n + id], gx[3 * n + id], gx[4 * n + id],
-                    gx[5 * n + id], UX);
-      from_gradient(k, gy[id], gy[n + id], gy[2 * n + id], gy[3 * n + id], gy[4 * n + id],
-                    gy[5 * n + id], UY);
-    } else {
-      const double* gx = grad;
-      const double* gy = grad + 5 * n;
-      to_U(k, gx[id], gx[n + id], gx[2 * n + id], gx[3 * n + id], gx[4 * n + id], UX);
-      to_U(k, gy[id], gy[n + id], gy[2 * n + id], gy[3 * n + id], gy[4 * n + id], UY);
-    }
+    load_raw<SRC>(v0, s0, n, id, r);
+    raw_U<SRC>(k, r, U);
+    constexpr int nf = SRC == INIT_FROM_GRADIENT ? 6 : 5;
+    load_raw<SRC>(grad, grad + 2 * n, n, id, r);
+    raw_U<SRC>(k, r, UX);
+    load_raw<SRC>(grad + nf * n, grad + (nf + 2) * n, n, id, r);
+    raw_U<SRC>(k, r, UY);
     for (int c = 0; c < NC; ++c) {
       UX[c] *= k.dx;
       UY[c] *= k.dx;
     }
   } else {
-    lattice_grad(k, v0, s0, g.nx, g.ny, x, y, 0, UX);
-    lattice_grad(k, v0, s0, g.nx, g.ny, x, y, 1, UY);
+    const Diff dx = lattice_diff(k.bc, x, g.nx), dy = lattice_diff(k.bc, y, g.ny);
+    const int64_t row = (int64_t)y * g.nx;
+    double xa[NRAW], xb[NRAW], ya[NRAW], yb[NRAW];
+    load_raw<SRC>(v0, s0, n, id, r);
+    load_raw<SRC>(v0, s0, n, row + dx.a, xa);
+    load_raw<SRC>(v0, s0, n, row + dx.b, xb);
+    load_raw<SRC>(v0, s0, n, (int64_t)dy.a * g.nx + x, ya);
+    load_raw<SRC>(v0, s0, n, (int64_t)dy.b * g.nx + x, yb);
+    for (int c = 0; c < NRAW; ++c) {
+      xa[c] = fma(dx.wa, xa[c], fma(dx.wb, xb[c], dx.wm * r[c]));
+      ya[c] = fma(dy.wa, ya[c], fma(dy.wb, yb[c], dy.wm * r[c]));
+    }
+    raw_U<SRC>(k, r, U);
+    raw_U<SRC>(k, xa, UX);
+    raw_U<SRC>(k, ya, UY);
   }
-
-  // Eq. ic_second in lattice units (c dt = dx absorbed into UX, UY):
-  // f_q = 1/4 [U + 2 C_q U]
-  //   - 1/8 { B + 2 C_q B + i UX + (2i^2-1) X(UX) - 2 C_q X(UX)
-  //           + j UY + (2j^2-1) Y(UY) - 2 C_q Y(UY) },  B = (B_hat_x, B_hat_y, 0, 0, 0)
-  double Bh[NC] = {0.0, 0.0, 0.0, 0.0, 0.0}, XB[NC], YB[NC];
-  if (F.rank > 0) body_hat0(F, x, y, Bh[0], Bh[1]);
-  flux_x(k, Bh, XB);
-  flux_y(k, Bh, YB);
-  double XU[NC], YU[NC], XUX[NC], YUY[NC], XXUX[NC], YXUX[NC], XYUY[NC], YYUY[NC];
-  flux_x(k, U, XU);
-  flux_y(k, U, YU);
+  double XUX[NC], YUY[NC], P[NC], S[NC], A[NC], B[NC], o[NC];
   flux_x(k, UX, XUX);
   flux_y(k, UY, YUY);
-  flux_x(k, XUX, XXUX);
-  flux_y(k, XUX, YXUX);
-  flux_x(k, YUY, XYUY);
-  flux_y(k, YUY, YYUY);
-  const int I[NQ] = {1, 0, -1, 0}, J[NQ] = {0, 1, 0, -1};
-  double f[NQ][NC];
-  for (int q = 0; q < NQ; ++q) {
-    const double i = I[q], j = J[q];
-    for (int c = 0; c < NC; ++c) {
-      const double eq = 0.25 * (U[c] + 2.0 * (i * XU[c] + j * YU[c]));
-      const double cb = Bh[c] + 2.0 * (i * XB[c] + j * YB[c]);
-      const double cx = i * UX[c] + (2.0 * i * i - 1.0) * XUX[c] - 2.0 * (i * XXUX[c] + j * YXUX[c]);
-      const double cy = j * UY[c] + (2.0 * j * j - 1.0) * YUY[c] - 2.0 * (i * XYUY[c] + j * YYUY[c]);
-      f[q][c] = eq - 0.125 * (cb + cx + cy);
-    }
+  for (int c = 0; c < NC; ++c) {
+    P[c] = XUX[c] - YUY[c];
+    S[c] = XUX[c] + YUY[c];
   }
-  // first collision in FP64 (omega = 2): f* = 2 f_eq(U_num) - f, U_num = sum f
-  double Un[NC], Xn[NC], Yn[NC];
-  for (int c = 0; c < NC; ++c) Un[c] = (f[0][c] + f[1][c]) + (f[2][c] + f[3][c]) + 0.5 * Bh[c];
-  flux_x(k, Un, Xn);
-  flux_y(k, Un, Yn);
-  for (int q = 0; q < NQ; ++q) {
-    const double i = I[q], j = J[q];
-    for (int c = 0; c < NC; ++c) {
-      const double fs = 0.5 * Un[c] + (i * Xn[c] + j * Yn[c]) - f[q][c];
-      dst[pidx(g, q * NC + c, y, x)] = (float)fs;
-    }
+  double Bh[NC] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (F.rank > 0) body_hat0(F, x, y, Bh[0], Bh[1]);
+  // odd parts: X(U)/2 + (2 X(B) + UX - 2 X(S))/8 = X(U/2 + B/4 - S/4) + UX/8
+  for (int c = 0; c < NC; ++c) o[c] = fma(0.25, Bh[c] - S[c], 0.5 * U[c]);
+  flux_x(k, o, A);
+  flux_y(k, o, B);
+  for (int c = 0; c < NC; ++c) {
+    const double e = fma(0.125, Bh[c], 0.25 * U[c]);
+    const double ex = fma(0.125, P[c], e), ey = fma(-0.125, P[c], e);
+    const double ox = fma(0.125, UX[c], A[c]), oy = fma(0.125, UY[c], B[c]);
+    __builtin_nontemporal_store((float)(ex + ox), dst + pidx(g, 0 * NC + c, y, x));
+    __builtin_nontemporal_store((float)(ey + oy), dst + pidx(g, 1 * NC + c, y, x));
+    __builtin_nontemporal_store((float)(ex - ox), dst + pidx(g, 2 * NC + c, y, x));
+    __builtin_nontemporal_store((float)(ey - oy), dst + pidx(g, 3 * NC + c, y, x));
   }
 }
 
+// A workgroup of 256 threads covers a tile of 64 columns x 4 rows (one wave
+// per row): a node's y neighbours are mostly another wave's row of the same
+// tile, and finding (x, y) takes no 64-bit division per thread.
+constexpr int FT_X = 64, FT_Y = 4;
+
+inline int field_tiles(const Grid& g) {
+  return ((g.nx + FT_X - 1) / FT_X) * ((g.ny + FT_Y - 1) / FT_Y);
+}
+
+// node (x, y) of this thread; false beyond the grid
+__device__ inline bool field_node(const Grid& g, int& x, int& y) {
+  const int tx = (g.nx + FT_X - 1) / FT_X, ty = (g.ny + FT_Y - 1) / FT_Y;
+  const int tile = xcd_tile(blockIdx.x, tx * ty);
+  const int ry = tile / tx;
+  x = (tile - ry * tx) * FT_X + (int)(threadIdx.x & 63);
+  // (one row per wave: uniform, so row addresses are formed in scalar registers)
+  y = ry * FT_Y + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return x < g.nx && y < g.ny;
+}
 
 }  // namespace lbmk
