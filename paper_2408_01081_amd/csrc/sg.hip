@@ -488,14 +488,30 @@ void launch_conv_shape(int k, sg_net* n, const Tensor& x, const float* xscale,
   }
 }
 
-template <int SPLIT, int PB, int NB, bool WL, int WT, int RW = 64 / WT>
+template <int SPLIT, int PB, int NB, bool WL, int WT>
 void launch_convt(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
-  constexpr int CT = (4 / (RW * WT / (16 * PB))) * 16 * NB;
-  dim3 grid((unsigned)((int64_t)n->B * x.H * x.W / (RW * WT)), (unsigned)(cout / CT));
-  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WL, WT, RW>), grid, dim3(256), 0, n->stream,
+  constexpr int CT = PB * 16 * NB;
+  dim3 grid((unsigned)((int64_t)n->B * x.H * x.W / 64), (unsigned)(cout / CT));
+  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WL, WT>), grid, dim3(256), 0, n->stream,
                      (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout, n->circular,
                      accumulate);
+}
+
+// k_convw where it has a workgroup for every CU (256 pixels x 32 channels
+// each); two workgroups share a CU, each running through its share.  With
+// fewer, the 64-pixel tiles of k_convt spread the layer over more CUs (256 x
+// 256, batch 1: 9.2 us against 11.9 for a layer of 32 channels, 256
+// workgroups; 128 x 128, 64 channels, has 128).
+template <int SPLIT, int WT>
+bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
+               const unsigned short* wl, Tensor& z, int cin, int cout) {
+  const int64_t work = (int64_t)n->B * x.H * x.W / 256 * (cout / 32);
+  if (x.W % WT || x.H % (256 / WT) || work < 256) return false;
+  hipLaunchKernelGGL((k_convw<SPLIT, WT>), dim3((unsigned)(work < 512 ? work : 512)), dim3(256), 0,
+                     n->stream, (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout,
+                     n->circular, (int)work);
+  return true;
 }
 
 // The LDS-tiled kernel where the row is a multiple of 64 pixels or 32 or 16
@@ -507,18 +523,6 @@ template <int SPLIT, int WT>
 void conv_tiled_w(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
   const int64_t tiles = (int64_t)n->B * x.H * x.W / 64;
-  // blocks of 4 rows x 64 pixels (one wave per row, 32 output channels)
-  // where they still give 256 workgroups: the halo rows (and the weights)
-  // are staged once for 4x as many pixels
-  if (WT == 64 && n->conv_mode != 2 && x.H % 4 == 0 && tiles / 4 * (cout / 32) >= 256) {
-    // weights read from L2 rather than staged, so that two workgroups share
-    // a CU, where the grid has more than one per CU
-    if (tiles / 4 * (cout / 32) >= 512)
-      launch_convt<SPLIT, 4, 2, false, 64, 4>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
-    else
-      launch_convt<SPLIT, 4, 2, true, 64, 4>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
-    return;
-  }
   if (cout % 64 == 0 && tiles * (cout / 64) >= 512)
     launch_convt<SPLIT, 2, 2, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else if (tiles * (cout / 32) < 256 && n->conv_mode == 2)
@@ -539,6 +543,10 @@ bool conv_tiled(sg_net* n, const Tensor& x, const float* xscale, const unsigned 
   // too few workgroups to fill the chip even with 16 output channels per
   // workgroup: the direct kernel splits the reduction over waves instead
   if ((int64_t)n->B * x.H * x.W / 64 * (cout / 16) < 256) return false;
+  if (n->conv_mode == 0 && !accumulate &&
+      (conv_wide<SPLIT, 32>(n, x, xscale, wh, wl, z, cin, cout) ||
+       conv_wide<SPLIT, 16>(n, x, xscale, wh, wl, z, cin, cout)))
+    return true;
   if (x.W % 64 == 0)
     conv_tiled_w<SPLIT, 64>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else if (x.W == 32)

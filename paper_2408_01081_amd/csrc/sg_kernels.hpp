@@ -40,24 +40,44 @@ __device__ inline bf16 as_bf16(unsigned short b) {
   return r;
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// two FP32 values rounded to nearest even to BF16 in one conversion
+// instruction (v_cvt_pk_bf16_f32), a0 in the low half; bitwise bf16_bits for
+// every finite input, subnormal ones included
+__device__ __forceinline__ uint32_t bf16_pair(float a0, float a1) {
+  const f32x2 v = {a0, a1};
+  const bf16x2 h = __builtin_convertvector(v, bf16x2);
+  uint32_t u;
+  __builtin_memcpy(&u, &h, 4);
+  return u;
+}
+// the pair's values (exact)
+__device__ __forceinline__ float pair_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float pair_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
+
+// BF16 hi and (SPLIT = 3) lo parts of 8 values: hi = bf16(a), lo = bf16(a - hi)
+template <int SPLIT>
+__device__ __forceinline__ void split_pairs(const float (&a)[8], uint32_t (&h)[4],
+                                            uint32_t (&l)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    h[j] = bf16_pair(a[2 * j], a[2 * j + 1]);
+    l[j] = SPLIT == 3 ? bf16_pair(a[2 * j] - pair_lo(h[j]), a[2 * j + 1] - pair_hi(h[j])) : 0u;
+  }
+}
+
 // BF16 hi (and, SPLIT = 3, lo) parts of 8 activations times their gains,
 // rounded to nearest even (a zero activation gives zero parts)
 template <int SPLIT>
 __device__ __forceinline__ void split8(const float (&x)[8], const float (&s)[8], bool scaled,
                                        bf16x8& hi, bf16x8& lo) {
-  uint32_t h[4], l[4] = {0u, 0u, 0u, 0u};
+  float a[8];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float a0 = scaled ? x[2 * j] * s[2 * j] : x[2 * j];
-    const float a1 = scaled ? x[2 * j + 1] * s[2 * j + 1] : x[2 * j + 1];
-    const unsigned short h0 = bf16_bits(a0), h1 = bf16_bits(a1);
-    h[j] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-    if (SPLIT == 3) {
-      const unsigned short l0 = bf16_bits(a0 - bf16_value(h0));
-      const unsigned short l1 = bf16_bits(a1 - bf16_value(h1));
-      l[j] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-    }
-  }
+  for (int j = 0; j < 8; ++j) a[j] = scaled ? x[j] * s[j] : x[j];
+  uint32_t h[4], l[4];
+  split_pairs<SPLIT>(a, h, l);
   __builtin_memcpy(&hi, h, 16);
   __builtin_memcpy(&lo, l, 16);
 }
@@ -193,7 +213,7 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ X,
 // ---------------------------------------------------------------------------
 // The same convolution with the input tile staged in LDS.  A workgroup computes
 // a block of RW rows x WT pixels of one image (WT = 64 with W % 64 == 0, or
-// WT = W = 32 or 16; RW * WT = 64 or 256) x CT output channels; for every
+// WT = W = 32 or 16; RW * WT = 64) x CT output channels; for every
 // 32-channel chunk of the input the neighbourhood of those pixels (one pixel
 // more on every side) is read from the FP32 activations, multiplied by the gain and
 // split into BF16 hi and lo parts exactly as split8 does, and stored in
@@ -204,7 +224,7 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ X,
 // blocks), so the two give bitwise identical results.  Cin % 32 == 0,
 // Cout % CT == 0.
 // ---------------------------------------------------------------------------
-template <int SPLIT, int PB, int NB, bool WL = false, int WT = 64, int RW = 64 / WT>
+template <int SPLIT, int PB, int NB, bool WL, int WT>
 __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
                                                const float* __restrict__ xscale,
                                                const unsigned short* __restrict__ Whi,
@@ -212,7 +232,7 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
                                                float* __restrict__ Z, int H, int W, int Cin,
                                                int Cout, int circular, int accumulate) {
   // the workgroup's pixels: RW rows of WT pixels (WT = 64 for W >= 64, else W)
-  constexpr int NPX = RW * WT;
+  constexpr int RW = 64 / WT, NPX = RW * WT;
   constexpr int WPX = NPX / (16 * PB);  // waves along the pixels
   constexpr int WCO = 4 / WPX;          // waves along the output channels
   static_assert(WPX * WCO == 4 && NPX % (16 * PB) == 0, "four waves per workgroup");
@@ -320,16 +340,7 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
           for (int j = 0; j < 8; ++j) a[j] *= sc[j];
         }
         uint32_t h[4], l[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const unsigned short h0 = bf16_bits(a[2 * j]), h1 = bf16_bits(a[2 * j + 1]);
-          h[j] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-          if (SPLIT == 3) {
-            const unsigned short l0 = bf16_bits(a[2 * j] - bf16_value(h0));
-            const unsigned short l1 = bf16_bits(a[2 * j + 1] - bf16_value(h1));
-            l[j] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-          }
-        }
+        split_pairs<SPLIT>(a, h, l);
         vh = (uint4){h[0], h[1], h[2], h[3]};
         if (SPLIT == 3) vl = (uint4){l[0], l[1], l[2], l[3]};
       }
@@ -398,6 +409,237 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
         float* zp = Z + pix * Cout + co0 + 16 * nb + m;
         *zp = accumulate ? *zp + acc[pb][nb][j] : acc[pb][nb][j];
       }
+}
+
+// ---------------------------------------------------------------------------
+// The same convolution for layers with many pixels: a workgroup computes RW x
+// WT = 256 pixels x CT = 32 output channels, each of its 4 waves 4 rows of 16
+// pixels x all CT channels, so that a weight fragment read from LDS feeds 64
+// pixels and a pixel fragment CT channels of up to three taps.  Input tile
+// and weights of a 32-channel chunk (9 taps x CT channels) are both in LDS,
+// 16 dwords per pixel and per channel row, whose 16-byte pieces are rotated
+// by the row (swz) so that fragment reads meet no bank conflicts without
+// padding: 80 KB, so two workgroups share a CU and one's staging runs beside
+// the other's products.  Workgroups run through their tiles (tile, chunk) by
+// (tile, chunk): the next chunk's or tile's loads are in registers while this
+// one's products run, and with one chunk and Cout = CT the weights are staged
+// once per workgroup.  The weights are the A operand, so a lane ends up with
+// 4 consecutive channels of a pixel and stores 16 bytes.  Cin % 32 == 0,
+// Cout % CT == 0, H % RW == 0, W % WT == 0.
+// Bound by the matrix cores: a layer of 29 GFLOP in three passes (batch 32,
+// 128 x 128: 32 channels at full, 64 at half, 128 at quarter resolution)
+// takes 33.7 us, 860 TFLOP/s; k_convt took 58, 52 and 77.  Measured on the
+// way: one workgroup of 4 waves x 64 channels per CU 37.5 us (its waves stage,
+// wait and multiply one after the other), 8 waves on 512 pixels 39.5 us.
+// ---------------------------------------------------------------------------
+// dword of 16-byte piece q of staged row p
+__device__ __forceinline__ int swz(int p, int q) { return 16 * p + 4 * (q ^ ((p >> 1) & 3)); }
+
+template <int SPLIT, int WT>
+__global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
+                                                  const float* __restrict__ xscale,
+                                                  const unsigned short* __restrict__ Whi,
+                                                  const unsigned short* __restrict__ Wlo,
+                                                  float* __restrict__ Z, int H, int W, int Cin,
+                                                  int Cout, int circular, int nwork) {
+  constexpr int NB = 2, CT = 16 * NB;
+  constexpr int RW = 256 / WT;  // rows of a tile
+  constexpr int TR = RW + 2, TW = WT + 2;
+  constexpr int NH = SPLIT == 3 ? 2 : 1;
+  constexpr int XS = TR * TW * 16, WS = 9 * CT * 16;  // dwords per hi/lo part
+  __shared__ uint4 lds4[NH * (XS + WS) / 4];
+  uint32_t* tile = reinterpret_cast<uint32_t*>(lds4);
+  uint32_t* wtile = tile + NH * XS;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int m = lane & 15, kq = lane >> 4;
+  const int q = threadIdx.x & 3;
+  // the wave's pixels: 4 rows of 16, from (wx, wy) of the tile
+  const int wx = 16 * (wave % (WT / 16)), wy = 4 * (wave / (WT / 16));
+
+  // work items (pixel tile, channel block) in runs per XCD, whose L2 then
+  // serves the halo rows and the channel blocks of a pixel tile
+  const int ncb = Cout / CT, tx = W / WT, tiles = (H / RW) * tx;
+  const int xcd = blockIdx.x & 7, nq = nwork >> 3, nr = nwork & 7;
+  const int first = xcd * nq + (xcd < nr ? xcd : nr), count = nq + (xcd < nr ? 1 : 0);
+  const int stride = (gridDim.x + 7 - xcd) >> 3;  // workgroups of this XCD's run
+  const bool keep_w = Cin == 32 && ncb == 1;
+
+  constexpr int NTILE = TR * TW * 4, PER = (NTILE + 255) / 256;
+  constexpr int NWT = 9 * CT * 4, PERW = (NWT + 255) / 256;
+  int off[PER];   // each staged piece's place in the image, in pieces of 8 channels
+  uint32_t live;  // bit k: piece k is inside the image (else zero)
+  float u[PER][8];
+  float sc[8];
+  uint32_t wh[PERW][4], wl[SPLIT == 3 ? PERW : 1][4];
+
+  auto place = [&](int item, int& b, int& y, int& x0, int& cb) __attribute__((always_inline)) {
+    const int pt = item / ncb;
+    cb = item - pt * ncb;
+    b = pt / tiles;
+    const int rem = pt - b * tiles;
+    y = (rem / tx) * RW;
+    x0 = (rem - (rem / tx) * tx) * WT;
+  };
+  auto offsets = [&](int y, int x0) __attribute__((always_inline)) {
+    live = 0u;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = (int)threadIdx.x + 256 * k;
+      const int row = (i >> 2) / TW, col = (i >> 2) - row * TW;
+      const int yr = y + row - 1, xr = x0 + col - 1;
+      // wrapped (at most one period; rows past the tile's end too)
+      const int ys = yr < 0 ? yr + H : (yr >= H ? yr - H : yr);
+      const int xs = xr < 0 ? xr + W : (xr >= W ? xr - W : xr);
+      const bool v = i < NTILE && (circular || (ys == yr && xs == xr));
+      live |= v ? 1u << k : 0u;
+      off[k] = v ? (ys * W + xs) * (Cin >> 3) + q : 0;
+    }
+  };
+  auto fetch = [&](int b, int c0) __attribute__((always_inline)) {
+    const float* xb = X + (int64_t)b * H * W * Cin + c0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const float* xp = xb + 8 * (int64_t)off[k];
+      const float4 a = *reinterpret_cast<const float4*>(xp);
+      const float4 c = *reinterpret_cast<const float4*>(xp + 4);
+      u[k][0] = a.x; u[k][1] = a.y; u[k][2] = a.z; u[k][3] = a.w;
+      u[k][4] = c.x; u[k][5] = c.y; u[k][6] = c.z; u[k][7] = c.w;
+    }
+    if (xscale) {
+      const float* sp = xscale + (int64_t)b * Cin + c0 + 8 * q;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sc[j] = sp[j];
+    }
+  };
+  auto fetch_w = [&](int cb, int c0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < PERW; ++k) {
+      const int i = (int)threadIdx.x + 256 * k;
+      if (NWT % 256 == 0 || k + 1 < PERW || i < NWT) {
+        const int co = (i >> 2) % CT, t = (i >> 2) / CT;
+        const int wo = (t * Cout + cb * CT + co) * Cin + c0 + 8 * q;
+        const uint4 a = *reinterpret_cast<const uint4*>(Whi + wo);
+        wh[k][0] = a.x; wh[k][1] = a.y; wh[k][2] = a.z; wh[k][3] = a.w;
+        if (SPLIT == 3) {
+          const uint4 c = *reinterpret_cast<const uint4*>(Wlo + wo);
+          wl[k][0] = c.x; wl[k][1] = c.y; wl[k][2] = c.z; wl[k][3] = c.w;
+        }
+      }
+    }
+  };
+
+  f32x4 acc[4][NB];
+  int k0 = blockIdx.x >> 3;
+  if (k0 >= count) return;  // uniform: the whole workgroup
+  int b, y, x0, cb;
+  place(first + k0, b, y, x0, cb);
+  offsets(y, x0);
+  fetch(b, 0);
+  fetch_w(cb, 0);
+  bool stage_w = true;
+  for (int c0 = 0;;) {
+    // this chunk's operands: registers -> LDS
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = (int)threadIdx.x + 256 * k;
+      if (NTILE % 256 == 0 || k + 1 < PER || i < NTILE) {
+        float a[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          a[j] = xscale ? u[k][j] * sc[j] : u[k][j];
+          a[j] = live >> k & 1 ? a[j] : 0.f;
+        }
+        uint32_t h[4], l[4];
+        split_pairs<SPLIT>(a, h, l);
+        const int d = swz(i >> 2, q);
+        *reinterpret_cast<uint4*>(tile + d) = (uint4){h[0], h[1], h[2], h[3]};
+        if (SPLIT == 3) *reinterpret_cast<uint4*>(tile + XS + d) = (uint4){l[0], l[1], l[2], l[3]};
+      }
+    }
+    if (stage_w) {
+#pragma unroll
+      for (int k = 0; k < PERW; ++k) {
+        const int i = (int)threadIdx.x + 256 * k;
+        if (NWT % 256 == 0 || k + 1 < PERW || i < NWT) {
+          const int d = swz(i >> 2, q);
+          *reinterpret_cast<uint4*>(wtile + d) = (uint4){wh[k][0], wh[k][1], wh[k][2], wh[k][3]};
+          if (SPLIT == 3)
+            *reinterpret_cast<uint4*>(wtile + WS + d) = (uint4){wl[k][0], wl[k][1], wl[k][2], wl[k][3]};
+        }
+      }
+    }
+    if (c0 == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[r][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    // the next chunk, or the first of the next tile, is fetched meanwhile
+    const bool last = c0 + 32 >= Cin;
+    const int kn = last ? k0 + stride : k0, cn = last ? 0 : c0 + 32;
+    const bool more = kn < count;
+    int bn = b, yn = y, xn = x0, cbn = cb;
+    if (more) {
+      if (last) {
+        place(first + kn, bn, yn, xn, cbn);
+        offsets(yn, xn);
+      }
+      fetch(bn, cn);
+      stage_w = !keep_w;
+      if (stage_w) fetch_w(cbn, cn);
+    }
+    __syncthreads();
+    // tap column by tap column: the six row fragments under it serve the
+    // three tap rows of all four pixel rows
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+      bf16x8 xh[6], xl[6];
+#pragma unroll
+      for (int r = 0; r < 6; ++r) {
+        const int d = swz((wy + r) * TW + wx + dx + m, kq);
+        xh[r] = *reinterpret_cast<const bf16x8*>(tile + d);
+        if (SPLIT == 3) xl[r] = *reinterpret_cast<const bf16x8*>(tile + XS + d);
+      }
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const int d = swz((3 * dy + dx) * CT + 16 * nb + m, kq);
+          const bf16x8 ah = *reinterpret_cast<const bf16x8*>(wtile + d);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xh[r + dy], acc[r][nb], 0, 0, 0);
+          if (SPLIT == 3) {
+            const bf16x8 al = *reinterpret_cast<const bf16x8*>(wtile + WS + d);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xl[r + dy], acc[r][nb], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, xh[r + dy], acc[r][nb], 0, 0, 0);
+          }
+        }
+      }
+    }
+    if (last) {
+      // D[row = channel 4 kq + j][col = pixel m]
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float* zp = Z + (((int64_t)b * H + y + wy + r) * W + x0 + wx + m) * Cout + cb * CT + 4 * kq;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4*>(zp + 16 * nb) = acc[r][nb];
+      }
+    }
+    if (!more) return;
+    __syncthreads();  // every wave is done with this chunk's operands
+    k0 = kn;
+    c0 = cn;
+    b = bn;
+    y = yn;
+    x0 = xn;
+    cb = cbn;
+  }
 }
 
 // ---------------------------------------------------------------------------
