@@ -248,52 +248,78 @@ __global__ __launch_bounds__(RT) void k_sum_partials(const double* __restrict__ 
   if (threadIdx.x == 0) *out = s;
 }
 
-// dgamma[b][c] = sum_p g[b,p,c] z[b,p,c] (FiLM gain gradient).
-// Two passes with coalesced reads: workgroup (b, s) takes
-// pixel chunk s of sample b for all C channels (thread t: channel t mod C,
-// every (RT / C)-th pixel), FP64 partial sums per channel added in a fixed
-// order; then dgam[b][c] = sum over the S chunks in order.
+// dgamma[b][c] = sum_p g[b,p,c] z[b,p,c] (FiLM gain gradient), in two passes.
+// First, workgroup (b, s) takes pixel chunk s of sample b for all C channels:
+// a thread 4 consecutive channels of every (4 RT / C)-th pixel, FP64 sums,
+// added per channel in a fixed order.  Bound by memory (both tensors read
+// once): 32 samples of 128 x 128 x 32 channels, 134 MB, took 35 us with one
+// float per load and 16 chunks per sample, 17 with 16-byte loads and 64 (the
+// gradient is still in the last-level cache).
 __global__ __launch_bounds__(RT) void k_film_grad_part(const float* __restrict__ g,
                                                        const float* __restrict__ z, int HW, int C,
                                                        int S, double* __restrict__ part) {
-  __shared__ double sh[RT];
-  const int b = blockIdx.x / S, sidx = blockIdx.x - (blockIdx.x / S) * S;
-  const int G = RT / C, c = threadIdx.x % C, grp = threadIdx.x / C;
-  const int64_t p0 = (int64_t)HW * sidx / S, p1 = (int64_t)HW * (sidx + 1) / S;
-  const float* gp = g + (int64_t)b * HW * C + c;
-  const float* zp = z + (int64_t)b * HW * C + c;
-  double acc = 0.0;
-  if (grp < G)
-    for (int64_t p = p0 + grp; p < p1; p += G) acc += (double)gp[p * C] * zp[p * C];
-  sh[threadIdx.x] = acc;
+  __shared__ double sh[RT][4];
+  const int b = blockIdx.x / S, sidx = blockIdx.x - b * S;
+  const int C4 = C / 4, G = RT / C4, c4 = threadIdx.x % C4, grp = threadIdx.x / C4;
+  const int p0 = (int)((int64_t)HW * sidx / S), p1 = (int)((int64_t)HW * (sidx + 1) / S);
+  const float* gp = g + (int64_t)b * HW * C + 4 * c4;
+  const float* zp = z + (int64_t)b * HW * C + 4 * c4;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int p = p0 + grp; p < p1; p += G) {
+    const float4 x = *reinterpret_cast<const float4*>(gp + (int64_t)p * C);
+    const float4 y = *reinterpret_cast<const float4*>(zp + (int64_t)p * C);
+    acc[0] += (double)x.x * y.x;
+    acc[1] += (double)x.y * y.y;
+    acc[2] += (double)x.z * y.z;
+    acc[3] += (double)x.w * y.w;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) sh[threadIdx.x][j] = acc[j];
   __syncthreads();
   if ((int)threadIdx.x < C) {
     double t = 0.0;
-    for (int k = 0; k < G; ++k) t += sh[k * C + threadIdx.x];
+    for (int k = 0; k < G; ++k) t += sh[k * C4 + threadIdx.x / 4][threadIdx.x % 4];
     part[(int64_t)blockIdx.x * C + threadIdx.x] = t;
   }
 }
 
-__global__ __launch_bounds__(RT) void k_film_grad_sum(const double* __restrict__ part, int B,
-                                                      int C, int S, float* __restrict__ dgam) {
-  const int e = blockIdx.x * RT + threadIdx.x;
-  if (e >= B * C) return;
-  const int b = e / C, c = e - b * C;
-  double t = 0.0;
-  for (int k = 0; k < S; ++k) t += part[((int64_t)b * S + k) * C + c];
-  dgam[e] = (float)t;
-}
+// Then, for every layer in one launch, dgamma[b][c] = the sum over the chunks
+// in order and the coefficient gradients da[c][m] = sum_b T[b][m] dgamma[b][c]
+// in order of b.  A workgroup takes 32 channels of one layer, 8 samples at a
+// time.  (As two launches per layer, the second a chain of B dependent reads,
+// they took 250 us of a step.)
+struct FilmArgs {
+  const double* part[NL];  // [b][s][c]
+  float* da[NL];
+  int cout[NL], S[NL];
+};
 
-// da[c][m] = sum_b T[b][m] dgam[b][c]
-__global__ __launch_bounds__(RT) void k_film_coef_grad(const float* __restrict__ dgam,
-                                                       const float* __restrict__ T, int B, int C,
-                                                       float* __restrict__ da) {
-  const int e = blockIdx.x * RT + threadIdx.x;
-  if (e >= C * NBASIS) return;
-  const int c = e / NBASIS, m = e - c * NBASIS;
+__global__ __launch_bounds__(RT) void k_film_grad_coef(FilmArgs a, const float* __restrict__ T,
+                                                       int B) {
+  __shared__ float dg[8][32];
+  int blk = blockIdx.x, l = 0;
+  while (blk >= a.cout[l] / 32) blk -= a.cout[l++] / 32;
+  const int C = a.cout[l], S = a.S[l];
+  const int c = threadIdx.x & 31, bg = threadIdx.x >> 5;
+  const double* part = a.part[l] + 32 * blk + c;
+  const int cc = threadIdx.x / NBASIS, m = threadIdx.x % NBASIS;
   float s = 0.f;
-  for (int b = 0; b < B; ++b) s = fmaf(T[b * NBASIS + m], dgam[b * C + c], s);
-  da[e] = s;
+  for (int b0 = 0; b0 < B; b0 += 8) {
+    const int b = b0 + bg;
+    double t = 0.0;
+    if (b < B) {
+#pragma unroll 16
+      for (int k = 0; k < S; ++k) t += part[((int64_t)b * S + k) * C];
+    }
+    dg[bg][c] = (float)t;
+    __syncthreads();
+    if ((int)threadIdx.x < 32 * NBASIS)
+      for (int k = 0; k < 8 && b0 + k < B; ++k)
+        s = fmaf(T[(b0 + k) * NBASIS + m], dg[k][cc], s);
+    __syncthreads();
+  }
+  if ((int)threadIdx.x < 32 * NBASIS) a.da[l][(32 * blk + cc) * NBASIS + m] = s;
 }
 
 __global__ __launch_bounds__(RT) void k_adam(float* __restrict__ p, const float* __restrict__ g,
@@ -324,11 +350,20 @@ struct Plan {
   int64_t nwq = 0;
   size_t bytes = 0;
   // workspace offsets
-  size_t o_param, o_grad, o_m, o_v, o_wfh, o_wfl, o_wbh, o_wbl, o_s, o_T, o_gam, o_dgam,
+  size_t o_param, o_grad, o_m, o_v, o_wfh, o_wfl, o_wbh, o_wbl, o_s, o_T, o_gam,
       o_part, o_spart, o_loss, o_x0, o_z[NL], o_pool[3], o_up[3], o_g[NL], o_gpool[3], o_gup[3],
-      o_gtmp[2], o_wpart;
+      o_wpart, o_fpart[NL];
   int64_t wpart_floats = 0;
 };
+
+// pixel chunks per sample of the FiLM gradient: about 2048 workgroups, at
+// least 64 pixels each
+constexpr int FILM_WG = 2048;
+int film_chunks(int B, int HW) {
+  int S = (FILM_WG + B - 1) / B;
+  if (S > HW / 64) S = HW / 64;
+  return S < 1 ? 1 : S;
+}
 
 int level_h(const Plan& P, int l) { return P.H >> l; }
 int level_w(const Plan& P, int l) { return P.W >> l; }
@@ -385,12 +420,12 @@ lbm_status make_plan(const sg_config* cfg, Plan* P) {
     P->o_grad = take(np * 4);
     P->o_m = take(np * 4);
     P->o_v = take(np * 4);
-    P->o_dgam = take((size_t)B * 128 * 4);
+    // chunk sums of any batch up to B (B S <= FILM_WG + B)
+    for (int l = 0; l < NL; ++l)
+      P->o_fpart[l] = take(((size_t)FILM_WG + B) * kLayers[l].cout * 8);
     for (int l = 0; l < NL; ++l) P->o_g[l] = take(act(kLayers[l].level, kLayers[l].cout));
     for (int k = 0; k < 3; ++k) P->o_gpool[k] = take(act(k + 1, pc[k]));
     for (int k = 0; k < 3; ++k) P->o_gup[k] = take(act(k, uc[k]));
-    P->o_gtmp[0] = take(act(0, 128));  // generic scratch (largest level-0 gradient)
-    P->o_gtmp[1] = take(act(0, 128));
     // weight-gradient partials: splits x 9 x Cout x Cin for the largest layer
     int64_t mx = 0;
     for (int l = 0; l < NL; ++l) {
@@ -417,12 +452,12 @@ struct sg_net {
   float* s;
   float* T;
   float* gam[NL];
-  float* dgam;
+  double* fpart[NL];  // FiLM gradient chunk sums
   double* part;
   double* spart;  // per-sample statistics partials [B][SB][3]
   double* loss;
   float* x0;
-  Tensor z[NL], pool[3], up[3], g[NL], gpool[3], gup[3], gtmp[2];
+  Tensor z[NL], pool[3], up[3], g[NL], gpool[3], gup[3];
   float* wpart;
   int B;          // batch of the current forward
   int circular;   // padding of the current forward
@@ -592,13 +627,19 @@ void upadd(sg_net* n, const Tensor& coarse, const float* sc, const Tensor& skip,
 }
 
 void prep_weights(sg_net* n) {
+  static_assert(NL <= MAXL, "PrepArgs size");
+  PrepArgs a;
+  a.n = NL;
+  a.at[0] = 0;
   for (int l = 0; l < NL; ++l) {
-    const int64_t e = (int64_t)9 * kLayers[l].cin * kLayers[l].cout;
-    hipLaunchKernelGGL(k_prep_weights, dim3(grid1(e)), dim3(RT), 0, n->stream,
-                       n->param + n->P.woff[l], kLayers[l].cin, kLayers[l].cout,
-                       n->wfh + n->P.wq_off[l], n->wfl + n->P.wq_off[l], n->wbh + n->P.wq_off[l],
-                       n->wbl + n->P.wq_off[l]);
+    a.woff[l] = n->P.woff[l];
+    a.wq_off[l] = n->P.wq_off[l];
+    a.cin[l] = kLayers[l].cin;
+    a.cout[l] = kLayers[l].cout;
+    a.at[l + 1] = a.at[l] + 9 * kLayers[l].cin * kLayers[l].cout;
   }
+  hipLaunchKernelGGL(k_prep_weights, dim3((unsigned)(a.at[NL] / 256)), dim3(256), 0, n->stream,
+                     (const float*)n->param, a, n->wfh, n->wfl, n->wbh, n->wbl);
   n->weights_ready = true;
 }
 
@@ -659,17 +700,10 @@ void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const floa
   const LayerSpec& L = kLayers[l];
   const Tensor& zl = n->z[l];
   const int HW = zl.H * zl.W;
-  // FiLM coefficients (the weight-gradient partials' buffer holds the
-  // per-chunk sums; it is rewritten only after they have been added)
-  int S = 16;
-  while (S > 1 && ((int64_t)n->B * S * L.cout * 2 > n->P.wpart_floats || HW / S < 64)) S /= 2;
-  hipLaunchKernelGGL(k_film_grad_part, dim3(n->B * S), dim3(RT), 0, n->stream, gy.p, zl.p, HW,
-                     L.cout, S, (double*)n->wpart);
-  hipLaunchKernelGGL(k_film_grad_sum, dim3(grid1((int64_t)n->B * L.cout)), dim3(RT), 0,
-                     n->stream, (const double*)n->wpart, n->B, L.cout, S, n->dgam);
-  hipLaunchKernelGGL(k_film_coef_grad, dim3(grid1(L.cout * NBASIS)), dim3(RT), 0, n->stream,
-                     (const float*)n->dgam, (const float*)n->T, n->B, L.cout,
-                     n->grad + P.aoff[l]);
+  // FiLM coefficients: the chunk sums now, the rest for all layers at the end
+  const int S = film_chunks(n->B, HW);
+  hipLaunchKernelGGL(k_film_grad_part, dim3((unsigned)(n->B * S)), dim3(RT), 0, n->stream, gy.p,
+                     zl.p, HW, L.cout, S, n->fpart[l]);
   // weights: dW = sum (gamma * gy) (x) (xscale * x)
   const int64_t pixels = (int64_t)n->B * HW;
   const bool rows_fit = zl.W % 64 == 0 || (64 % zl.W == 0 && zl.H % (64 / zl.W) == 0);
@@ -770,6 +804,17 @@ lbm_status backward(sg_net* n) {
   conv_back(n, L_E0B, g[L_E0B], z[L_E0A], gm[L_E0A], g[L_E0A], 0);
   conv_back(n, L_E0A, g[L_E0A], z[L_IN], gm[L_IN], g[L_IN], 0);
   conv_back(n, L_IN, g[L_IN], x0, nullptr, none, 0);
+  FilmArgs a;
+  int groups = 0;
+  for (int l = 0; l < NL; ++l) {
+    a.part[l] = n->fpart[l];
+    a.da[l] = n->grad + n->P.aoff[l];
+    a.cout[l] = kLayers[l].cout;
+    a.S[l] = film_chunks(n->B, z[l].H * z[l].W);
+    groups += kLayers[l].cout / 32;
+  }
+  hipLaunchKernelGGL(k_film_grad_coef, dim3((unsigned)groups), dim3(RT), 0, n->stream, a,
+                     (const float*)n->T, n->B);
   return launch_check("surrogate backward");
 }
 
@@ -830,7 +875,7 @@ lbm_status sg_create(const sg_config* cfg, void* d_ws, size_t ws_bytes, void* hi
     n->grad = (float*)(w + P.o_grad);
     n->m = (float*)(w + P.o_m);
     n->v = (float*)(w + P.o_v);
-    n->dgam = (float*)(w + P.o_dgam);
+    for (int l = 0; l < NL; ++l) n->fpart[l] = (double*)(w + P.o_fpart[l]);
     for (int l = 0; l < NL; ++l) {
       const int lv = kLayers[l].level;
       n->g[l] = Tensor{(float*)(w + P.o_g[l]), level_h(P, lv), level_w(P, lv), kLayers[l].cout};

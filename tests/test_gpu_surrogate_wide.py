@@ -92,3 +92,26 @@ def test_wide_gradients_match_direct(circular):
         err = np.linalg.norm(grads[0][k] - grads[1][k]) / max(n, 1e-30)
         # the backward pass adds its own 16 layers: twice the sums
         assert err < 2 * TOL, (k, err)
+
+
+@gpu
+def test_gradients_match_reference_odd_batch():
+    # FiLM sums of a batch that is no multiple of the 8 samples a workgroup
+    # takes at a time, against the FP64 reference at the tolerance of the
+    # gradient test (tests/test_gpu_surrogate.py)
+    torch = _torch()
+    from oracle import surrogate_ref as R
+    B, H, W = 9, 64, 128
+    x = _input(torch, B, H, W, 5)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    t = x[:, :5] + 0.1 * torch.randn(B, 5, H, W, device="cuda", generator=g)
+    net = _net(B, H, W, 3, 0, train=True)
+    P = {k: v.astype(np.float64) for k, v in S.unpack_params(net.get_params().cpu().numpy()).items()}
+    net.train_step(x, t, circular=False, lr=0.0)
+    G = S.unpack_params(net.get_grads().double().cpu().numpy())
+    ref = R.Forward(P, x.double().cpu().numpy(), False)
+    ref.loss(t.double().cpu().numpy())
+    want = ref.backward()
+    for k in want:
+        n = np.linalg.norm(want[k])
+        assert np.linalg.norm(G[k] - want[k]) <= 1e-3 * n, k
