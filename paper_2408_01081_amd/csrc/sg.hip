@@ -706,6 +706,25 @@ void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const floa
                      zl.p, HW, L.cout, S, n->fpart[l]);
   // weights: dW = sum (gamma * gy) (x) (xscale * x)
   const int64_t pixels = (int64_t)n->B * HW;
+  const int wt = zl.W % 32 == 0 && zl.H % 8 == 0 ? 32 : zl.W % 16 == 0 && zl.H % 16 == 0 ? 16 : 0;
+  const int64_t ntile = pixels / 256, nct = (L.cout / 32) * (L.cin / 32);
+  if (n->conv_mode != 1 && wt && ntile * nct >= 128) {
+    // two workgroups per CU
+    int64_t ng = 512 / nct;
+    const int64_t cap = n->P.wpart_floats / ((int64_t)9 * L.cout * L.cin);
+    ng = ng > cap ? cap : ng;
+    ng = ng > ntile ? ntile : ng;
+    auto fn = P.split == 3 ? (wt == 32 ? &k_wgradw<3, 32> : &k_wgradw<3, 16>)
+                           : (wt == 32 ? &k_wgradw<1, 32> : &k_wgradw<1, 16>);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(ng * nct)), dim3(256), 0, n->stream, gy.p,
+                       (const float*)n->gam[l], xin.p, xscale, n->wpart, zl.H, zl.W, L.cin, L.cout,
+                       n->circular, (int)ntile, (int)ng);
+    const int64_t nw = (int64_t)9 * L.cout * L.cin;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nw + 63) / 64)), dim3(RT), 0, n->stream,
+                       (const float*)n->wpart, (int)ng, L.cin, L.cout, n->grad + P.woff[l]);
+    if (gin.p) conv(n, gy, n->gam[l], l, gin, true, accumulate);
+    return;
+  }
   const bool rows_fit = zl.W % 64 == 0 || (64 % zl.W == 0 && zl.H % (64 / zl.W) == 0);
   if (n->conv_mode != 1 && rows_fit && L.cin % 32 == 0 && L.cout % 32 == 0) {
     // LDS-staged kernel: ~256 workgroups (one per CU: 92 KB of LDS), as many

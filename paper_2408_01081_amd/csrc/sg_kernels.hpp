@@ -921,6 +921,218 @@ __global__ __launch_bounds__(256) void k_wgradt(const float* __restrict__ G,
           acc[t][j];
 }
 
+// The weight gradient for layers with many pixels.  A workgroup owns a 32 x
+// 32 (output, input channel) tile of all 9 taps and runs through pixel tiles
+// of RW x WT = 256 pixels, group `g` of `ng` taking every ng-th; the next
+// tile's loads are in registers while this one's products run.  Both operands
+// are staged as the convolution stages them (pixel rows of 32 channels, BF16
+// hi and lo, one copy), and the matrix core's fragments, which run along the
+// pixels, come from transposing LDS reads (ds_read_b64_tr_b16: four lanes
+// give the addresses of a pixel's 16 channels, lane i of a group of 16 gets
+// channel i of four pixels; lane layout checked on gfx950 by an in-bounds
+// probe), which take any pixel offset, so a tap is an offset and nothing is
+// staged three times.
+// K step s of a tile: 32 pixels, the row s (WT = 32) or the rows s and s + 8
+// (WT = 16).  Wave w takes steps 4 (w / 2) .. + 3 and 16 input channels,
+// w mod 2, of all 32 output channels and 9 taps (72 accumulators; all 32 input
+// channels of half as many steps spilled): an input row's fragments (three
+// dx) serve the steps above, at and below it.  Waves 2 and 3 hand their sums
+// to 0 and 1 through LDS, which write partial[g][t][o][i].  76 KB of LDS: two
+// workgroups share a CU.
+// Bound by the matrix cores and the staging between them: 29 GFLOP in three
+// passes (batch 32, 128 x 128: 32 channels at full, 64 at half, 128 at quarter
+// resolution) 35.6 us, 810 TFLOP/s, where k_wgradt, which writes single BF16
+// values of three shifted copies, took 172, 167 and 102.
+template <int SPLIT, int WT>
+__global__ __launch_bounds__(256, 2) void k_wgradw(const float* __restrict__ G,
+                                                   const float* __restrict__ gscale,
+                                                   const float* __restrict__ X,
+                                                   const float* __restrict__ xscale,
+                                                   float* __restrict__ partial, int H, int W,
+                                                   int Cin, int Cout, int circular, int npt,
+                                                   int ng) {
+  constexpr int RW = 256 / WT, TR = RW + 2, TW = WT + 2;
+  constexpr int NH = SPLIT == 3 ? 2 : 1;
+  constexpr int XS = TR * TW * 16, GS = 256 * 16;  // dwords per hi/lo part
+  constexpr int RED = 18 * 64 * 4;                 // sums of a wave
+  constexpr int LDS = NH * (XS + GS) > 2 * RED ? NH * (XS + GS) : 2 * RED;
+  __shared__ uint4 lds4[LDS / 4];
+  uint32_t* xt = reinterpret_cast<uint32_t*>(lds4);
+  uint32_t* gt = xt + NH * XS;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int m = lane & 15, kq = lane >> 4;
+  const int q = threadIdx.x & 3;
+  const int kh = wave >> 1, ch = wave & 1;
+  // group and channel tile: the channel tiles of a pixel group on one XCD
+  const int nit = Cin / 32, nct = (Cout / 32) * nit;
+  int g, ct;
+  if (ng % 8 == 0) {
+    const int i = blockIdx.x >> 3;
+    ct = i % nct;
+    g = (i / nct) * 8 + (blockIdx.x & 7);
+  } else {
+    ct = blockIdx.x % nct;
+    g = blockIdx.x / nct;
+  }
+  const int o0 = ct / nit * 32, i0 = ct % nit * 32;
+  const int tx = W / WT, tiles = (H / RW) * tx;
+
+  // 16-byte piece q of the pixel at column c sits at q ^ rot(c): conflict-free
+  // for 8 pixels' equal pieces (staging) and for 4 pixels' piece pairs
+  auto rot = [](int c) __attribute__((always_inline)) { return (c & 2) | ((c >> 2) & 1); };
+  // dword offsets of this lane's 8 bytes of a transposing read (channels 0 ..
+  // 15; channels 16 .. 31: ^ 8): pixel 4 h + m / 4 of its 8, 4-channel piece m % 4
+  const int row8 = WT == 16 ? 8 * (kq >> 1) : 0, col8 = WT == 16 ? 8 * (kq & 1) : 8 * kq;
+  auto at = [&](int tw, int col) __attribute__((always_inline)) {
+    return 16 * ((row8 + 4 * kh) * tw + col) + 4 * (((m & 3) >> 1) ^ rot(col)) + 2 * (m & 1);
+  };
+  int ga[2], xa[3][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int col = col8 + 4 * h + (m >> 2);
+    ga[h] = at(WT, col);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) xa[d][h] = at(TW, col + d) ^ (8 * ch);
+  }
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* LdsP;
+  auto frag = [&](const uint32_t* base, int a0, int a1) __attribute__((always_inline)) {
+    const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsP)(base + a0));
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsP)(base + a1));
+    bf16x8 r;
+    __builtin_memcpy(&r, &u, 8);
+    __builtin_memcpy(reinterpret_cast<char*>(&r) + 8, &v, 8);
+    return r;
+  };
+
+  f32x4 acc[9][2];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int a = 0; a < 2; ++a) acc[t][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  // staged pieces of 8 channels: PER of the input (with its halo), then 4 of
+  // the gradient
+  constexpr int NTILE = TR * TW * 4, PER = (NTILE + 255) / 256;
+  float u[PER + 4][8];
+  uint32_t live;  // bit k: input piece k is inside the image (else zero)
+  auto fetch = [&](int pt) __attribute__((always_inline)) {
+    const int b = pt / tiles, rem = pt - b * tiles;
+    const int y = (rem / tx) * RW, x0 = (rem - (rem / tx) * tx) * WT;
+    const float* xb = X + (int64_t)b * H * W * Cin + i0 + 8 * q;
+    const float* gb = G + (int64_t)b * H * W * Cout + o0 + 8 * q;
+    live = 0u;
+    // (recomputed for every tile: rows and columns kept across the products
+    // would spill, and a reload waits for all loads in flight)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int k = 0; k < PER + 4; ++k) {
+      const float* p;
+      if (k < PER) {
+        const int i = tid + 256 * k;
+        const int row = (i >> 2) / TW, col = (i >> 2) - row * TW;
+        const int yr = y + row - 1, xr = x0 + col - 1;
+        const int ys = yr < 0 ? yr + H : (yr >= H ? yr - H : yr);
+        const int xs = xr < 0 ? xr + W : (xr >= W ? xr - W : xr);
+        const bool v = i < NTILE && (circular || (ys == yr && xs == xr));
+        live |= v ? 1u << k : 0u;
+        p = xb + (v ? ((int64_t)ys * W + xs) * Cin : 0);
+      } else {
+        const int i = (tid >> 2) + 64 * (k - PER), row = i / WT, col = i - row * WT;
+        p = gb + ((int64_t)(y + row) * W + x0 + col) * Cout;
+      }
+      const float4 a = *reinterpret_cast<const float4*>(p), c = *reinterpret_cast<const float4*>(p + 4);
+      u[k][0] = a.x; u[k][1] = a.y; u[k][2] = a.z; u[k][3] = a.w;
+      u[k][4] = c.x; u[k][5] = c.y; u[k][6] = c.z; u[k][7] = c.w;
+    }
+  };
+  if (g < npt) fetch(g);
+  for (int pt = g; pt < npt; pt += ng) {
+    const int b = pt / tiles;
+    float sx[8], sg[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      sx[j] = xscale ? xscale[(int64_t)b * Cin + i0 + 8 * q + j] : 1.f;
+      sg[j] = gscale ? gscale[(int64_t)b * Cout + o0 + 8 * q + j] : 1.f;
+    }
+    __syncthreads();  // the previous tile's fragments have been read
+#pragma unroll
+    for (int k = 0; k < PER + 4; ++k) {
+      const int i = (int)threadIdx.x + 256 * (k < PER ? k : k - PER);
+      if (k + 1 == PER && NTILE % 256 != 0 && i >= NTILE) continue;
+      float a[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        a[j] = u[k][j] * (k < PER ? sx[j] : sg[j]);
+        if (k < PER) a[j] = live >> k & 1 ? a[j] : 0.f;
+      }
+      uint32_t h[4], l[4];
+      split_pairs<SPLIT>(a, h, l);
+      const int p = i >> 2, col = k < PER ? p % TW : p % WT;
+      const int d = 16 * p + 4 * (q ^ rot(col));
+      uint32_t* t = k < PER ? xt : gt;
+      *reinterpret_cast<uint4*>(t + d) = (uint4){h[0], h[1], h[2], h[3]};
+      if (SPLIT == 3)
+        *reinterpret_cast<uint4*>(t + (k < PER ? XS : GS) + d) = (uint4){l[0], l[1], l[2], l[3]};
+    }
+    if (pt + ng < npt) fetch(pt + ng);
+    __syncthreads();
+    bf16x8 gh[4][2], gl[4][2];  // [step][half of the output channels]
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {  // input row 4 kh + r of the tile
+      if (r < 4) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const uint32_t* base = gt + r * WT * 16;
+          gh[r][a] = frag(base, ga[0] ^ (8 * a), ga[1] ^ (8 * a));
+          if (SPLIT == 3) gl[r][a] = frag(base + GS, ga[0] ^ (8 * a), ga[1] ^ (8 * a));
+        }
+      }
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        const uint32_t* base = xt + r * TW * 16;
+        const bf16x8 xh = frag(base, xa[dx][0], xa[dx][1]);
+        bf16x8 xl;
+        if (SPLIT == 3) xl = frag(base + XS, xa[dx][0], xa[dx][1]);
+#pragma unroll
+        for (int part = 0; part < SPLIT; ++part)
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy) {
+            const int s = r - dy;
+            if (s < 0 || s > 3) continue;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+              f32x4& d = acc[3 * dy + dx][a];
+              d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part == 1 ? gl[s][a] : gh[s][a],
+                                                          part == 2 ? xl : xh, d, 0, 0, 0);
+            }
+          }
+      }
+    }
+  }
+  // D[row = o (4 kq + j)][col = i (m)]; the second half's steps are added to
+  // the first's
+  float* red = reinterpret_cast<float*>(lds4) + ch * RED;
+  __syncthreads();
+  if (kh) {
+#pragma unroll
+    for (int e = 0; e < 18; ++e)
+      *reinterpret_cast<f32x4*>(red + (e * 64 + lane) * 4) = acc[e >> 1][e & 1];
+  }
+  __syncthreads();
+  if (kh) return;
+#pragma unroll
+  for (int e = 0; e < 18; ++e) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(red + (e * 64 + lane) * 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      partial[(((int64_t)g * 9 + (e >> 1)) * Cout + o0 + 16 * (e & 1) + 4 * kq + j) * Cin + i0 +
+              16 * ch + m] = acc[e >> 1][e & 1][j] + v[j];
+  }
+}
+
 // Sum of the weight-gradient partials in a fixed order: 64 weights per
 // workgroup as 16 x 4, 16 groups of threads summing every 16th partial, then
 // the group sums in order.  One float per thread and 4 groups left a chain of
