@@ -295,13 +295,19 @@ lbm_status lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t use_cache, int32_t* 
  * per segment, store type and rows prefetched ahead (h_prefetch); h_seg_rows
  * 0 means the segment length is chosen at launch so that one wave per
  * resident slot covers the grid, -k that k waves per slot do, -100 that one
- * wave per SIMD (4 per CU) does whatever the occupancy.  index -1 disables blocking; lbm_autotune
+ * wave per SIMD (4 per CU) does whatever the occupancy.  h_seg_rows =
+ * -1000 - R is a tile variant for small lattices: a workgroup holds 64 columns
+ * x R rows in registers and advances all of them one step at a time (rows
+ * meet in LDS), storing 64 - 2T columns x R - 2T rows; it takes any number
+ * of steps up to T per launch, also with a body load of rank <= 32 and/or
+ * the displacement state.  index -1 disables blocking; lbm_autotune
  * selects a variant when it is faster per step than the best single-step
  * configuration.  With a variant of T steps enabled, lbm_step(n) runs the
  * steps in chunks of floor(420 / T) T steps, T per launch; the r = n mod T
  * steps after the last full launch take one launch of an r-step variant
  * (the fastest one lbm_autotune timed, else the r-step variant of the
- * nearest launch shape), or of the single-step kernel for r = 1.  Row base
+ * nearest launch shape; a tile variant takes them itself), or of the
+ * single-step kernel for r = 1.  Row base
  * addresses are 64-bit; only the byte offsets inside one row's 20 planes
  * ((19 plane strides + one row) * 4 B) must stay below 2^31, which fails
  * for the plane-major layout beyond about 28 M nodes and for rows of more
@@ -352,7 +358,8 @@ lbm_status lbm_select_for_steps(lbm_ctx* ctx, int64_t nsteps, int32_t* h_index);
 /* The r-step blocked variant (r = 2 .. 10) lbm_step launches for the last r
  * steps of a run when r is below the selected variant's T: the fastest
  * r-step variant lbm_autotune timed (kept in its cache file as well), else
- * the r-step variant nearest to the selected one's launch shape;
+ * the r-step variant nearest to the selected one's launch shape; a selected
+ * tile variant itself, for r below its T.
  * *h_index = -1 when no variant is selected or r is outside 2 .. 10.
  * LBM_E_ARG for a NULL argument. */
 lbm_status lbm_get_tblock_remainder(const lbm_ctx* ctx, int32_t r, int32_t* h_index);

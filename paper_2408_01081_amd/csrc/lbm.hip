@@ -27,6 +27,7 @@
 #include "lbm_step.hpp"
 #include "lbm_tblock.hpp"
 #include "lbm_tb_tables.hpp"
+#include "lbm_tile.hpp"
 #include "lbm_init.hpp"
 #include "lbm_host.hpp"
 
@@ -782,12 +783,13 @@ struct TBTables {
   TBFn fn[kNumTBVariants][2];       // load-free, [variant][bc]
   TBExtFns xfn[kNumTBExtVariants];  // with extras, [variant][extras][bc]
   TBSplitFn sfn[kNumTBSplitVariants];  // split Dirichlet launches
+  TileTable tile;                   // tile kernels (lbm_tile.hpp)
 };
 
 const TBTables& tb_tables() {
   static const TBTables t = [] {
     TBTables r;
-    TBFn p[kNumTBVariants], d[kNumTBVariants];
+    TBFn p[kNumTBVariants] = {}, d[kNumTBVariants] = {};  // (null for the tiles)
     tb_fill_periodic_a(p);
     tb_fill_periodic_b(p);
     tb_fill_dirichlet_a(d);
@@ -799,6 +801,7 @@ const TBTables& tb_tables() {
     tb_fill_extra_a(r.xfn);
     tb_fill_extra_b(r.xfn);
     tb_fill_split(r.sfn);
+    tile_fill(r.tile);
     return r;
   }();
   return t;
@@ -976,10 +979,46 @@ bool split_plan(lbm_ctx* c, int index, SplitPlan& sp) {
   return true;
 }
 
-// one launch of variant `index`: kTBVariants[index].steps steps, level l with
-// the walls of table entry s0 + l - 1
-void launch_tb(lbm_ctx* c, int index, const float* src, float* dst, const WallSeq& ws) {
+// ---- tile launches ---------------------------------------------------------
+bool is_tile(int index) { return index >= kNumTBSweeps; }
+
+// waves of a launch of tile variant `index` with extras m (3: none)
+int tile_waves(const lbm_ctx* c, int index, int m) {
+  const int nw = (TB_SEG_TILE - kTBVariants[index].seg_rows) / TILE_K;
+  const int most = tile_max_waves(m);
+  return nw < most ? nw : most;
+}
+
+// most steps of such a launch
+int tile_steps_of(const lbm_ctx* c, int index, int m) {
+  const int T = kTBVariants[index].steps;
+  const int most = tile_max_steps(TILE_K * tile_waves(c, index, m));
+  return m == 3 || T < most ? T : most;
+}
+
+TBConst tile_const(const lbm_ctx* c, int index, int m, int T) {
+  return tblock_const(c->g, (float)c->kK, (float)c->km,
+                      TILE_K * tile_waves(c, index, m) - 2 * T, T);
+}
+
+// one launch of tile variant `index` advancing T <= tile_steps_of steps
+void launch_tile(lbm_ctx* c, int index, int m, int T, const float* src, float* dst,
+                 const WallSeq& ws, const TileExtra& F) {
+  const TBConst sc = tile_const(c, index, m, T);
+  hipLaunchKernelGGL(tb_tables().tile.fn[m][c->force_rank > 16][c->p.bc],
+                     dim3((unsigned)(sc.nstrips * sc.nseg)), dim3(64 * tile_waves(c, index, m)), 0,
+                     c->stream, src, dst, c->g, sc, ws, F, T);
+}
+
+// one launch of variant `index`: `steps` steps (0: the variant's own number;
+// fewer only for tiles), level l with the walls of table entry s0 + l - 1
+void launch_tb(lbm_ctx* c, int index, const float* src, float* dst, const WallSeq& ws,
+               int steps = 0) {
   const TBVariant& k = kTBVariants[index];
+  if (is_tile(index)) {
+    launch_tile(c, index, 3, steps ? steps : k.steps, src, dst, ws, TileExtra{});
+    return;
+  }
   SplitPlan sp;
   if (split_plan(c, index, sp)) {
     hipLaunchKernelGGL(tb_tables().sfn[sp.kernel], dim3((unsigned)((sp.ntiles + 3) / 4)),
@@ -998,13 +1037,15 @@ void launch_tb(lbm_ctx* c, int index, const float* src, float* dst, const WallSe
 // r-step variant when it has timed them, else the r-step variant nearest to
 // that shape (same rows per segment, store type and prefetch, then the same
 // rows per segment and prefetch, then the same rows per segment, then the
-// first); -1 if none, or if `shape` is not a blocked variant.
+// first); a tile variant takes them itself; -1 if none, or if `shape` is not
+// a blocked variant.
 int remainder_variant(const lbm_ctx* c, int r, int shape) {
   if (r < 2 || r > TB_MAX_STEPS || shape < 0 || shape >= kNumTBVariants) return -1;
+  if (is_tile(shape)) return r < kTBVariants[shape].steps ? shape : -1;
   if (c->tb_rem[r] >= 0) return c->tb_rem[r];
   const TBVariant& t = kTBVariants[shape];
   int best = -1, best_score = -1;
-  for (int i = 0; i < kNumTBVariants; ++i) {
+  for (int i = 0; i < kNumTBSweeps; ++i) {
     const TBVariant& k = kTBVariants[i];
     if (k.steps != r) continue;
     const int score = (k.seg_rows == t.seg_rows ? 4 : 0) + (k.pf == t.pf ? 2 : 0) +
@@ -1168,6 +1209,36 @@ static lbm_status step_extra_blocked(lbm_ctx* c, int64_t nsteps, int vi, int m) 
   return launch_check("k_tblock launch (load / displacement)");
 }
 
+// whether steps with extras take tiles: a tile variant is selected and the
+// load's rank has a kernel
+static bool extra_tiles(const lbm_ctx* c) {
+  return c->tb_cfg >= 0 && is_tile(c->tb_cfg) && c->force_rank <= TB_MAXR && tblock_fits(c->g);
+}
+
+// Steps with a body load and/or the displacement state (no error norms) in
+// launches of the selected tile variant; the last launch of a run takes the
+// steps left.
+static lbm_status step_extra_tiles(lbm_ctx* c, int64_t nsteps, int m) {
+  const int T = tile_steps_of(c, c->tb_cfg, m);
+  const int chunk = WALL_CHUNK / T * T;
+  for (int64_t done = 0; done < nsteps;) {
+    const int n = (int)(nsteps - done < chunk ? nsteps - done : chunk);
+    eval_walls(c, c->nstep, n);
+    for (int j = 0; j < n;) {
+      const int t = n - j < T ? n - j : T;
+      const TileExtra F{c->force_X, c->force_Y,
+                        c->force_rank ? c->force_T + (c->nstep + 1) * c->force_rank : nullptr,
+                        c->force_rank, (float)(c->p.dt / c->p.rho), c->disp, 0.5 * c->p.dt};
+      launch_tile(c, c->tb_cfg, m, t, c->buf[c->cur], c->buf[c->cur ^ 1], walls_from(c, j, true), F);
+      c->cur ^= 1;
+      c->nstep += t;
+      j += t;
+    }
+    done += n;
+  }
+  return launch_check("k_tile launch (load / displacement)");
+}
+
 lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   if (!c) return fail(LBM_E_ARG, "null ctx");
   if (!c->initialised) return fail(LBM_E_STATE, "lbm_step before lbm_init");
@@ -1182,6 +1253,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
     return fail(LBM_E_ARG, "reference table too short for the requested steps");
   if ((c->force_rank > 0 || c->disp) && !c->err_on) {
     const int m = c->force_rank > 0 ? (c->disp ? 2 : 0) : 1;
+    if (extra_tiles(c)) return step_extra_tiles(c, nsteps, m);
     const int vi = extra_variant(c, m);
     if (vi >= 0) return step_extra_blocked(c, nsteps, vi, m);
   }
@@ -1207,7 +1279,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
       }
       const int ri = remainder_variant(c, m - k, c->tb_cfg);
       if (ri >= 0) {
-        launch_tb(c, ri, c->buf[c->cur], c->buf[c->cur ^ 1], walls_from(c, k, true));
+        launch_tb(c, ri, c->buf[c->cur], c->buf[c->cur ^ 1], walls_from(c, k, true), m - k);
         c->cur ^= 1;
         k = m;
       }
@@ -1257,6 +1329,9 @@ TuneVal tune_val(int cfg, int cfg2, const int* rem, const lbm_ctx* timed = nullp
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tune_cache;
 bool g_tune_file_loaded = false;
+
+// most tiles of a grid on which the autotuner times tile variants (eight per CU)
+constexpr int TILE_TUNE = 2048;
 
 int find_config(int vec, int threads, int nt, int xmode) {
   for (int i = 0; i < kNumStepConfigs; ++i) {
@@ -1406,6 +1481,11 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t reps, int32_t use_cache, int32_t* h_
     rem_ms[r] = 1e300;
   }
   for (int i = 0; i < kNumTBVariants && s == LBM_OK && tblock_fits(c->g); ++i) {
+    // grids of many tiles are the sweep's: its overlap is smaller
+    if (is_tile(i)) {
+      const TBConst sc = tile_const(c, i, 3, kTBVariants[i].steps);
+      if ((int64_t)sc.nstrips * sc.nseg > TILE_TUNE) continue;
+    }
     for (int r = 0; r < reps + 2; ++r) {
       if (r == 2) hipEventRecord(e0, c->stream);
       launch_tb(c, i, c->buf[c->cur], c->buf[c->cur ^ 1], ws);
@@ -1465,6 +1545,7 @@ int32_t lbm_steps_per_launch(const lbm_ctx* c) {
   if (c->err_on) return 1;
   if (c->force_rank > 0 || c->disp) {
     const int m = c->force_rank > 0 ? (c->disp ? 2 : 0) : 1;
+    if (extra_tiles(c)) return tile_steps_of(c, c->tb_cfg, m);
     const int vi = extra_variant(c, m);
     return vi >= 0 ? kTBExtVariants[vi].steps : 1;
   }
@@ -1500,6 +1581,9 @@ lbm_status lbm_select_for_steps(lbm_ctx* c, int64_t nsteps, int32_t* h_index) {
     double rest = 0.0;
     if (r == 1) {
       rest = c->step_launch_ms;
+    } else if (r > 1 && v >= 0 && is_tile(v)) {
+      // the same tile with fewer steps: a launch costs about two steps beside them
+      rest = full * (r + 2) / (T + 2);
     } else if (r > 1) {
       const int ri = remainder_variant(c, r, v);
       rest = ri >= 0 && c->tb_launch_ms[ri] > 0.0 ? c->tb_launch_ms[ri] : r * c->step_launch_ms;

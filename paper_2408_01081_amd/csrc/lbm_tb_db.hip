@@ -7,7 +7,7 @@ namespace lbmk {
 
 void tb_fill_dirichlet_b(TBFn* out) {
   tb_fill_range<LBM_DIRICHLET, kTBSplit>(
-      out, std::make_integer_sequence<int, kNumTBVariants - kTBSplit>{});
+      out, std::make_integer_sequence<int, kNumTBSweeps - kTBSplit>{});
 }
 
 }  // namespace lbmk

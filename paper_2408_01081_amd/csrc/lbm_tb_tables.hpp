@@ -15,12 +15,13 @@ typedef void (*TBFn)(const float*, float*, Grid, TBConst, WallSeq, TBExtra);
 
 // T steps per launch, output rows per segment (0: as many as give one wave per
 // resident slot across the grid, -k: k waves per slot, TB_SEG_SIMD: one wave
-// per SIMD whatever the occupancy), nontemporal stores, level-0 rows
-// prefetched ahead.
+// per SIMD whatever the occupancy; TB_SEG_TILE - R: a tile of R rows per
+// workgroup, lbm_tile.hpp), nontemporal stores, level-0 rows prefetched ahead.
 struct TBVariant {
   int steps, seg_rows, nt, pf;
 };
 constexpr int TB_SEG_SIMD = -100;
+constexpr int TB_SEG_TILE = -1000;
 constexpr int TB_MAX_STEPS = 10;  // most steps of a launch
 
 // Load-free variants; the index is the public variant number
@@ -35,8 +36,18 @@ constexpr TBVariant kTBVariants[] = {
     {8, 20, 0, 2}, {8, 30, 0, 2}, {8, 24, 0, 1}, {8, 32, 0, 1}, {8, 0, 0, 2},  {8, -2, 0, 2},
     {8, 0, 0, 1},  {7, 0, 0, 2},  {4, 0, 0, 1},  {3, 0, 0, 1},  {4, 375, 0, 2}, {5, 375, 0, 2},
     {4, TB_SEG_SIMD, 0, 3}, {5, TB_SEG_SIMD, 0, 3}, {3, TB_SEG_SIMD, 0, 3}, {2, TB_SEG_SIMD, 0, 3},
-    {10, -2, 0, 2}, {10, 0, 0, 2}, {9, 0, 0, 2}};
+    {10, -2, 0, 2}, {10, 0, 0, 2}, {9, 0, 0, 2},
+    // tiles (lbm_tile.hpp): steps, TB_SEG_TILE - rows held
+    {4, TB_SEG_TILE - 16, 0, 0}, {5, TB_SEG_TILE - 16, 0, 0}, {6, TB_SEG_TILE - 24, 0, 0},
+    {8, TB_SEG_TILE - 24, 0, 0}};
 constexpr int kNumTBVariants = (int)(sizeof(kTBVariants) / sizeof(kTBVariants[0]));
+constexpr int tb_num_sweeps() {
+  int n = 0;
+  for (const TBVariant& v : kTBVariants) n += v.seg_rows > TB_SEG_TILE;
+  return n;
+}
+// the sweep kernels' variants come first, then the tiles
+constexpr int kNumTBSweeps = tb_num_sweeps();
 constexpr bool tb_steps_in_range() {
   for (const TBVariant& v : kTBVariants)
     if (v.steps < 2 || v.steps > TB_MAX_STEPS) return false;
