@@ -56,28 +56,6 @@ enum { L_IN, L_E0A, L_E0B, L_E1A, L_E1B, L_E2A, L_E2B, L_E3A, L_E3B, L_D2A, L_D2
 constexpr int RT = 256;
 
 // ---- per-sample statistics and pre/post -------------------------------------
-struct Mat {
-  float cK, cm, rho;
-};
-__device__ inline Mat material(const float* in, int64_t HW, int64_t p) {
-  const float lam = in[5 * HW + p], mu = in[6 * HW + p], rho = in[7 * HW + p];
-  Mat m;
-  m.cK = sqrtf((lam + mu) / rho);
-  m.cm = sqrtf(mu / rho);
-  m.rho = rho;
-  return m;
-}
-__device__ inline void phys_to_U(const float* f, int64_t HW, int64_t p, const Mat& m,
-                                 float U[5]) {
-  const float sxx = f[2 * HW + p] / m.rho, syy = f[3 * HW + p] / m.rho,
-              sxy = f[4 * HW + p] / m.rho;
-  U[0] = f[p];
-  U[1] = f[HW + p];
-  U[2] = -(sxx + syy) / (2.f * m.cK);
-  U[3] = -(sxx - syy) / (2.f * m.cm);
-  U[4] = -sxy / m.cm;
-}
-
 __device__ inline double wg_sum(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
@@ -122,6 +100,7 @@ __global__ __launch_bounds__(RT) void k_stats_partial(const float* __restrict__ 
 }
 
 // the FiLM gains of every layer, gamma[l][b][c] = sum_k a_l[c][k] T[b][k]
+// (formed by k_stats, which has just formed T)
 struct GammaArgs {
   const float* a[NL];
   float* g[NL];
@@ -130,8 +109,10 @@ struct GammaArgs {
 };
 
 __global__ __launch_bounds__(RT) void k_stats(const double* __restrict__ part, int HW,
-                                              float* __restrict__ sv, float* __restrict__ T) {
+                                              float* __restrict__ sv, float* __restrict__ T,
+                                              GammaArgs ga) {
   __shared__ double sh[RT];
+  __shared__ float Ts[NBASIS];
   const int b = blockIdx.x;
   const double* q = part + (int64_t)b * SB * 3;
   const bool mine = (int)threadIdx.x < SB;
@@ -147,25 +128,23 @@ __global__ __launch_bounds__(RT) void k_stats(const double* __restrict__ part, i
     Tm[0] = 1.0;
     Tm[1] = t;
     for (int k = 2; k < NBASIS; ++k) Tm[k] = 2.0 * t * Tm[k - 1] - Tm[k - 2];
-    for (int k = 0; k < NBASIS; ++k) T[b * NBASIS + k] = (float)Tm[k];
+    for (int k = 0; k < NBASIS; ++k) T[b * NBASIS + k] = Ts[k] = (float)Tm[k];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < ga.total; e += RT) {
+    int c = e, l = 0;
+    while (c >= ga.cout[l]) c -= ga.cout[l++];
+    float s = 0.f;
+    for (int k = 0; k < NBASIS; ++k) s = fmaf(ga.a[l][c * NBASIS + k], Ts[k], s);
+    ga.g[l][b * ga.cout[l] + c] = s;
   }
 }
 
-// x0[b][p][c] = U_c / s_b for c < 5, 0 otherwise; threads e < B * total
-// also form the FiLM gain of one (sample, layer, channel)
+// x0[b][p][c] = U_c / s_b for c < 5, 0 otherwise
 __global__ __launch_bounds__(RT) void k_pre(const float* __restrict__ in, int B, int HW,
                                             const float* __restrict__ sv,
-                                            float* __restrict__ x0, GammaArgs ga,
-                                            const float* __restrict__ T) {
+                                            float* __restrict__ x0) {
   const int64_t e = (int64_t)blockIdx.x * RT + threadIdx.x;
-  if (e < (int64_t)B * ga.total) {
-    const int b = (int)(e / ga.total);
-    int c = (int)(e - (int64_t)b * ga.total), l = 0;
-    while (c >= ga.cout[l]) c -= ga.cout[l++];
-    float s = 0.f;
-    for (int k = 0; k < NBASIS; ++k) s = fmaf(ga.a[l][c * NBASIS + k], T[b * NBASIS + k], s);
-    ga.g[l][b * ga.cout[l] + c] = s;
-  }
   if (e >= (int64_t)B * HW) return;
   const int b = (int)(e / HW);
   const int64_t p = e - (int64_t)b * HW;
@@ -540,12 +519,18 @@ void launch_convt(sg_net* n, const Tensor& x, const float* xscale, const unsigne
 // workgroups; 128 x 128, 64 channels, has 128).
 template <int SPLIT, int WT>
 bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
-               const unsigned short* wl, Tensor& z, int cin, int cout) {
+               const unsigned short* wl, Tensor& z, int cin, int cout, int epi, const ConvEpi& E) {
   const int64_t work = (int64_t)n->B * x.H * x.W / 256 * (cout / 32);
   if (x.W % WT || x.H % (256 / WT) || work < 256) return false;
-  hipLaunchKernelGGL((k_convw<SPLIT, WT>), dim3((unsigned)(work < 512 ? work : 512)), dim3(256), 0,
-                     n->stream, (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout,
-                     n->circular, (int)work);
+  auto fn = epi == EPI_POOL   ? &k_convw<SPLIT, WT, EPI_POOL>
+            : epi == EPI_UP   ? &k_convw<SPLIT, WT, EPI_UP>
+                              : &k_convw<SPLIT, WT, EPI_NONE>;
+  // (the last layer's rows are a multiple of 128 pixels)
+  if constexpr (WT == 32)
+    if (epi == EPI_POST) fn = &k_convw<SPLIT, WT, EPI_POST>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)(work < 512 ? work : 512)), dim3(256), 0, n->stream,
+                     (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout, n->circular,
+                     (int)work, E);
   return true;
 }
 
@@ -578,10 +563,6 @@ bool conv_tiled(sg_net* n, const Tensor& x, const float* xscale, const unsigned 
   // too few workgroups to fill the chip even with 16 output channels per
   // workgroup: the direct kernel splits the reduction over waves instead
   if ((int64_t)n->B * x.H * x.W / 64 * (cout / 16) < 256) return false;
-  if (n->conv_mode == 0 && !accumulate &&
-      (conv_wide<SPLIT, 32>(n, x, xscale, wh, wl, z, cin, cout) ||
-       conv_wide<SPLIT, 16>(n, x, xscale, wh, wl, z, cin, cout)))
-    return true;
   if (x.W % 64 == 0)
     conv_tiled_w<SPLIT, 64>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else if (x.W == 32)
@@ -593,17 +574,24 @@ bool conv_tiled(sg_net* n, const Tensor& x, const float* xscale, const unsigned 
   return true;
 }
 
-void conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, bool backward,
-          int accumulate) {
+// epi: what follows the layer (k_convw's epilogues); returns whether it was done
+bool conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, bool backward,
+          int accumulate, int epi = EPI_NONE, const ConvEpi& E = ConvEpi{}) {
   const LayerSpec& L = kLayers[l];
   const int cin = backward ? L.cout : L.cin, cout = backward ? L.cin : L.cout;
   const unsigned short* wh = (backward ? n->wbh : n->wfh) + n->P.wq_off[l];
   const unsigned short* wl = (backward ? n->wbl : n->wfl) + n->P.wq_off[l];
   const int64_t pixels = (int64_t)n->B * x.H * x.W;
+  if (n->conv_mode == 0 && !accumulate &&
+      (n->P.split == 3 ? conv_wide<3, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                             conv_wide<3, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E)
+                       : conv_wide<1, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                             conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E)))
+    return true;
   // the LDS-tiled kernel splits its input tiles itself
   if (n->P.split == 3 ? conv_tiled<3>(n, x, xscale, wh, wl, z, cin, cout, accumulate)
                       : conv_tiled<1>(n, x, xscale, wh, wl, z, cin, cout, accumulate))
-    return;
+    return false;
   // the direct kernel splits its input (with its gain) into BF16 hi/lo parts
   // as it reads it
   const int k = conv_shape(pixels, cin, cout);
@@ -611,6 +599,7 @@ void conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, boo
     launch_conv_shape<3>(k, n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else
     launch_conv_shape<1>(k, n, x, xscale, wh, wl, z, cin, cout, accumulate);
+  return false;
 }
 
 void pool(sg_net* n, const Tensor& in, const float* scale, Tensor& out) {
@@ -624,6 +613,33 @@ void upadd(sg_net* n, const Tensor& coarse, const float* sc, const Tensor& skip,
   const int64_t e = (int64_t)n->B * out.H * out.W * out.C / 4;  // 4 channels per thread
   hipLaunchKernelGGL(k_upadd, dim3(grid1(e)), dim3(RT), 0, n->stream, coarse.p, sc, skip.p, ss,
                      out.p, n->B, out.H, out.W, out.C);
+}
+
+// the input map and the first layer in one launch, with k_convw's tiles
+bool conv_in(sg_net* n, const float* in, Tensor& z) {
+  const int64_t work = (int64_t)n->B * z.H * z.W / 256;
+  if (n->conv_mode != 0 || z.W % 32 || z.H % 8 || work < 256) return false;
+  hipLaunchKernelGGL(n->P.split == 3 ? &k_conv_in<3> : &k_conv_in<1>, dim3((unsigned)work),
+                     dim3(256), 0, n->stream, in, (const float*)n->s,
+                     (const unsigned short*)n->wfh + n->P.wq_off[L_IN],
+                     (const unsigned short*)n->wfl + n->P.wq_off[L_IN], z.p, z.H, z.W,
+                     n->circular);
+  return true;
+}
+
+// layer l followed by the pooling of its output
+void conv_pool(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& pooled) {
+  ConvEpi E{pooled.p, n->gam[l], nullptr, nullptr, nullptr, nullptr, 1};
+  if (!conv(n, x, xscale, l, n->z[l], false, 0, EPI_POOL, E)) pool(n, n->z[l], n->gam[l], pooled);
+}
+
+// layer l followed by the skip sum up(gain y) + gain_s z_skip; keep: the
+// layer's own output is needed again (the backward pass)
+void conv_up(sg_net* n, const Tensor& x, const float* xscale, int l, int skip, Tensor& out,
+             int keep) {
+  ConvEpi E{out.p, n->gam[l], n->z[skip].p, n->gam[skip], nullptr, nullptr, keep};
+  if (!conv(n, x, xscale, l, n->z[l], false, 0, EPI_UP, E))
+    upadd(n, n->z[l], n->gam[l], n->z[skip], n->gam[skip], out);
 }
 
 void prep_weights(sg_net* n) {
@@ -643,7 +659,10 @@ void prep_weights(sg_net* n) {
   n->weights_ready = true;
 }
 
-lbm_status forward(sg_net* n, const float* in, int B, int circular) {
+// out: the physical output fields, or null for a training step (which keeps
+// every layer's input and output for the backward pass and forms the loss
+// from z_out)
+lbm_status forward(sg_net* n, const float* in, int B, int circular, float* out) {
   Plan& P = n->P;
   n->B = B;
   n->circular = circular;
@@ -651,8 +670,6 @@ lbm_status forward(sg_net* n, const float* in, int B, int circular) {
   if (!n->weights_ready) prep_weights(n);
   const int HW = P.H * P.W;
   hipLaunchKernelGGL(k_stats_partial, dim3(SB, B), dim3(RT), 0, n->stream, in, HW, n->spart);
-  hipLaunchKernelGGL(k_stats, dim3(B), dim3(RT), 0, n->stream, (const double*)n->spart, HW, n->s,
-                     n->T);
   GammaArgs ga;
   ga.total = 0;
   for (int l = 0; l < NL; ++l) {
@@ -661,34 +678,46 @@ lbm_status forward(sg_net* n, const float* in, int B, int circular) {
     ga.cout[l] = kLayers[l].cout;
     ga.total += kLayers[l].cout;
   }
-  const int64_t npre = (int64_t)B * (HW > ga.total ? HW : ga.total);
-  hipLaunchKernelGGL(k_pre, dim3(grid1(npre)), dim3(RT), 0, n->stream, in, B, HW, n->s, n->x0, ga,
-                     (const float*)n->T);
+  hipLaunchKernelGGL(k_stats, dim3(B), dim3(RT), 0, n->stream, (const double*)n->spart, HW, n->s,
+                     n->T, ga);
   Tensor x0{n->x0, P.H, P.W, CP};
   Tensor* z = n->z;
   float** gm = n->gam;
-  conv(n, x0, nullptr, L_IN, z[L_IN], false, 0);
+  // the input map goes into the first layer and the output map into the last
+  // where x0 and z_out are not needed again
+  const bool fused = !out ? false : conv_in(n, in, z[L_IN]);
+  if (!fused) {
+    hipLaunchKernelGGL(k_pre, dim3(grid1((int64_t)B * HW)), dim3(RT), 0, n->stream, in, B, HW,
+                       n->s, n->x0);
+    conv(n, x0, nullptr, L_IN, z[L_IN], false, 0);
+  }
   conv(n, z[L_IN], gm[L_IN], L_E0A, z[L_E0A], false, 0);
-  conv(n, z[L_E0A], gm[L_E0A], L_E0B, z[L_E0B], false, 0);
-  pool(n, z[L_E0B], gm[L_E0B], n->pool[0]);
+  conv_pool(n, z[L_E0A], gm[L_E0A], L_E0B, n->pool[0]);
   conv(n, n->pool[0], nullptr, L_E1A, z[L_E1A], false, 0);
-  conv(n, z[L_E1A], gm[L_E1A], L_E1B, z[L_E1B], false, 0);
-  pool(n, z[L_E1B], gm[L_E1B], n->pool[1]);
+  conv_pool(n, z[L_E1A], gm[L_E1A], L_E1B, n->pool[1]);
   conv(n, n->pool[1], nullptr, L_E2A, z[L_E2A], false, 0);
-  conv(n, z[L_E2A], gm[L_E2A], L_E2B, z[L_E2B], false, 0);
-  pool(n, z[L_E2B], gm[L_E2B], n->pool[2]);
+  conv_pool(n, z[L_E2A], gm[L_E2A], L_E2B, n->pool[2]);
   conv(n, n->pool[2], nullptr, L_E3A, z[L_E3A], false, 0);
-  conv(n, z[L_E3A], gm[L_E3A], L_E3B, z[L_E3B], false, 0);
-  upadd(n, z[L_E3B], gm[L_E3B], z[L_E2B], gm[L_E2B], n->up[2]);
+  conv_up(n, z[L_E3A], gm[L_E3A], L_E3B, L_E2B, n->up[2], !out);
   conv(n, n->up[2], nullptr, L_D2A, z[L_D2A], false, 0);
-  conv(n, z[L_D2A], gm[L_D2A], L_D2B, z[L_D2B], false, 0);
-  upadd(n, z[L_D2B], gm[L_D2B], z[L_E1B], gm[L_E1B], n->up[1]);
+  conv_up(n, z[L_D2A], gm[L_D2A], L_D2B, L_E1B, n->up[1], !out);
   conv(n, n->up[1], nullptr, L_D1A, z[L_D1A], false, 0);
-  conv(n, z[L_D1A], gm[L_D1A], L_D1B, z[L_D1B], false, 0);
-  upadd(n, z[L_D1B], gm[L_D1B], z[L_E0B], gm[L_E0B], n->up[0]);
+  conv_up(n, z[L_D1A], gm[L_D1A], L_D1B, L_E0B, n->up[0], !out);
   conv(n, n->up[0], nullptr, L_D0A, z[L_D0A], false, 0);
   conv(n, z[L_D0A], gm[L_D0A], L_D0B, z[L_D0B], false, 0);
-  conv(n, z[L_D0B], gm[L_D0B], L_OUT, z[L_OUT], false, 0);
+  if (!out) {
+    conv(n, z[L_D0B], gm[L_D0B], L_OUT, z[L_OUT], false, 0);
+    return launch_check("surrogate forward");
+  }
+  ConvEpi E{};
+  E.out = out;
+  E.gain = gm[L_OUT];
+  E.in = in;
+  E.sv = n->s;
+  if (!conv(n, z[L_D0B], gm[L_D0B], L_OUT, z[L_OUT], false, 0, EPI_POST, E))
+    hipLaunchKernelGGL(k_post, dim3(grid1((int64_t)B * HW)), dim3(RT), 0, n->stream, in,
+                       (const float*)z[L_OUT].p, (const float*)gm[L_OUT], (const float*)n->s, B,
+                       HW, out);
   return launch_check("surrogate forward");
 }
 
@@ -957,13 +986,7 @@ lbm_status sg_forward(sg_net* n, const float* d_in, int32_t batch, int32_t circu
                       float* d_out) {
   if (!n || !d_in || !d_out) return fail(LBM_E_ARG, "null argument");
   if (batch < 1 || batch > n->P.B) return fail(LBM_E_ARG, "batch out of range");
-  lbm_status s = forward(n, d_in, batch, circular ? 1 : 0);
-  if (s) return s;
-  const int HW = n->P.H * n->P.W;
-  hipLaunchKernelGGL(k_post, dim3(grid1((int64_t)batch * HW)), dim3(RT), 0, n->stream, d_in,
-                     (const float*)n->z[L_OUT].p, (const float*)n->gam[L_OUT],
-                     (const float*)n->s, batch, HW, d_out);
-  return launch_check("surrogate post");
+  return forward(n, d_in, batch, circular ? 1 : 0, d_out);
 }
 
 lbm_status sg_train_step(sg_net* n, const float* d_in, const float* d_target, int32_t batch,
@@ -971,7 +994,7 @@ lbm_status sg_train_step(sg_net* n, const float* d_in, const float* d_target, in
   if (!n || !d_in || !d_target) return fail(LBM_E_ARG, "null argument");
   if (!n->P.train) return fail(LBM_E_STATE, "network created without training buffers");
   if (batch < 1 || batch > n->P.B) return fail(LBM_E_ARG, "batch out of range");
-  lbm_status s = forward(n, d_in, batch, circular ? 1 : 0);
+  lbm_status s = forward(n, d_in, batch, circular ? 1 : 0, nullptr);
   if (s) return s;
   const int HW = n->P.H * n->P.W;
   const int64_t np = (int64_t)batch * HW;

@@ -435,14 +435,148 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
 // dword of 16-byte piece q of staged row p
 __device__ __forceinline__ int swz(int p, int q) { return 16 * p + 4 * (q ^ ((p >> 1) & 3)); }
 
-template <int SPLIT, int WT>
+struct Mat {
+  float cK, cm, rho;
+};
+__device__ inline Mat material(const float* in, int64_t HW, int64_t p) {
+  const float lam = in[5 * HW + p], mu = in[6 * HW + p], rho = in[7 * HW + p];
+  Mat m;
+  m.cK = sqrtf((lam + mu) / rho);
+  m.cm = sqrtf(mu / rho);
+  m.rho = rho;
+  return m;
+}
+__device__ inline void phys_to_U(const float* f, int64_t HW, int64_t p, const Mat& m,
+                                 float U[5]) {
+  const float sxx = f[2 * HW + p] / m.rho, syy = f[3 * HW + p] / m.rho,
+              sxy = f[4 * HW + p] / m.rho;
+  U[0] = f[p];
+  U[1] = f[HW + p];
+  U[2] = -(sxx + syy) / (2.f * m.cK);
+  U[3] = -(sxx - syy) / (2.f * m.cm);
+  U[4] = -sxy / m.cm;
+}
+
+// physical output fields of a pixel from U
+__device__ inline void U_to_phys(const float U[5], float* o, int64_t HW, int64_t p, const Mat& m) {
+  o[p] = U[0];
+  o[HW + p] = U[1];
+  o[2 * HW + p] = -m.rho * (m.cK * U[2] + m.cm * U[3]);
+  o[3 * HW + p] = -m.rho * (m.cK * U[2] - m.cm * U[3]);
+  o[4 * HW + p] = -m.rho * (m.cm * U[4]);
+}
+
+// What a workgroup does with its sums besides (or instead of) writing Z: the
+// 2 x 2 pooling or the up-sampled skip sum of the layer's output, or the map
+// to the physical output fields, which as kernels of their own read Z back
+// (batch 32, 128 x 128: 27 us of pooling, 42 of skip sums and 16 of output
+// map per forward pass); one by one the operations of k_pool, k_upadd and
+// k_post.  EPI_POST is the network's last layer: only its first 16 output
+// channels are computed (5 are used).
+enum { EPI_NONE = 0, EPI_POOL = 1, EPI_UP = 2, EPI_POST = 3 };
+struct ConvEpi {
+  float* out;          // pooled [B][H/2][W/2][Cout], up-sampled [B][2H][2W][Cout] or fields
+  const float* gain;   // this layer's gains [B][Cout]
+  const float* skip;   // [B][2H][2W][Cout] (EPI_UP)
+  const float* sgain;  // the skip's gains [B][Cout]
+  const float* in;     // the network's input (EPI_POST)
+  const float* sv;     // its samples' RMS
+  int store;           // write Z as well (EPI_POOL, EPI_UP)
+};
+
+// the value of the lane holding the other pixel of a horizontal pair (m ^ 1)
+__device__ __forceinline__ float lane_pair(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
+}
+
+// A wave's sums: 4 rows from yy on, the lane's column xx, channels co + 16 nb
+// .. + 3 (lane 16 kq + m: channels 4 kq .. of 16, pixel m).
+template <int EPI, int NB>
+__device__ __forceinline__ void conv_epilogue(const f32x4 (&acc)[4][NB], float* __restrict__ Z,
+                                              const ConvEpi& E, int b, int yy, int xx, int m,
+                                              int kq, int co, int H, int W, int Cout) {
+  if (EPI == EPI_NONE || (EPI != EPI_POST && E.store)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float* zp = Z + (((int64_t)b * H + yy + r) * W + xx) * Cout + co;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4*>(zp + 16 * nb) = acc[r][nb];
+    }
+  }
+  if constexpr (EPI == EPI_POST) {
+    // lane (m, kq) takes pixel m of row kq: channels 0 .. 3 are in lane m,
+    // channel 4 in lane 16 + m
+    float z[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        const float v = __shfl(acc[r][0][c & 3], c < 4 ? m : 16 + m, 64);
+        z[c] = kq == r ? v : z[c];
+      }
+    const int64_t HW = (int64_t)H * W, p = (int64_t)(yy + kq) * W + xx;
+    const float* f = E.in + (int64_t)b * 8 * HW;
+    const Mat mt = material(f, HW, p);
+    float U[5];
+    phys_to_U(f, HW, p, mt, U);
+    const float* gp = E.gain + (int64_t)b * Cout;
+    const float sv = E.sv[b];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) U[c] = U[c] + sv * (gp[c] * z[c]);
+    U_to_phys(U, E.out + (int64_t)b * 5 * HW, HW, p, mt);
+  } else if constexpr (EPI != EPI_NONE) {
+    f32x4 gn[NB], sg[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      gn[nb] = *reinterpret_cast<const f32x4*>(E.gain + (int64_t)b * Cout + co + 16 * nb);
+      if (EPI == EPI_UP)
+        sg[nb] = *reinterpret_cast<const f32x4*>(E.sgain + (int64_t)b * Cout + co + 16 * nb);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        if constexpr (EPI == EPI_POOL) {
+          if (r & 1) continue;
+          const int64_t px = ((int64_t)b * (H / 2) + (yy + r) / 2) * (W / 2) + xx / 2;
+          f32x4 o;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float p = acc[r][nb][j] + lane_pair(acc[r][nb][j]);
+            const float q = acc[r + 1][nb][j] + lane_pair(acc[r + 1][nb][j]);
+            o[j] = 0.25f * gn[nb][j] * (p + q);
+          }
+          if (!(m & 1)) *reinterpret_cast<f32x4*>(E.out + px * Cout + co + 16 * nb) = o;
+        } else {
+          const int64_t p0 = ((int64_t)b * 2 * H + 2 * (yy + r)) * 2 * W + 2 * xx;
+          f32x4 k[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            k[e] = *reinterpret_cast<const f32x4*>(
+                E.skip + (p0 + (e >> 1) * 2 * W + (e & 1)) * Cout + co + 16 * nb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            f32x4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              o[j] = gn[nb][j] * acc[r][nb][j] + sg[nb][j] * k[e][j];
+            *reinterpret_cast<f32x4*>(E.out + (p0 + (e >> 1) * 2 * W + (e & 1)) * Cout + co +
+                                      16 * nb) = o;
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int SPLIT, int WT, int EPI>
 __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
                                                   const float* __restrict__ xscale,
                                                   const unsigned short* __restrict__ Whi,
                                                   const unsigned short* __restrict__ Wlo,
                                                   float* __restrict__ Z, int H, int W, int Cin,
-                                                  int Cout, int circular, int nwork) {
-  constexpr int NB = 2, CT = 16 * NB;
+                                                  int Cout, int circular, int nwork, ConvEpi E) {
+  constexpr int NB = EPI == EPI_POST ? 1 : 2, CT = 16 * NB;
   constexpr int RW = 256 / WT;  // rows of a tile
   constexpr int TR = RW + 2, TW = WT + 2;
   constexpr int NH = SPLIT == 3 ? 2 : 1;
@@ -459,7 +593,7 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
 
   // work items (pixel tile, channel block) in runs per XCD, whose L2 then
   // serves the halo rows and the channel blocks of a pixel tile
-  const int ncb = Cout / CT, tx = W / WT, tiles = (H / RW) * tx;
+  const int ncb = EPI == EPI_POST ? 1 : Cout / CT, tx = W / WT, tiles = (H / RW) * tx;
   const int xcd = blockIdx.x & 7, nq = nwork >> 3, nr = nwork & 7;
   const int first = xcd * nq + (xcd < nr ? xcd : nr), count = nq + (xcd < nr ? 1 : 0);
   const int stride = (gridDim.x + 7 - xcd) >> 3;  // workgroups of this XCD's run
@@ -483,9 +617,12 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
   };
   auto offsets = [&](int y, int x0) __attribute__((always_inline)) {
     live = 0u;
+    // (rows and columns recomputed for every tile: kept, they would spill)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int i = (int)threadIdx.x + 256 * k;
+      const int i = tid + 256 * k;
       const int row = (i >> 2) / TW, col = (i >> 2) - row * TW;
       const int yr = y + row - 1, xr = x0 + col - 1;
       // wrapped (at most one period; rows past the tile's end too)
@@ -624,12 +761,8 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
     }
     if (last) {
       // D[row = channel 4 kq + j][col = pixel m]
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float* zp = Z + (((int64_t)b * H + y + wy + r) * W + x0 + wx + m) * Cout + cb * CT + 4 * kq;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4*>(zp + 16 * nb) = acc[r][nb];
-      }
+      conv_epilogue<EPI, NB>(acc, Z, E, b, y + wy, x0 + wx + m, m, kq, cb * CT + 4 * kq, H, W,
+                             Cout);
     }
     if (!more) return;
     __syncthreads();  // every wave is done with this chunk's operands
@@ -639,6 +772,112 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
     y = yn;
     x0 = xn;
     cb = cbn;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The network's first layer from its physical input: the tile's pixels are
+// mapped to U / s as they are staged (the operations of k_pre), 5 channels
+// padded to 8, so a product of K = 32 holds 4 taps x 8 channels (lane group
+// kq tap 4 s + kq of step s; taps 9 .. 11 have zero weights) and the layer
+// takes 3 K steps instead of 9 and reads 32 B per pixel instead of 128.  Tile
+// of 8 x 32 pixels x 32 channels per workgroup, waves as in k_convw.  Bound by
+// the 128 B written per pixel (batch 32, 128 x 128: 25 us; input map and
+// layer as two kernels 23 + 42, batch 1, 256 x 256: 7.0 us).
+// ---------------------------------------------------------------------------
+template <int SPLIT>
+__global__ __launch_bounds__(256) void k_conv_in(const float* __restrict__ in,
+                                                 const float* __restrict__ sv,
+                                                 const unsigned short* __restrict__ Whi,
+                                                 const unsigned short* __restrict__ Wlo,
+                                                 float* __restrict__ Z, int H, int W,
+                                                 int circular) {
+  constexpr int WT = 32, RW = 8, TR = RW + 2, TW = WT + 2, NPX = TR * TW, CO = 32;
+  constexpr int NH = SPLIT == 3 ? 2 : 1;
+  __shared__ uint4 xt[NH][NPX];      // 8 channels of a pixel
+  __shared__ uint4 wt[NH][12 * CO];  // 8 input channels of (tap, output channel)
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int m = lane & 15, kq = lane >> 4;
+  const int wx = 16 * (wave & 1), wy = 4 * (wave >> 1);
+  const int tx = W / WT, tiles = (H / RW) * tx;
+  const int nt = (int)gridDim.x, xq = nt >> 3, xr = nt & 7, xcd = blockIdx.x & 7;
+  const int pt = xcd * xq + (xcd < xr ? xcd : xr) + (int)(blockIdx.x >> 3);
+  const int b = pt / tiles, rem = pt - b * tiles;
+  const int y = (rem / tx) * RW, x0 = (rem - (rem / tx) * tx) * WT;
+  const int64_t HW = (int64_t)H * W;
+  const float* f = in + (int64_t)b * 8 * HW;
+  const float r = 1.f / sv[b];
+  for (int i = threadIdx.x; i < 12 * CO; i += 256) {
+    const int t = i / CO, o = i - t * CO;
+    uint4 h = {0u, 0u, 0u, 0u}, l = {0u, 0u, 0u, 0u};
+    if (t < 9) {
+      h = *reinterpret_cast<const uint4*>(Whi + (t * CO + o) * 32);
+      if (SPLIT == 3) l = *reinterpret_cast<const uint4*>(Wlo + (t * CO + o) * 32);
+    }
+    // (channels 5 .. 7 meet zeros in the pixels)
+    wt[0][i] = h;
+    if (SPLIT == 3) wt[NH - 1][i] = l;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = (int)threadIdx.x + 256 * k;
+    if (i >= NPX) continue;
+    const int row = i / TW, col = i - row * TW;
+    const int yr = y + row - 1, xr2 = x0 + col - 1;
+    const int ys = yr < 0 ? yr + H : (yr >= H ? yr - H : yr);
+    const int xs = xr2 < 0 ? xr2 + W : (xr2 >= W ? xr2 - W : xr2);
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (circular || (ys == yr && xs == xr2)) {
+      const int64_t p = (int64_t)ys * W + xs;
+      float U[5];
+      phys_to_U(f, HW, p, material(f, HW, p), U);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) a[c] = U[c] * r;
+    }
+    uint32_t h[4], l[4];
+    split_pairs<SPLIT>(a, h, l);
+    xt[0][i] = (uint4){h[0], h[1], h[2], h[3]};
+    if (SPLIT == 3) xt[NH - 1][i] = (uint4){l[0], l[1], l[2], l[3]};
+  }
+  __syncthreads();
+  f32x4 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) acc[i][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int t = 4 * s + kq, tt = t < 9 ? t : 0;
+    bf16x8 xh[4], xl[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int d = (wy + i + tt / 3) * TW + wx + tt % 3 + m;
+      xh[i] = *reinterpret_cast<const bf16x8*>(&xt[0][d]);
+      if (SPLIT == 3) xl[i] = *reinterpret_cast<const bf16x8*>(&xt[NH - 1][d]);
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&wt[0][t * CO + 16 * nb + m]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[i][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xh[i], acc[i][nb], 0, 0, 0);
+      if (SPLIT == 3) {
+        const bf16x8 al = *reinterpret_cast<const bf16x8*>(&wt[NH - 1][t * CO + 16 * nb + m]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xl[i], acc[i][nb], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, xh[i], acc[i][nb], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float* zp = Z + (((int64_t)b * H + y + wy + i) * W + x0 + wx + m) * CO + 4 * kq;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) *reinterpret_cast<f32x4*>(zp + 16 * nb) = acc[i][nb];
   }
 }
 
