@@ -443,8 +443,7 @@ struct sg_net {
   const float* in;
   int64_t adam_step;
   bool weights_ready;
-  int conv_mode;  // 0: LDS-tiled kernel where it applies; 1: direct kernel only;
-                  // 2: tiled, weights from global memory
+  int conv_mode;  // 0: k_convw, k_convs; 1: direct kernel only; 2: k_convt
 };
 
 namespace {
@@ -502,21 +501,20 @@ void launch_conv_shape(int k, sg_net* n, const Tensor& x, const float* xscale,
   }
 }
 
-template <int SPLIT, int PB, int NB, bool WL, int WT>
+template <int SPLIT, int PB, int NB, int WT>
 void launch_convt(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
   constexpr int CT = PB * 16 * NB;
   dim3 grid((unsigned)((int64_t)n->B * x.H * x.W / 64), (unsigned)(cout / CT));
-  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WL, WT>), grid, dim3(256), 0, n->stream,
+  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WT>), grid, dim3(256), 0, n->stream,
                      (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout, n->circular,
                      accumulate);
 }
 
 // k_convw where it has a workgroup for every CU (256 pixels x 32 channels
 // each); two workgroups share a CU, each running through its share.  With
-// fewer, the 64-pixel tiles of k_convt spread the layer over more CUs (256 x
-// 256, batch 1: 9.2 us against 11.9 for a layer of 32 channels, 256
-// workgroups; 128 x 128, 64 channels, has 128).
+// fewer, k_convs spreads the layer over more CUs (128 x 128 pixels, 64
+// channels, batch 1: 128 workgroups of k_convw 11.9 us, 512 of k_convs 9.8).
 template <int SPLIT, int WT>
 bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                const unsigned short* wl, Tensor& z, int cin, int cout, int epi, const ConvEpi& E) {
@@ -534,32 +532,61 @@ bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned s
   return true;
 }
 
-// The LDS-tiled kernel where the row is a multiple of 64 pixels or 32 or 16
-// pixels long and it gives at least 256 workgroups: 64 output channels per
-// workgroup (2 x 2 waves of 32 x 32) when that still gives 512 workgroups,
-// else 32 (4 waves of 16 pixels x 32 channels, weights staged in LDS too),
-// or 16 where 32 gives fewer than 256 workgroups.
+// k_convs for the layers with fewer pixels
+template <int SPLIT, int NG, int TR>
+void launch_convs(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
+                  const unsigned short* wl, Tensor& z, int cout, int epi, const ConvEpi& E) {
+  auto fn = epi == EPI_POOL   ? &k_convs<SPLIT, NG, TR, EPI_POOL>
+            : epi == EPI_UP   ? &k_convs<SPLIT, NG, TR, EPI_UP>
+                              : &k_convs<SPLIT, NG, TR, EPI_NONE>;
+  if constexpr (NG == 1)
+    if (epi == EPI_POST) fn = &k_convs<SPLIT, NG, TR, EPI_POST>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)((int64_t)n->B * x.H * x.W / (16 * TR) * (cout / 32))),
+                     dim3(128 * NG), 0, n->stream, (const float*)x.p, xscale, wh, wl, z.p, x.H,
+                     x.W, cout, n->circular, E);
+}
+
+template <int SPLIT>
+bool conv_small(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
+                const unsigned short* wl, Tensor& z, int cin, int cout, int epi,
+                const ConvEpi& E) {
+  if (x.W % 16 || x.H % 8) return false;
+  const int64_t work = (int64_t)n->B * x.H * x.W / 64 * (cout / 32);
+  switch (cin) {
+    case 32: launch_convs<SPLIT, 1, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
+    case 64: launch_convs<SPLIT, 2, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
+    case 128:
+      // (a workgroup fills its CU)
+      if (work > 256)
+        launch_convs<SPLIT, 4, 8>(n, x, xscale, wh, wl, z, cout, epi, E);
+      else
+        launch_convs<SPLIT, 4, 4>(n, x, xscale, wh, wl, z, cout, epi, E);
+      return true;
+  }
+  return false;
+}
+
+// The tiled kernel of conv mode 2, where the row is a multiple of 64 pixels or
+// 32 or 16 pixels long and it gives at least 256 workgroups: 64 output
+// channels per workgroup (2 x 2 waves of 32 x 32) when that still gives 512
+// workgroups, else 32 (4 waves of 16 pixels x 32 channels), or 16 where 32
+// gives fewer than 256 workgroups.
 template <int SPLIT, int WT>
 void conv_tiled_w(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
   const int64_t tiles = (int64_t)n->B * x.H * x.W / 64;
   if (cout % 64 == 0 && tiles * (cout / 64) >= 512)
-    launch_convt<SPLIT, 2, 2, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
-  else if (tiles * (cout / 32) < 256 && n->conv_mode == 2)
-    launch_convt<SPLIT, 1, 1, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+    launch_convt<SPLIT, 2, 2, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else if (tiles * (cout / 32) < 256)
-    // 16 output channels per workgroup, for enough workgroups
-    launch_convt<SPLIT, 1, 1, true, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
-  else if (n->conv_mode == 2)
-    launch_convt<SPLIT, 1, 2, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+    launch_convt<SPLIT, 1, 1, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else
-    launch_convt<SPLIT, 1, 2, true, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+    launch_convt<SPLIT, 1, 2, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
 }
 
 template <int SPLIT>
 bool conv_tiled(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                 const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
-  if (n->conv_mode == 1 || cin % 32 || cout % 32 || ((int64_t)x.H * x.W) % 64) return false;
+  if (n->conv_mode != 2 || cin % 32 || cout % 32 || ((int64_t)x.H * x.W) % 64) return false;
   // too few workgroups to fill the chip even with 16 output channels per
   // workgroup: the direct kernel splits the reduction over waves instead
   if ((int64_t)n->B * x.H * x.W / 64 * (cout / 16) < 256) return false;
@@ -584,11 +611,13 @@ bool conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, boo
   const int64_t pixels = (int64_t)n->B * x.H * x.W;
   if (n->conv_mode == 0 && !accumulate &&
       (n->P.split == 3 ? conv_wide<3, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_wide<3, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E)
+                             conv_wide<3, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                             conv_small<3>(n, x, xscale, wh, wl, z, cin, cout, epi, E)
                        : conv_wide<1, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E)))
+                             conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                             conv_small<1>(n, x, xscale, wh, wl, z, cin, cout, epi, E)))
     return true;
-  // the LDS-tiled kernel splits its input tiles itself
+  // modes 1 and 2; the tiled kernel splits its input tiles itself
   if (n->P.split == 3 ? conv_tiled<3>(n, x, xscale, wh, wl, z, cin, cout, accumulate)
                       : conv_tiled<1>(n, x, xscale, wh, wl, z, cin, cout, accumulate))
     return false;

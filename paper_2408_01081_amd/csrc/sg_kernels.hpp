@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ X,
 // blocks), so the two give bitwise identical results.  Cin % 32 == 0,
 // Cout % CT == 0.
 // ---------------------------------------------------------------------------
-template <int SPLIT, int PB, int NB, bool WL, int WT>
+template <int SPLIT, int PB, int NB, int WT>
 __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
                                                const float* __restrict__ xscale,
                                                const unsigned short* __restrict__ Whi,
@@ -241,12 +241,8 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
   constexpr int TW = WT + 2;           // tile columns: WT pixels + one each side
   constexpr int PS = 20;               // dwords per tile pixel
   constexpr int NH = SPLIT == 3 ? 2 : 1;
-  // WL: the chunk's weights of the workgroup's CT channels for all 9 taps
-  // are staged in LDS as well ([hi/lo][tap][channel], PS dwords per channel)
-  constexpr int WS = WL ? 9 * CT * PS : 0;
-  __shared__ uint4 tile4[NH * (TR * TW * PS + WS) / 4];
+  __shared__ uint4 tile4[NH * TR * TW * PS / 4];
   uint32_t* tile = reinterpret_cast<uint32_t*>(tile4);
-  uint32_t* wtile = tile + NH * TR * TW * PS;
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = lane & 15, kq = lane >> 4;
@@ -266,19 +262,16 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[pb][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  // staging: thread t handles the items t, t + 256, ... of the tile (and of
-  // the weights); 256 is a multiple of 4, so its piece q of 8 channels is
-  // the same in every item.  A chunk's loads (input tile, gains, weights)
-  // are all issued before the first is used, so their latencies overlap, and
-  // those of the next chunk are in flight during this chunk's products.
+  // staging: thread t handles the items t, t + 256, ... of the tile; 256 is a
+  // multiple of 4, so its piece q of 8 channels is the same in every item.  A
+  // chunk's loads (input tile, gains) are all issued before the first is used,
+  // so their latencies overlap, and those of the next chunk are in flight
+  // during this chunk's products.
   constexpr int NTILE = TR * TW * 4, PER = (NTILE + 255) / 256;
-  constexpr int NWT = WL ? 9 * CT * 4 : 1, PERW = (NWT + 255) / 256;
   const int q = threadIdx.x & 3;
   float4 u0[PER], u1[PER];
   bool valid[PER];
   float sc[8];
-  // (dword arrays: arrays of uint4 were placed in scratch memory)
-  uint32_t wh[WL ? PERW : 1][4], wl[WL ? PERW : 1][4];
   auto issue = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -303,24 +296,6 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
       const float* sp = xscale + (int64_t)b * Cin + c0 + 8 * q;
 #pragma unroll
       for (int j = 0; j < 8; ++j) sc[j] = sp[j];
-    }
-    if (WL) {
-      // 9 taps x CT channels x 4 pieces of 8 input channels (from L2: every
-      // workgroup reads the same weights)
-#pragma unroll
-      for (int k = 0; k < PERW; ++k) {
-        const int i = threadIdx.x + 256 * k;
-        if (i < NWT) {
-          const int co = (i >> 2) % CT, t = (i >> 2) / CT;
-          const int64_t wo = ((int64_t)t * Cout + blockIdx.y * CT + co) * Cin + c0 + 8 * q;
-          const uint4 a = *reinterpret_cast<const uint4*>(Whi + wo);
-          wh[k][0] = a.x; wh[k][1] = a.y; wh[k][2] = a.z; wh[k][3] = a.w;
-          if (SPLIT == 3) {
-            const uint4 c = *reinterpret_cast<const uint4*>(Wlo + wo);
-            wl[k][0] = c.x; wl[k][1] = c.y; wl[k][2] = c.z; wl[k][3] = c.w;
-          }
-        }
-      }
     }
   };
   issue(0);
@@ -349,19 +324,6 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
       if (SPLIT == 3) *reinterpret_cast<uint4*>(tile + TR * TW * PS + d) = vl;
       }
     }
-    if (WL) {
-#pragma unroll
-      for (int k = 0; k < PERW; ++k) {
-        const int i = threadIdx.x + 256 * k;
-        if (i < NWT) {
-          const int co = (i >> 2) % CT, t = (i >> 2) / CT;
-          const int d = (t * CT + co) * PS + 4 * q;
-          *reinterpret_cast<uint4*>(wtile + d) = (uint4){wh[k][0], wh[k][1], wh[k][2], wh[k][3]};
-          if (SPLIT == 3)
-            *reinterpret_cast<uint4*>(wtile + WS + d) = (uint4){wl[k][0], wl[k][1], wl[k][2], wl[k][3]};
-        }
-      }
-    }
     if (c0 + 32 < Cin) issue(c0 + 32);
     __syncthreads();
 #pragma unroll
@@ -378,15 +340,9 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         bf16x8 bhi, blo;
-        if (WL) {
-          const int d = (t * CT + cw + 16 * nb + m) * PS + 4 * kq;
-          bhi = *reinterpret_cast<const bf16x8*>(wtile + d);
-          if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(wtile + WS + d);
-        } else {
-          const int64_t wo = ((int64_t)t * Cout + co0 + 16 * nb + m) * Cin + 8 * kq + c0;
-          bhi = *reinterpret_cast<const bf16x8*>(Whi + wo);
-          if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(Wlo + wo);
-        }
+        const int64_t wo = ((int64_t)t * Cout + co0 + 16 * nb + m) * Cin + 8 * kq + c0;
+        bhi = *reinterpret_cast<const bf16x8*>(Whi + wo);
+        if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(Wlo + wo);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
           acc[pb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[pb], bhi, acc[pb][nb], 0, 0, 0);
@@ -490,11 +446,13 @@ __device__ __forceinline__ float lane_pair(float v) {
 }
 
 // A wave's sums: 4 rows from yy on, the lane's column xx, channels co + 16 nb
-// .. + 3 (lane 16 kq + m: channels 4 kq .. of 16, pixel m).
-template <int EPI, int NB>
+// .. + 3 (lane 16 kq + m: channels 4 kq .. of 16, pixel m).  PRE: the skip
+// values of EPI_UP are in pre[row][pixel of 2 x 2].
+template <int EPI, int NB, bool PRE = false>
 __device__ __forceinline__ void conv_epilogue(const f32x4 (&acc)[4][NB], float* __restrict__ Z,
                                               const ConvEpi& E, int b, int yy, int xx, int m,
-                                              int kq, int co, int H, int W, int Cout) {
+                                              int kq, int co, int H, int W, int Cout,
+                                              const f32x4 (*pre)[4] = nullptr) {
   if (EPI == EPI_NONE || (EPI != EPI_POST && E.store)) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -552,8 +510,9 @@ __device__ __forceinline__ void conv_epilogue(const f32x4 (&acc)[4][NB], float* 
           f32x4 k[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            k[e] = *reinterpret_cast<const f32x4*>(
-                E.skip + (p0 + (e >> 1) * 2 * W + (e & 1)) * Cout + co + 16 * nb);
+            k[e] = PRE ? pre[r][e]
+                       : *reinterpret_cast<const f32x4*>(
+                             E.skip + (p0 + (e >> 1) * 2 * W + (e & 1)) * Cout + co + 16 * nb);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             f32x4 o;
@@ -773,6 +732,152 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
     x0 = xn;
     cb = cbn;
   }
+}
+
+// ---------------------------------------------------------------------------
+// The same convolution for layers with few pixels, where a workgroup's chain
+// of latencies is the layer's time: all NG = Cin / 32 chunks at once.  A
+// workgroup of 2 NG waves computes TR x 16 pixels x 32 output channels; wave
+// (g, h) takes chunk g and channels 16 h .. + 15, its weights read from global
+// memory (L2) straight into fragments while the chunks of the input tile are
+// loaded, converted and staged; the chunks' sums are added in LDS in chunk
+// order.  W % 16 == 0, H % TR == 0.
+// (Batch 1, 256 x 256: a layer of 64 x 64 pixels and 128 channels takes
+// 10.2 us, one of 32 x 32 9.0, one of 128 x 128 and 64 channels 9.8; with the
+// chunks one after the other 11.7, 12.0 and 10.2, and 3.4 to 4.9 for the
+// pooling or skip sum.  Batch 32 of 128 x 128, 16 x 16 pixels and 128 channels:
+// TR = 8 14.5 us, TR = 4 19.8, one after the other 18.2.)
+// ---------------------------------------------------------------------------
+template <int SPLIT, int NG, int TR, int EPI>
+__global__ __launch_bounds__(128 * NG) void k_convs(const float* __restrict__ X,
+                                                    const float* __restrict__ xscale,
+                                                    const unsigned short* __restrict__ Whi,
+                                                    const unsigned short* __restrict__ Wlo,
+                                                    float* __restrict__ Z, int H, int W, int Cout,
+                                                    int circular, ConvEpi E) {
+  constexpr int Cin = 32 * NG, NT = 128 * NG, TW = 18, NPX = (TR + 2) * TW;
+  constexpr int NH = SPLIT == 3 ? 2 : 1;
+  constexpr int XS = NPX * 16;  // dwords of a chunk's hi or lo part
+  constexpr int SUMS = (NG - 1) * 2 * TR * 64 * 4;  // dwords of the chunks' sums
+  __shared__ uint4 lds4[(NG * NH * XS > SUMS ? NG * NH * XS : SUMS) / 4];
+  uint32_t* tile = reinterpret_cast<uint32_t*>(lds4);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int m = lane & 15, kq = lane >> 4, q = threadIdx.x & 3;
+  const int g = wave >> 1, h = wave & 1;
+  const int ncb = Cout / 32, tx = W / 16, tiles = (H / TR) * tx;
+  const int nt = (int)gridDim.x, xq = nt >> 3, xr = nt & 7, xcd = blockIdx.x & 7;
+  const int item = xcd * xq + (xcd < xr ? xcd : xr) + (int)(blockIdx.x >> 3);
+  const int pt = item / ncb, cb = item - pt * ncb;
+  const int b = pt / tiles, rem = pt - b * tiles;
+  const int y = (rem / tx) * TR, x0 = (rem - (rem / tx) * tx) * 16;
+
+  // input pieces of 8 channels: (chunk, pixel, q)
+  constexpr int NTILE = NG * NPX * 4, PER = (NTILE + NT - 1) / NT;
+  float u[PER][8], sc[PER][8];
+  uint32_t live = 0u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = ((int)threadIdx.x + NT * k) >> 2;
+    const int c = i / NPX, p = i - c * NPX, row = p / TW, col = p - row * TW;
+    const int yr = y + row - 1, xr2 = x0 + col - 1;
+    const int ys = yr < 0 ? yr + H : (yr >= H ? yr - H : yr);
+    const int xs = xr2 < 0 ? xr2 + W : (xr2 >= W ? xr2 - W : xr2);
+    const bool v = c < NG && (circular || (ys == yr && xs == xr2));
+    live |= v ? 1u << k : 0u;
+    const int c0 = v ? 32 * c + 8 * q : 0;
+    const float* xp = X + (((int64_t)b * H + (v ? ys : 0)) * W + (v ? xs : 0)) * Cin + c0;
+    const float4 a = *reinterpret_cast<const float4*>(xp), d = *reinterpret_cast<const float4*>(xp + 4);
+    u[k][0] = a.x; u[k][1] = a.y; u[k][2] = a.z; u[k][3] = a.w;
+    u[k][4] = d.x; u[k][5] = d.y; u[k][6] = d.z; u[k][7] = d.w;
+    if (xscale) {
+      const float* sp = xscale + (int64_t)b * Cin + c0;
+      const float4 e = *reinterpret_cast<const float4*>(sp), f = *reinterpret_cast<const float4*>(sp + 4);
+      sc[k][0] = e.x; sc[k][1] = e.y; sc[k][2] = e.z; sc[k][3] = e.w;
+      sc[k][4] = f.x; sc[k][5] = f.y; sc[k][6] = f.z; sc[k][7] = f.w;
+    }
+  }
+  bf16x8 ah[9], al[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    const int wo = (t * Cout + cb * 32 + 16 * h + m) * Cin + 32 * g + 8 * kq;
+    ah[t] = *reinterpret_cast<const bf16x8*>(Whi + wo);
+    if (SPLIT == 3) al[t] = *reinterpret_cast<const bf16x8*>(Wlo + wo);
+  }
+  // (the skip values too, where the registers hold them)
+  constexpr bool PRE = EPI == EPI_UP && TR == 4;
+  f32x4 pre[4][4] = {};
+  if (PRE && g == 0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        pre[r][e] = *reinterpret_cast<const f32x4*>(
+            E.skip + (((int64_t)b * 2 * H + 2 * (y + r) + (e >> 1)) * 2 * W + 2 * (x0 + m) +
+                      (e & 1)) * Cout + cb * 32 + 16 * h + 4 * kq);
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = ((int)threadIdx.x + NT * k) >> 2;
+    if (NTILE % NT != 0 && k + 1 == PER && i >= NG * NPX) continue;
+    const int c = i / NPX, p = i - c * NPX;
+    float a[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      a[j] = xscale ? u[k][j] * sc[k][j] : u[k][j];
+      a[j] = live >> k & 1 ? a[j] : 0.f;
+    }
+    uint32_t hi[4], lo[4];
+    split_pairs<SPLIT>(a, hi, lo);
+    uint32_t* t = tile + c * NH * XS + swz(p, q);
+    *reinterpret_cast<uint4*>(t) = (uint4){hi[0], hi[1], hi[2], hi[3]};
+    if (SPLIT == 3) *reinterpret_cast<uint4*>(t + XS) = (uint4){lo[0], lo[1], lo[2], lo[3]};
+  }
+  __syncthreads();
+  f32x4 acc[TR / 4][4][1];
+#pragma unroll
+  for (int r = 0; r < TR; ++r) acc[r >> 2][r & 3][0] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  const uint32_t* mine = tile + g * NH * XS;
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx) {
+    bf16x8 xh[TR + 2], xl[TR + 2];
+#pragma unroll
+    for (int r = 0; r < TR + 2; ++r) {
+      const int d = swz(r * TW + dx + m, kq);
+      xh[r] = *reinterpret_cast<const bf16x8*>(mine + d);
+      if (SPLIT == 3) xl[r] = *reinterpret_cast<const bf16x8*>(mine + XS + d);
+    }
+#pragma unroll
+    for (int part = 0; part < SPLIT; ++part)
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int r = 0; r < TR; ++r)
+          acc[r >> 2][r & 3][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              part == 2 ? al[3 * dy + dx] : ah[3 * dy + dx], part == 1 ? xl[r + dy] : xh[r + dy],
+              acc[r >> 2][r & 3][0], 0, 0, 0);
+  }
+  if (NG > 1) {
+    f32x4* red = reinterpret_cast<f32x4*>(lds4);
+    __syncthreads();  // the tile is no longer read
+    if (g) {
+#pragma unroll
+      for (int r = 0; r < TR; ++r)
+        red[(((g - 1) * 2 + h) * TR + r) * 64 + lane] = acc[r >> 2][r & 3][0];
+    }
+    __syncthreads();
+    if (g) return;
+#pragma unroll
+    for (int k = 1; k < NG; ++k)
+#pragma unroll
+      for (int r = 0; r < TR; ++r)
+        acc[r >> 2][r & 3][0] += red[(((k - 1) * 2 + h) * TR + r) * 64 + lane];
+  }
+  if (EPI == EPI_POST && h) return;  // (channels 16 .. 31 are not used)
+#pragma unroll
+  for (int r = 0; r < TR / 4; ++r)
+    conv_epilogue<EPI, 1, PRE>(acc[r], Z, E, b, y + 4 * r, x0 + m, m, kq,
+                               cb * 32 + 16 * h + 4 * kq, H, W, Cout, pre);
 }
 
 // ---------------------------------------------------------------------------
@@ -1333,7 +1438,7 @@ __global__ __launch_bounds__(256, 2) void k_wgradw(const float* __restrict__ G,
       for (int dx = 0; dx < 3; ++dx) {
         const uint32_t* base = xt + r * TW * 16;
         const bf16x8 xh = frag(base, xa[dx][0], xa[dx][1]);
-        bf16x8 xl;
+        bf16x8 xl = xh;  // (plain BF16 operands: not used)
         if (SPLIT == 3) xl = frag(base + XS, xa[dx][0], xa[dx][1]);
 #pragma unroll
         for (int part = 0; part < SPLIT; ++part)
