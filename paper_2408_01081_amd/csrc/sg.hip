@@ -34,10 +34,7 @@ using lbmh::round_up;
 
 namespace {
 
-constexpr int NBASIS = 4;
 constexpr int CP = 32;  // padded input/output channels
-constexpr double THETA_LO = 8.0 * M_PI / 180.0;
-constexpr double THETA_HI = 45.0 * M_PI / 180.0;
 
 struct LayerSpec {
   const char* name;
@@ -50,6 +47,7 @@ const LayerSpec kLayers[] = {
     {"e3b", 128, 128, 3}, {"d2a", 128, 128, 2}, {"d2b", 128, 64, 2},  {"d1a", 64, 64, 1},
     {"d1b", 64, 32, 1},   {"d0a", 32, 32, 0},   {"d0b", 32, 32, 0},   {"out", 32, 32, 0}};
 constexpr int NL = (int)(sizeof(kLayers) / sizeof(kLayers[0]));
+static_assert(NL == NLAYER, "SampleStats size");
 enum { L_IN, L_E0A, L_E0B, L_E1A, L_E1B, L_E2A, L_E2B, L_E3A, L_E3B, L_D2A, L_D2B, L_D1A,
        L_D1B, L_D0A, L_D0B, L_OUT };
 
@@ -68,19 +66,20 @@ __device__ inline double wg_sum(double v, double* sh) {
   return r;
 }
 
-// Per-sample statistics in two passes: SB workgroups per sample sum |U|^2,
-// c_K and c_mu over their pixels (FP64), then one workgroup per sample adds
-// the SB partial sums in a fixed order and forms s_b and the Chebyshev values
-// T[b][m].
-constexpr int SB = 64;  // workgroups per sample in the first pass
-
+// Per-sample statistics in two passes: stats_chunks(HW) workgroups per sample
+// sum |U|^2, c_K and c_mu over their pixels (FP64), then sample_stats (the
+// workgroups at the end of k_conv_in's grid, or k_stats) adds the partial sums
+// in a fixed order and forms s_b, the Chebyshev values T[b][m] and the gains.
+// (256 x 256, batch 1: 64 workgroups of 4 pixels per thread 6.2 us, 256 of one
+// 3.7; the rest 8.3 us as a launch of its own, 4.7 with the loads ahead of the
+// sums, and hidden behind the first layer.)
 __global__ __launch_bounds__(RT) void k_stats_partial(const float* __restrict__ in, int HW,
                                                       double* __restrict__ part) {
-  __shared__ double sh[RT];
+  __shared__ double sh[3][RT / 64];
   const int b = blockIdx.y;
   const float* f = in + (int64_t)b * 8 * HW;
   double u2 = 0.0, ck = 0.0, cm = 0.0;
-  for (int p = blockIdx.x * RT + threadIdx.x; p < HW; p += SB * RT) {
+  for (int p = blockIdx.x * RT + threadIdx.x; p < HW; p += gridDim.x * RT) {
     const Mat m = material(f, HW, p);
     float U[5];
     phys_to_U(f, HW, p, m, U);
@@ -88,57 +87,22 @@ __global__ __launch_bounds__(RT) void k_stats_partial(const float* __restrict__ 
     ck += m.cK;
     cm += m.cm;
   }
-  u2 = wg_sum(u2, sh);
-  ck = wg_sum(ck, sh);
-  cm = wg_sum(cm, sh);
-  if (threadIdx.x == 0) {
-    double* o = part + ((int64_t)b * SB + blockIdx.x) * 3;
-    o[0] = u2;
-    o[1] = ck;
-    o[2] = cm;
-  }
-}
-
-// the FiLM gains of every layer, gamma[l][b][c] = sum_k a_l[c][k] T[b][k]
-// (formed by k_stats, which has just formed T)
-struct GammaArgs {
-  const float* a[NL];
-  float* g[NL];
-  int cout[NL];
-  int total;  // sum of cout
-};
-
-__global__ __launch_bounds__(RT) void k_stats(const double* __restrict__ part, int HW,
-                                              float* __restrict__ sv, float* __restrict__ T,
-                                              GammaArgs ga) {
-  __shared__ double sh[RT];
-  __shared__ float Ts[NBASIS];
-  const int b = blockIdx.x;
-  const double* q = part + (int64_t)b * SB * 3;
-  const bool mine = (int)threadIdx.x < SB;
-  const double u2 = wg_sum(mine ? q[3 * threadIdx.x] : 0.0, sh);
-  const double ck = wg_sum(mine ? q[3 * threadIdx.x + 1] : 0.0, sh);
-  const double cm = wg_sum(mine ? q[3 * threadIdx.x + 2] : 0.0, sh);
-  if (threadIdx.x == 0) {
-    const double s = sqrt(u2 / (5.0 * HW));
-    sv[b] = (float)(s > 0 ? s : 1.0);
-    const double th = atan2(cm, ck);
-    const double t = 2.0 * (th - THETA_LO) / (THETA_HI - THETA_LO) - 1.0;
-    double Tm[NBASIS];
-    Tm[0] = 1.0;
-    Tm[1] = t;
-    for (int k = 2; k < NBASIS; ++k) Tm[k] = 2.0 * t * Tm[k - 1] - Tm[k - 2];
-    for (int k = 0; k < NBASIS; ++k) T[b * NBASIS + k] = Ts[k] = (float)Tm[k];
+  u2 = wave_total(u2);
+  ck = wave_total(ck);
+  cm = wave_total(cm);
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = u2;
+    sh[1][threadIdx.x >> 6] = ck;
+    sh[2][threadIdx.x >> 6] = cm;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < ga.total; e += RT) {
-    int c = e, l = 0;
-    while (c >= ga.cout[l]) c -= ga.cout[l++];
-    float s = 0.f;
-    for (int k = 0; k < NBASIS; ++k) s = fmaf(ga.a[l][c * NBASIS + k], Ts[k], s);
-    ga.g[l][b * ga.cout[l] + c] = s;
+  if (threadIdx.x < 3) {
+    const double* q = sh[threadIdx.x];
+    part[((int64_t)b * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = (q[0] + q[1]) + (q[2] + q[3]);
   }
 }
+
+__global__ __launch_bounds__(RT) void k_stats(SampleStats st) { sample_stats(st, blockIdx.x); }
 
 // x0[b][p][c] = U_c / s_b for c < 5, 0 otherwise
 __global__ __launch_bounds__(RT) void k_pre(const float* __restrict__ in, int B, int HW,
@@ -387,7 +351,7 @@ lbm_status make_plan(const sg_config* cfg, Plan* P) {
   P->o_T = take(B * NBASIS * 4);
   P->o_gam = take((size_t)NL * B * 128 * 4);
   P->o_part = take(((size_t)B * P->H * P->W / RT + 1) * 8);
-  P->o_spart = take((size_t)B * SB * 3 * 8);
+  P->o_spart = take((size_t)B * stats_chunks((int64_t)P->H * P->W) * 3 * 8);
   P->o_loss = take(8);
   P->o_x0 = take(act(0, CP));
   for (int l = 0; l < NL; ++l) P->o_z[l] = take(act(kLayers[l].level, kLayers[l].cout));
@@ -433,7 +397,7 @@ struct sg_net {
   float* gam[NL];
   double* fpart[NL];  // FiLM gradient chunk sums
   double* part;
-  double* spart;  // per-sample statistics partials [B][SB][3]
+  double* spart;  // per-sample statistics partials [B][stats_chunks][3]
   double* loss;
   float* x0;
   Tensor z[NL], pool[3], up[3], g[NL], gpool[3], gup[3];
@@ -644,15 +608,16 @@ void upadd(sg_net* n, const Tensor& coarse, const float* sc, const Tensor& skip,
                      out.p, n->B, out.H, out.W, out.C);
 }
 
-// the input map and the first layer in one launch, with k_convw's tiles
-bool conv_in(sg_net* n, const float* in, Tensor& z) {
+// the input map and the first layer in one launch, with k_convw's tiles, and
+// one workgroup per sample for what k_stats forms
+bool conv_in(sg_net* n, const float* in, Tensor& z, const SampleStats& st) {
   const int64_t work = (int64_t)n->B * z.H * z.W / 256;
   if (n->conv_mode != 0 || z.W % 32 || z.H % 8 || work < 256) return false;
-  hipLaunchKernelGGL(n->P.split == 3 ? &k_conv_in<3> : &k_conv_in<1>, dim3((unsigned)work),
-                     dim3(256), 0, n->stream, in, (const float*)n->s,
+  hipLaunchKernelGGL(n->P.split == 3 ? &k_conv_in<3> : &k_conv_in<1>, 
+                     dim3((unsigned)(work + n->B)), dim3(256), 0, n->stream, in,
                      (const unsigned short*)n->wfh + n->P.wq_off[L_IN],
                      (const unsigned short*)n->wfl + n->P.wq_off[L_IN], z.p, z.H, z.W,
-                     n->circular);
+                     n->circular, (int)work, st);
   return true;
 }
 
@@ -698,24 +663,22 @@ lbm_status forward(sg_net* n, const float* in, int B, int circular, float* out) 
   n->in = in;
   if (!n->weights_ready) prep_weights(n);
   const int HW = P.H * P.W;
-  hipLaunchKernelGGL(k_stats_partial, dim3(SB, B), dim3(RT), 0, n->stream, in, HW, n->spart);
-  GammaArgs ga;
-  ga.total = 0;
+  SampleStats st{n->spart, stats_chunks(HW), HW, n->s, n->T, {}, {}, {}};
   for (int l = 0; l < NL; ++l) {
-    ga.a[l] = n->param + P.aoff[l];
-    ga.g[l] = n->gam[l];
-    ga.cout[l] = kLayers[l].cout;
-    ga.total += kLayers[l].cout;
+    st.a[l] = n->param + P.aoff[l];
+    st.g[l] = n->gam[l];
+    st.cout[l] = kLayers[l].cout;
   }
-  hipLaunchKernelGGL(k_stats, dim3(B), dim3(RT), 0, n->stream, (const double*)n->spart, HW, n->s,
-                     n->T, ga);
+  hipLaunchKernelGGL(k_stats_partial, dim3(st.chunks, B), dim3(RT), 0, n->stream, in, HW,
+                     n->spart);
   Tensor x0{n->x0, P.H, P.W, CP};
   Tensor* z = n->z;
   float** gm = n->gam;
   // the input map goes into the first layer and the output map into the last
   // where x0 and z_out are not needed again
-  const bool fused = !out ? false : conv_in(n, in, z[L_IN]);
+  const bool fused = !out ? false : conv_in(n, in, z[L_IN], st);
   if (!fused) {
+    hipLaunchKernelGGL(k_stats, dim3(B), dim3(RT), 0, n->stream, st);
     hipLaunchKernelGGL(k_pre, dim3(grid1((int64_t)B * HW)), dim3(RT), 0, n->stream, in, B, HW,
                        n->s, n->x0);
     conv(n, x0, nullptr, L_IN, z[L_IN], false, 0);

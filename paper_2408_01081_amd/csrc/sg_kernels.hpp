@@ -13,6 +13,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace sgk {
@@ -420,6 +421,91 @@ __device__ inline void U_to_phys(const float U[5], float* o, int64_t HW, int64_t
   o[2 * HW + p] = -m.rho * (m.cK * U[2] + m.cm * U[3]);
   o[3 * HW + p] = -m.rho * (m.cK * U[2] - m.cm * U[3]);
   o[4 * HW + p] = -m.rho * (m.cm * U[4]);
+}
+
+// ---------------------------------------------------------------------------
+// Scale, Chebyshev values and FiLM gains of a sample
+// ---------------------------------------------------------------------------
+constexpr int NBASIS = 4;
+constexpr int NLAYER = 16;
+constexpr double THETA_LO = 8.0 * M_PI / 180.0;
+constexpr double THETA_HI = 45.0 * M_PI / 180.0;
+
+// partial sums per sample: a pixel per thread up to 256 workgroups
+inline int stats_chunks(int64_t HW) { return (int)(HW < 65536 ? (HW + 255) / 256 : 256); }
+
+struct SampleStats {
+  const double* part;  // [B][chunks][3]: sums of |U|^2, c_K, c_mu
+  int chunks, HW;
+  float* s;  // [B]
+  float* T;  // [B][NBASIS]
+  const float* a[NLAYER];  // gain coefficients [cout][NBASIS] of the layers
+  float* g[NLAYER];        // gains [B][cout]: sum_k a[c][k] T[b][k]
+  int cout[NLAYER];        // <= 128
+};
+
+// the sum over a wave, in every lane
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
+  return v;
+}
+
+// sum j of sample b's partial sums, in every lane
+__device__ __forceinline__ double sample_sum(const SampleStats& st, int b, int j) {
+  const double* q = st.part + (int64_t)b * st.chunks * 3 + j;
+  double v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int i = (int)(threadIdx.x & 63) + 64 * k;
+    v[k] = i < st.chunks ? q[3 * i] : 0.0;
+  }
+  return wave_total((v[0] + v[1]) + (v[2] + v[3]));
+}
+
+__device__ __forceinline__ float sample_scale(double u2, int HW) {
+  const double s = sqrt(u2 / (5.0 * HW));
+  return (float)(s > 0 ? s : 1.0);
+}
+
+// A workgroup of 256 for sample b.  A chain of latencies: the coefficients are
+// loaded before the sums that T needs, and every wave forms T itself.
+__device__ __forceinline__ void sample_stats(const SampleStats& st, int b) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  float a[NLAYER / 4][2][NBASIS];
+#pragma unroll
+  for (int i = 0; i < NLAYER / 4; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int l = wave + 4 * i, c = lane + 64 * h;
+      const float* p = st.a[l] + (c < st.cout[l] ? c : 0) * NBASIS;
+#pragma unroll
+      for (int k = 0; k < NBASIS; ++k) a[i][h][k] = p[k];
+    }
+  const double u2 = sample_sum(st, b, 0), ck = sample_sum(st, b, 1), cm = sample_sum(st, b, 2);
+  const double th = atan2(cm, ck);
+  const double t = 2.0 * (th - THETA_LO) / (THETA_HI - THETA_LO) - 1.0;
+  double Tm[NBASIS];
+  Tm[0] = 1.0;
+  Tm[1] = t;
+#pragma unroll
+  for (int k = 2; k < NBASIS; ++k) Tm[k] = 2.0 * t * Tm[k - 1] - Tm[k - 2];
+  if (threadIdx.x == 0) {
+    st.s[b] = sample_scale(u2, st.HW);
+#pragma unroll
+    for (int k = 0; k < NBASIS; ++k) st.T[b * NBASIS + k] = (float)Tm[k];
+  }
+#pragma unroll
+  for (int i = 0; i < NLAYER / 4; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int l = wave + 4 * i, c = lane + 64 * h;
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < NBASIS; ++k) s = fmaf(a[i][h][k], (float)Tm[k], s);
+      if (c < st.cout[l]) st.g[l][b * st.cout[l] + c] = s;
+    }
 }
 
 // What a workgroup does with its sums besides (or instead of) writing Z: the
@@ -888,31 +974,36 @@ __global__ __launch_bounds__(128 * NG) void k_convs(const float* __restrict__ X,
 // takes 3 K steps instead of 9 and reads 32 B per pixel instead of 128.  Tile
 // of 8 x 32 pixels x 32 channels per workgroup, waves as in k_convw.  Bound by
 // the 128 B written per pixel (batch 32, 128 x 128: 25 us; input map and
-// layer as two kernels 23 + 42, batch 1, 256 x 256: 7.0 us).
+// layer as two kernels 23 + 42, batch 1, 256 x 256: 7.0 us; with the scale
+// summed here and one more workgroup per sample for the gains 28 and 8.1, in
+// place of k_stats of 10 and 8).
 // ---------------------------------------------------------------------------
 template <int SPLIT>
 __global__ __launch_bounds__(256) void k_conv_in(const float* __restrict__ in,
-                                                 const float* __restrict__ sv,
                                                  const unsigned short* __restrict__ Whi,
                                                  const unsigned short* __restrict__ Wlo,
                                                  float* __restrict__ Z, int H, int W,
-                                                 int circular) {
+                                                 int circular, int work, SampleStats st) {
   constexpr int WT = 32, RW = 8, TR = RW + 2, TW = WT + 2, NPX = TR * TW, CO = 32;
   constexpr int NH = SPLIT == 3 ? 2 : 1;
   __shared__ uint4 xt[NH][NPX];      // 8 channels of a pixel
   __shared__ uint4 wt[NH][12 * CO];  // 8 input channels of (tap, output channel)
+  if ((int)blockIdx.x >= work) {
+    sample_stats(st, (int)blockIdx.x - work);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int m = lane & 15, kq = lane >> 4;
   const int wx = 16 * (wave & 1), wy = 4 * (wave >> 1);
   const int tx = W / WT, tiles = (H / RW) * tx;
-  const int nt = (int)gridDim.x, xq = nt >> 3, xr = nt & 7, xcd = blockIdx.x & 7;
+  const int nt = work, xq = nt >> 3, xr = nt & 7, xcd = blockIdx.x & 7;
   const int pt = xcd * xq + (xcd < xr ? xcd : xr) + (int)(blockIdx.x >> 3);
   const int b = pt / tiles, rem = pt - b * tiles;
   const int y = (rem / tx) * RW, x0 = (rem - (rem / tx) * tx) * WT;
   const int64_t HW = (int64_t)H * W;
   const float* f = in + (int64_t)b * 8 * HW;
-  const float r = 1.f / sv[b];
+  const float r = 1.f / sample_scale(sample_sum(st, b, 0), st.HW);
   for (int i = threadIdx.x; i < 12 * CO; i += 256) {
     const int t = i / CO, o = i - t * CO;
     uint4 h = {0u, 0u, 0u, 0u}, l = {0u, 0u, 0u, 0u};
