@@ -498,21 +498,55 @@ void err_accumulate(lbm_ctx* c, int64_t level) {
                      (const double*)c->err_part, nb, c->err_acc);
 }
 
-// V[s][link][2] = wall velocity of step `step0 + s` at every link
-__global__ void k_wall_eval(const float* __restrict__ W, const float* __restrict__ T, int rank,
-                            int L, int nsteps, float* __restrict__ V) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)nsteps * L) return;
-  const int s = (int)(i / L), link = (int)(i - (int64_t)s * L);
-  Wall w;
-  w.W = W;
-  w.Trow = T + (int64_t)s * rank;
-  w.rank = rank;
-  w.L = L;
-  float a, b;
-  wall_series(w, link, a, b);
-  V[2 * i] = a;
-  V[2 * i + 1] = b;
+// V[s][link][2] = wall velocity of step `step0 + s` at every link (the sum of
+// wall_series, in its order).  A thread forms WALL_STEPS steps of a link from
+// one read of its factors; all loads of 32 ranks are in flight at once, the
+// time factors by way of LDS.  Bound by that latency (2048 x 1024, rank 30, 20
+// steps: 5.1 us; a step per thread and a rank at a time 15.8, four steps
+// and 8 ranks at a time 16.3).
+constexpr int WALL_STEPS = 4, WALL_RANKS = 32;
+__global__ __launch_bounds__(256) void k_wall_eval(const float* __restrict__ W,
+                                                   const float* __restrict__ T, int rank, int L,
+                                                   int nsteps, float* __restrict__ V) {
+  __shared__ float ts[WALL_RANKS][WALL_STEPS];
+  const int link = (int)(blockIdx.x * 256 + threadIdx.x), s0 = (int)blockIdx.y * WALL_STEPS;
+  const int at = link < L ? link : L - 1;
+  float a[WALL_STEPS] = {}, b[WALL_STEPS] = {};
+  for (int r0 = 0; r0 < rank; r0 += WALL_RANKS) {
+    const int m = rank - r0 < WALL_RANKS ? rank - r0 : WALL_RANKS;
+    const int tk = (int)threadIdx.x / WALL_RANKS, tr = (int)threadIdx.x % WALL_RANKS;
+    float t = 0.f;
+    if (tk < WALL_STEPS && s0 + tk < nsteps && tr < m) t = T[(int64_t)(s0 + tk) * rank + r0 + tr];
+    float p[WALL_RANKS][2];
+#pragma unroll
+    for (int j = 0; j < WALL_RANKS; ++j) {
+      const float* q = W + ((int64_t)(r0 + (j < m ? j : 0)) * L + at) * 2;
+      p[j][0] = q[0];
+      p[j][1] = q[1];
+    }
+    if (r0) __syncthreads();  // the last ranks' factors are no longer read
+    if (tk < WALL_STEPS) ts[tr][tk] = t;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < WALL_RANKS; ++j) {
+      if (j < m) {
+#pragma unroll
+        for (int k = 0; k < WALL_STEPS; ++k) {
+          a[k] = fmaf(p[j][0], ts[j][k], a[k]);
+          b[k] = fmaf(p[j][1], ts[j][k], b[k]);
+        }
+      }
+    }
+  }
+  if (link >= L) return;
+#pragma unroll
+  for (int k = 0; k < WALL_STEPS; ++k) {
+    if (s0 + k < nsteps) {
+      float* v = V + ((int64_t)(s0 + k) * L + link) * 2;
+      v[0] = a[k];
+      v[1] = b[k];
+    }
+  }
 }
 
 lbm_status reduce(lbm_ctx* c, int mode, const double* ref, double out[2]) {
@@ -817,8 +851,9 @@ static_assert(kNumTBSplitVariants <= 8, "tbs_slots size");
 void eval_walls(lbm_ctx* c, int64_t step0, int n) {
   if (c->wall_rank == 0 || n <= 0) return;
   const int L = 2 * (c->g.nx + c->g.ny);
-  const int64_t total = (int64_t)n * L;
-  hipLaunchKernelGGL(k_wall_eval, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream,
+  hipLaunchKernelGGL(k_wall_eval,
+                     dim3((unsigned)((L + 255) / 256), (unsigned)((n + WALL_STEPS - 1) / WALL_STEPS)),
+                     dim3(256), 0, c->stream,
                      c->wall_W, c->wall_T + step0 * c->wall_rank, c->wall_rank, L, n, c->wall_v);
 }
 
