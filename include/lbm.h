@@ -303,11 +303,14 @@ lbm_status lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t use_cache, int32_t* 
  * the displacement state.  index -1 disables blocking; lbm_autotune
  * selects a variant when it is faster per step than the best single-step
  * configuration.  With a variant of T steps enabled, lbm_step(n) runs the
- * steps in chunks of floor(420 / T) T steps, T per launch; the r = n mod T
+ * steps T per launch; the r = n mod T
  * steps after the last full launch take one launch of an r-step variant
  * (the fastest one lbm_autotune timed, else the r-step variant of the
  * nearest launch shape; a tile variant takes them itself), or of the
- * single-step kernel for r = 1.  Row base
+ * single-step kernel for r = 1.  With launch times from lbm_autotune in
+ * this process and r > 0, the last launches of T steps and those r steps are
+ * divided into the launches whose times add up to least (not while the
+ * stream is captured).  Row base
  * addresses are 64-bit; only the byte offsets inside one row's 20 planes
  * ((19 plane strides + one row) * 4 B) must stay below 2^31, which fails
  * for the plane-major layout beyond about 28 M nodes and for rows of more
@@ -355,8 +358,8 @@ int32_t lbm_tblock_split_active(lbm_ctx* ctx, int32_t index);
  * Applies to lbm_step without a body load, displacement state or error
  * tracking.  LBM_E_ARG for a NULL argument or nsteps < 1. */
 lbm_status lbm_select_for_steps(lbm_ctx* ctx, int64_t nsteps, int32_t* h_index);
-/* The r-step blocked variant (r = 2 .. 10) lbm_step launches for the last r
- * steps of a run when r is below the selected variant's T: the fastest
+/* The r-step blocked variant (r = 2 .. 10) lbm_step launches for r of the
+ * last steps of a run when r is below the selected variant's T: the fastest
  * r-step variant lbm_autotune timed (kept in its cache file as well), else
  * the r-step variant nearest to the selected one's launch shape; a selected
  * tile variant itself, for r below its T.
@@ -456,7 +459,9 @@ lbm_status lbm_batch_set_wall_velocity(lbm_batch* b, int32_t i, int32_t rank, co
  * (one step per kernel, or T per kernel with a blocked variant selected; the
  * r = n mod T steps after the last full launch as one launch of an r-step
  * variant for r >= 2 -- the fastest one lbm_batch_autotune timed, else the
- * one nearest to the selected variant's shape -- or one step for r = 1). */
+ * one nearest to the selected variant's shape -- or one step for r = 1; after
+ * lbm_batch_autotune, for r > 0, the last launches as its times add up to
+ * least). */
 lbm_status lbm_batch_step(lbm_batch* b, int64_t n);
 
 /* Same steps launched one kernel at a time (no graph). */

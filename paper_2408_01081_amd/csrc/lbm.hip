@@ -1274,6 +1274,30 @@ static lbm_status step_extra_tiles(lbm_ctx* c, int64_t nsteps, int m) {
   return launch_check("k_tile launch (load / displacement)");
 }
 
+// the variant of a launch of t >= 2 steps: the selected one for its own number
+// of steps, remainder_variant's below it, above it the fastest the autotuner timed
+static int steps_variant(const lbm_ctx* c, int t) {
+  const int T = kTBVariants[c->tb_cfg].steps;
+  if (t == T) return c->tb_cfg;
+  return t < T ? remainder_variant(c, t, c->tb_cfg) : c->tb_rem[t];
+}
+
+// the launches of a run without load, displacement or error norms
+static LaunchPlan step_plan(const lbm_ctx* c, int64_t nsteps) {
+  if (c->tb_cfg < 0) return LaunchPlan{nsteps, 1, {}};
+  const int T = kTBVariants[c->tb_cfg].steps, r = (int)(nsteps % T);
+  double ms[TB_MAX_STEPS + 1] = {};
+  // (a tile variant takes any smaller number of steps itself)
+  if (r && !is_tile(c->tb_cfg) && c->step_launch_ms > 0.0 && !capturing(c->stream)) {
+    ms[1] = c->step_launch_ms;
+    for (int t = 2; t <= TB_MAX_STEPS; ++t) {
+      const int v = steps_variant(c, t);
+      if (v >= 0) ms[t] = c->tb_launch_ms[v];
+    }
+  }
+  return plan_launches(nsteps, T, remainder_variant(c, r, c->tb_cfg) >= 0, ms, TB_MAX_STEPS);
+}
+
 lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   if (!c) return fail(LBM_E_ARG, "null ctx");
   if (!c->initialised) return fail(LBM_E_STATE, "lbm_step before lbm_init");
@@ -1297,33 +1321,28 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   const StepConfig& cfg = kStepConfigs[c->step_cfg];
   const StepConst sc = step_const(cfg, g, (float)c->kK, (float)c->km);
   const StepFn fn = cfg.fn[c->p.bc];
-  // chunks of a multiple of T steps (at most WALL_CHUNK): the chunk's wall
-  // velocities are summed first, then its steps run, T per launch with a
-  // blocked variant; the r < T steps after the last full launch of a run take
-  // one launch of an r-step variant (r >= 2) or of the single-step kernel
-  const int T = c->tb_cfg >= 0 ? kTBVariants[c->tb_cfg].steps : 1;
-  const int chunk = WALL_CHUNK / T * T;
-  for (int64_t s0 = 0; s0 < nsteps; s0 += chunk) {
-    const int m = (int)(nsteps - s0 < chunk ? nsteps - s0 : chunk);
+  // chunks of whole launches (at most WALL_CHUNK steps): the chunk's wall
+  // velocities are summed first, then its launches run
+  const LaunchPlan plan = step_plan(c, nsteps);
+  const int64_t launches = plan.head + (int64_t)plan.tail.size();
+  auto steps_of = [&](int64_t l) { return l < plan.head ? plan.T : plan.tail[l - plan.head]; };
+  for (int64_t l = 0, s0 = 0; l < launches;) {
+    int64_t end = l;
+    int m = 0;
+    for (; end < launches && m + steps_of(end) <= WALL_CHUNK; ++end) m += steps_of(end);
     eval_walls(c, c->nstep + s0, m);
-    int k = 0;
-    if (T > 1) {
-      for (; k + T <= m; k += T) {
-        launch_tb(c, c->tb_cfg, c->buf[c->cur], c->buf[c->cur ^ 1], walls_from(c, k, true));
-        c->cur ^= 1;
-      }
-      const int ri = remainder_variant(c, m - k, c->tb_cfg);
-      if (ri >= 0) {
-        launch_tb(c, ri, c->buf[c->cur], c->buf[c->cur ^ 1], walls_from(c, k, true), m - k);
-        c->cur ^= 1;
-        k = m;
-      }
-    }
-    for (; k < m; ++k) {
-      hipLaunchKernelGGL(fn, dim3(sc.ntiles), dim3(cfg.threads), 0, c->stream,
-                         (const float*)c->buf[c->cur], c->buf[c->cur ^ 1], g, sc, wall_at(c, k));
+    for (int k = 0; l < end; ++l) {
+      const int t = steps_of(l);
+      if (t == 1)
+        hipLaunchKernelGGL(fn, dim3(sc.ntiles), dim3(cfg.threads), 0, c->stream,
+                           (const float*)c->buf[c->cur], c->buf[c->cur ^ 1], g, sc, wall_at(c, k));
+      else
+        launch_tb(c, steps_variant(c, t), c->buf[c->cur], c->buf[c->cur ^ 1],
+                  walls_from(c, k, true), t);
       c->cur ^= 1;
+      k += t;
     }
+    s0 += m;
   }
   c->nstep += nsteps;
   return launch_check("k_step launch");

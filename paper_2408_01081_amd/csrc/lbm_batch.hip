@@ -479,6 +479,7 @@ struct lbm_batch {
   bool any_wall;
   int tb_cfg;  // selected blocked variant, -1: one step per launch
   double tb_ms[kNumBatchTB];  // launch time of each variant the autotuner timed, -1: not timed
+  double step_ms;             // and of the single-step kernel
   // (steps, parity, blocked variant) -> graph, built while no instance has walls
   std::map<std::tuple<int64_t, int, int>, hipGraphExec_t> graphs;
 };
@@ -496,19 +497,19 @@ lbm_status upload_descs(lbm_batch* b) {
                    "descriptor upload");
 }
 
-// The blocked variant that takes the last r (2 <= r < T) steps of a run in
-// one launch after full launches of the selected variant: the fastest r-step
-// variant the autotuner timed, else the r-step variant nearest to the
-// selected one's shape (rows per segment, then store type and prefetch);
-// -1 if none (no variant selected, or r outside 2 .. 7).
-int remainder_variant(const lbm_batch* b, int r) {
-  if (b->tb_cfg < 0 || r < 2 || r >= kBatchTB[b->tb_cfg].steps) return -1;
-  const BatchTBConfig& t = kBatchTB[b->tb_cfg];
+// The blocked variant of a launch of t >= 2 steps: the selected one for its
+// own number of steps, else the fastest t-step variant the autotuner timed,
+// else the t-step variant nearest to the selected one's shape (rows per
+// segment, then store type and prefetch); -1 if none.
+int steps_variant(const lbm_batch* b, int t) {
+  if (b->tb_cfg < 0 || t < 2) return -1;
+  const BatchTBConfig& sel = kBatchTB[b->tb_cfg];
+  if (t == sel.steps) return b->tb_cfg;
   int best = -1, best_score = -1;
   double best_ms = 1e300;
   for (int i = 0; i < kNumBatchTB; ++i) {
     const BatchTBConfig& k = kBatchTB[i];
-    if (k.steps != r) continue;
+    if (k.steps != t) continue;
     if (b->tb_ms[i] > 0.0) {
       if (best_score < 8 || b->tb_ms[i] < best_ms) {
         best_score = 8;
@@ -517,8 +518,8 @@ int remainder_variant(const lbm_batch* b, int r) {
       }
       continue;
     }
-    const int score = (k.seg_rows == t.seg_rows ? 4 : 0) + (k.pf == t.pf ? 2 : 0) +
-                      (k.nt == t.nt ? 1 : 0);
+    const int score = (k.seg_rows == sel.seg_rows ? 4 : 0) + (k.pf == sel.pf ? 2 : 0) +
+                      (k.nt == sel.nt ? 1 : 0);
     if (score > best_score) {
       best_score = score;
       best = i;
@@ -527,20 +528,24 @@ int remainder_variant(const lbm_batch* b, int r) {
   return best;
 }
 
-// Steps per launch for `steps` steps: T per launch with a blocked variant,
-// then the r < T steps left as one launch of an r-step variant (r >= 2) or
-// one step.
+// Steps per launch for `steps` steps (plan_launches; without launch times T
+// per launch, then the r < T steps left as one launch of an r-step variant
+// (r >= 2) or one step).
 std::vector<int> launch_plan(const lbm_batch* b, int64_t steps) {
-  std::vector<int> p;
-  const int T = b->tb_cfg >= 0 ? kBatchTB[b->tb_cfg].steps : 1;
-  int64_t k = 0;
-  for (; T > 1 && k + T <= steps; k += T) p.push_back(T);
-  if (T > 1 && steps - k >= 2 && remainder_variant(b, (int)(steps - k)) >= 0) {
-    p.push_back((int)(steps - k));
-    k = steps;
+  if (b->tb_cfg < 0) return std::vector<int>(steps, 1);
+  const int T = kBatchTB[b->tb_cfg].steps, r = (int)(steps % T);
+  double ms[BATCH_TB_MAXT + 1] = {};
+  if (r && b->step_ms > 0.0 && !capturing(b->stream)) {
+    ms[1] = b->step_ms;
+    for (int t = 2; t <= BATCH_TB_MAXT; ++t) {
+      const int v = steps_variant(b, t);
+      if (v >= 0) ms[t] = b->tb_ms[v];
+    }
   }
-  for (; k < steps; ++k) p.push_back(1);
-  return p;
+  const LaunchPlan p = plan_launches(steps, T, steps_variant(b, r) >= 0, ms, BATCH_TB_MAXT);
+  std::vector<int> out(p.head, T);
+  out.insert(out.end(), p.tail.begin(), p.tail.end());
+  return out;
 }
 
 // Launch parameters of one launch advancing `t` steps from step index `step`
@@ -576,8 +581,7 @@ void make_launch(const lbm_batch* b, int t, int parity, int64_t step, LaunchArgs
     a->kp.func = reinterpret_cast<void*>(&k_batch_step<BT>);
     a->kp.gridDim = dim3((unsigned)a->ntiles);
   } else {
-    // the selected variant, or for the last steps of a run a shorter one
-    const int v = t == kBatchTB[b->tb_cfg].steps ? b->tb_cfg : remainder_variant(b, t);
+    const int v = steps_variant(b, t);
     const BatchTBConfig& k = kBatchTB[v];
     a->waves = b->d_waves + b->L.tb_wave0[v];
     a->nwaves = b->L.tb_waves[v];
@@ -726,6 +730,7 @@ lbm_status lbm_batch_create(int32_t n, const lbm_params* params, void* d_ws, siz
     b->L.desc[i].V = b->L.voff[i] >= 0 ? (float*)(b->ws + b->L.off_wallv) + b->L.voff[i] : nullptr;
   b->tb_cfg = -1;
   for (int v = 0; v < kNumBatchTB; ++v) b->tb_ms[v] = -1.0;
+  b->step_ms = -1.0;
   b->cur = 0;
   b->initialised = false;
   b->nstep = 0;
@@ -930,7 +935,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t reps, int32_t* h_index, doub
     float ms = 0.f;
     if (s == LBM_OK) s = hip_check(hipEventElapsedTime(&ms, e0, e1), "autotune timing");
     const double per = (double)ms / reps / t;
-    if (s == LBM_OK && v >= 0) b->tb_ms[v] = (double)ms / reps;
+    if (s == LBM_OK) (v >= 0 ? b->tb_ms[v] : b->step_ms) = (double)ms / reps;
     if (s == LBM_OK && per < best_ms) {
       best_ms = per;
       best = v;

@@ -9,6 +9,7 @@
 #include <stdio.h>
 
 #include <string>
+#include <vector>
 
 #include "lbm.h"
 #include "lbm_kernels.hpp"
@@ -35,6 +36,60 @@ inline lbm_status hip_check(hipError_t e, const char* what) {
 inline lbm_status launch_check(const char* what) { return hip_check(hipGetLastError(), what); }
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
+
+// The launches of a run of n steps: `head` of T steps, then those of `tail`.
+struct LaunchPlan {
+  int64_t head;
+  int T;
+  std::vector<int> tail;
+};
+
+// Plan of a run of n steps with a variant of T steps.  ms[t], 1 <= t <= maxt:
+// time of a launch of t steps, as far as known (else <= 0); one_launch: the
+// n mod T steps left take one launch (else one each).  Where every time
+// needed is known, the last up to eight launches of T steps and the steps left
+// are divided into the launches whose times add up to least, if that saves
+// more than the 1% by which such times scatter: a launch of one or two steps
+// costs as much as three or four more steps in a longer one (1000 x 777,
+// periodic: 7 steps 31 us, a single step 18.6; initialisation, 50 steps and
+// moments 262 us as 7 x 7 + 1, 251 so planned).
+inline LaunchPlan plan_launches(int64_t n, int T, bool one_launch, const double* ms, int maxt) {
+  LaunchPlan p{n / T, T, {}};
+  const int r = (int)(n % T);
+  if (r == 0) return p;
+  if (one_launch)
+    p.tail.assign(1, r);
+  else
+    p.tail.assign(r, 1);
+  const double rest = one_launch ? ms[r] : r * ms[1];
+  if (ms[T] <= 0.0 || rest <= 0.0) return p;
+  const int q = (int)(p.head < 8 ? p.head : 8), K = q * T + r;
+  std::vector<double> cost(K + 1, 1e300);
+  std::vector<int> last(K + 1, 0);
+  cost[0] = 0.0;
+  for (int k = 1; k <= K; ++k)
+    for (int t = 1; t <= maxt && t <= k; ++t)
+      if (ms[t] > 0.0 && cost[k - t] + ms[t] < cost[k]) {
+        cost[k] = cost[k - t] + ms[t];
+        last[k] = t;
+      }
+  if (cost[K] >= 0.99 * (q * ms[T] + rest)) return p;
+  p.head -= q;
+  p.tail.clear();
+  for (int k = K; k > 0; k -= last[k]) p.tail.push_back(last[k]);
+  return p;
+}
+
+// whether the stream is being captured (a captured run keeps the launches that
+// its step count alone determines)
+inline bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
 
 // Inverse of a symmetric positive definite 5x5 matrix by Cholesky
 // factorisation; returns false if the matrix is not positive definite.
