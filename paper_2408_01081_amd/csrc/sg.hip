@@ -363,9 +363,13 @@ lbm_status make_plan(const sg_config* cfg, Plan* P) {
     P->o_grad = take(np * 4);
     P->o_m = take(np * 4);
     P->o_v = take(np * 4);
-    // chunk sums of any batch up to B (B S <= FILM_WG + B)
-    for (int l = 0; l < NL; ++l)
-      P->o_fpart[l] = take(((size_t)FILM_WG + B) * kLayers[l].cout * 8);
+    // chunk sums of any batch up to B (B S <= FILM_WG + B, or a chunk per
+    // tile of k_convw)
+    for (int l = 0; l < NL; ++l) {
+      const size_t tiles = (size_t)B * (P->H >> kLayers[l].level) * (P->W >> kLayers[l].level) / 256;
+      const size_t chunks = (size_t)FILM_WG + B;
+      P->o_fpart[l] = take((chunks > tiles ? chunks : tiles) * kLayers[l].cout * 8);
+    }
     for (int l = 0; l < NL; ++l) P->o_g[l] = take(act(kLayers[l].level, kLayers[l].cout));
     for (int k = 0; k < 3; ++k) P->o_gpool[k] = take(act(k + 1, pc[k]));
     for (int k = 0; k < 3; ++k) P->o_gup[k] = take(act(k, uc[k]));
@@ -396,6 +400,7 @@ struct sg_net {
   float* T;
   float* gam[NL];
   double* fpart[NL];  // FiLM gradient chunk sums
+  int fchunks[NL];    // and their number per sample, 0 until the backward pass has them
   double* part;
   double* spart;  // per-sample statistics partials [B][stats_chunks][3]
   double* loss;
@@ -486,6 +491,7 @@ bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned s
   if (x.W % WT || x.H % (256 / WT) || work < 256) return false;
   auto fn = epi == EPI_POOL   ? &k_convw<SPLIT, WT, EPI_POOL>
             : epi == EPI_UP   ? &k_convw<SPLIT, WT, EPI_UP>
+            : epi == EPI_FILM ? &k_convw<SPLIT, WT, EPI_FILM>
                               : &k_convw<SPLIT, WT, EPI_NONE>;
   // (the last layer's rows are a multiple of 128 pixels)
   if constexpr (WT == 32)
@@ -573,14 +579,17 @@ bool conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, boo
   const unsigned short* wh = (backward ? n->wbh : n->wfh) + n->P.wq_off[l];
   const unsigned short* wl = (backward ? n->wbl : n->wfl) + n->P.wq_off[l];
   const int64_t pixels = (int64_t)n->B * x.H * x.W;
-  if (n->conv_mode == 0 && !accumulate &&
-      (n->P.split == 3 ? conv_wide<3, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_wide<3, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_small<3>(n, x, xscale, wh, wl, z, cin, cout, epi, E)
-                       : conv_wide<1, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
-                             conv_small<1>(n, x, xscale, wh, wl, z, cin, cout, epi, E)))
-    return true;
+  if (n->conv_mode == 0 && !accumulate) {
+    if (n->P.split == 3 ? conv_wide<3, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                              conv_wide<3, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E)
+                        : conv_wide<1, 32>(n, x, xscale, wh, wl, z, cin, cout, epi, E) ||
+                              conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E))
+      return true;
+    const int e = epi == EPI_FILM ? EPI_NONE : epi;
+    if (n->P.split == 3 ? conv_small<3>(n, x, xscale, wh, wl, z, cin, cout, e, E)
+                        : conv_small<1>(n, x, xscale, wh, wl, z, cin, cout, e, E))
+      return e == epi;
+  }
   // modes 1 and 2; the tiled kernel splits its input tiles itself
   if (n->P.split == 3 ? conv_tiled<3>(n, x, xscale, wh, wl, z, cin, cout, accumulate)
                       : conv_tiled<1>(n, x, xscale, wh, wl, z, cin, cout, accumulate))
@@ -623,7 +632,7 @@ bool conv_in(sg_net* n, const float* in, Tensor& z, const SampleStats& st) {
 
 // layer l followed by the pooling of its output
 void conv_pool(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& pooled) {
-  ConvEpi E{pooled.p, n->gam[l], nullptr, nullptr, nullptr, nullptr, 1};
+  ConvEpi E{pooled.p, n->gam[l], nullptr, nullptr, nullptr, nullptr, 1, nullptr};
   if (!conv(n, x, xscale, l, n->z[l], false, 0, EPI_POOL, E)) pool(n, n->z[l], n->gam[l], pooled);
 }
 
@@ -631,7 +640,7 @@ void conv_pool(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& p
 // layer's own output is needed again (the backward pass)
 void conv_up(sg_net* n, const Tensor& x, const float* xscale, int l, int skip, Tensor& out,
              int keep) {
-  ConvEpi E{out.p, n->gam[l], n->z[skip].p, n->gam[skip], nullptr, nullptr, keep};
+  ConvEpi E{out.p, n->gam[l], n->z[skip].p, n->gam[skip], nullptr, nullptr, keep, nullptr};
   if (!conv(n, x, xscale, l, n->z[l], false, 0, EPI_UP, E))
     upadd(n, n->z[l], n->gam[l], n->z[skip], n->gam[skip], out);
 }
@@ -713,18 +722,40 @@ lbm_status forward(sg_net* n, const float* in, int B, int circular, float* out) 
   return launch_check("surrogate forward");
 }
 
+// data gradient: conv with flipped, transposed weights of (gamma * gy).  The
+// FiLM sums of layer prev go with it where the chunks they leave to add in a
+// row are not more than FILM_TILES per sample (k_film_grad_part's are as many
+// at batch 1 of 512 x 512).
+constexpr int FILM_TILES = 1024;
+void data_grad(sg_net* n, int l, const Tensor& gy, Tensor& gin, int accumulate, int prev) {
+  if (!gin.p) return;
+  const int tiles = gin.H * gin.W / 256;
+  if (prev < 0 || tiles > FILM_TILES) {
+    conv(n, gy, n->gam[l], l, gin, true, accumulate);
+    return;
+  }
+  ConvEpi E{};
+  E.skip = n->z[prev].p;
+  E.part = n->fpart[prev];
+  if (conv(n, gy, n->gam[l], l, gin, true, accumulate, EPI_FILM, E)) n->fchunks[prev] = tiles;
+}
+
 // backward through conv layer l: g_y (dL/dy_l) -> parameter gradients and
-// dL/d(input of l) written to gin (accumulated if accumulate)
+// dL/d(input of l) written to gin (accumulated if accumulate); prev >= 0: gin
+// is dL/dy of that layer, whose FiLM sums the convolution then forms as well
 void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const float* xscale,
-               Tensor& gin, int accumulate) {
+               Tensor& gin, int accumulate, int prev = -1) {
   Plan& P = n->P;
   const LayerSpec& L = kLayers[l];
   const Tensor& zl = n->z[l];
   const int HW = zl.H * zl.W;
   // FiLM coefficients: the chunk sums now, the rest for all layers at the end
-  const int S = film_chunks(n->B, HW);
-  hipLaunchKernelGGL(k_film_grad_part, dim3((unsigned)(n->B * S)), dim3(RT), 0, n->stream, gy.p,
-                     zl.p, HW, L.cout, S, n->fpart[l]);
+  if (!n->fchunks[l]) {
+    const int S = film_chunks(n->B, HW);
+    hipLaunchKernelGGL(k_film_grad_part, dim3((unsigned)(n->B * S)), dim3(RT), 0, n->stream, gy.p,
+                       zl.p, HW, L.cout, S, n->fpart[l]);
+    n->fchunks[l] = S;
+  }
   // weights: dW = sum (gamma * gy) (x) (xscale * x)
   const int64_t pixels = (int64_t)n->B * HW;
   const int wt = zl.W % 32 == 0 && zl.H % 8 == 0 ? 32 : zl.W % 16 == 0 && zl.H % 16 == 0 ? 16 : 0;
@@ -743,7 +774,7 @@ void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const floa
     const int64_t nw = (int64_t)9 * L.cout * L.cin;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nw + 63) / 64)), dim3(RT), 0, n->stream,
                        (const float*)n->wpart, (int)ng, L.cin, L.cout, n->grad + P.woff[l]);
-    if (gin.p) conv(n, gy, n->gam[l], l, gin, true, accumulate);
+    data_grad(n, l, gy, gin, accumulate, prev);
     return;
   }
   const bool rows_fit = zl.W % 64 == 0 || (64 % zl.W == 0 && zl.H % (64 / zl.W) == 0);
@@ -768,7 +799,7 @@ void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const floa
     const int64_t nw = (int64_t)9 * L.cout * L.cin;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nw + 63) / 64)), dim3(RT), 0, n->stream,
                        (const float*)n->wpart, (int)ng, L.cin, L.cout, n->grad + P.woff[l]);
-    if (gin.p) conv(n, gy, n->gam[l], l, gin, true, accumulate);
+    data_grad(n, l, gy, gin, accumulate, prev);
     return;
   }
   int nsplit = 1;
@@ -799,8 +830,7 @@ void conv_back(sg_net* n, int l, const Tensor& gy, const Tensor& xin, const floa
   const int64_t nw = (int64_t)9 * L.cout * L.cin;
   hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nw + 63) / 64)), dim3(RT), 0, n->stream,
                      (const float*)n->wpart, nsplit, L.cin, L.cout, n->grad + P.woff[l]);
-  // data gradient: conv with flipped, transposed weights of (gamma * gy)
-  if (gin.p) conv(n, gy, n->gam[l], l, gin, true, accumulate);
+  data_grad(n, l, gy, gin, accumulate, prev);
 }
 
 void up_back(sg_net* n, const Tensor& g, Tensor& out) {
@@ -821,28 +851,29 @@ lbm_status backward(sg_net* n) {
   float** gm = n->gam;
   Tensor x0{n->x0, n->P.H, n->P.W, CP};
   Tensor none;
+  for (int l = 0; l < NL; ++l) n->fchunks[l] = 0;
   // g[L_OUT] holds dL/dy_out from the loss kernel
-  conv_back(n, L_OUT, g[L_OUT], z[L_D0B], gm[L_D0B], g[L_D0B], 0);
-  conv_back(n, L_D0B, g[L_D0B], z[L_D0A], gm[L_D0A], g[L_D0A], 0);
+  conv_back(n, L_OUT, g[L_OUT], z[L_D0B], gm[L_D0B], g[L_D0B], 0, L_D0B);
+  conv_back(n, L_D0B, g[L_D0B], z[L_D0A], gm[L_D0A], g[L_D0A], 0, L_D0A);
   conv_back(n, L_D0A, g[L_D0A], n->up[0], nullptr, n->gup[0], 0);       // dL/du0
   up_back(n, n->gup[0], g[L_D1B]);                                        // dL/dy_d1b
-  conv_back(n, L_D1B, g[L_D1B], z[L_D1A], gm[L_D1A], g[L_D1A], 0);
+  conv_back(n, L_D1B, g[L_D1B], z[L_D1A], gm[L_D1A], g[L_D1A], 0, L_D1A);
   conv_back(n, L_D1A, g[L_D1A], n->up[1], nullptr, n->gup[1], 0);       // dL/du1
   up_back(n, n->gup[1], g[L_D2B]);
-  conv_back(n, L_D2B, g[L_D2B], z[L_D2A], gm[L_D2A], g[L_D2A], 0);
+  conv_back(n, L_D2B, g[L_D2B], z[L_D2A], gm[L_D2A], g[L_D2A], 0, L_D2A);
   conv_back(n, L_D2A, g[L_D2A], n->up[2], nullptr, n->gup[2], 0);       // dL/du2
   up_back(n, n->gup[2], g[L_E3B]);
-  conv_back(n, L_E3B, g[L_E3B], z[L_E3A], gm[L_E3A], g[L_E3A], 0);
+  conv_back(n, L_E3B, g[L_E3B], z[L_E3A], gm[L_E3A], g[L_E3A], 0, L_E3A);
   conv_back(n, L_E3A, g[L_E3A], n->pool[2], nullptr, n->gpool[2], 0);   // dL/dp3
   pool_back(n, n->gpool[2], n->gup[2].p, g[L_E2B]);                      // + skip from u2
-  conv_back(n, L_E2B, g[L_E2B], z[L_E2A], gm[L_E2A], g[L_E2A], 0);
+  conv_back(n, L_E2B, g[L_E2B], z[L_E2A], gm[L_E2A], g[L_E2A], 0, L_E2A);
   conv_back(n, L_E2A, g[L_E2A], n->pool[1], nullptr, n->gpool[1], 0);
   pool_back(n, n->gpool[1], n->gup[1].p, g[L_E1B]);
-  conv_back(n, L_E1B, g[L_E1B], z[L_E1A], gm[L_E1A], g[L_E1A], 0);
+  conv_back(n, L_E1B, g[L_E1B], z[L_E1A], gm[L_E1A], g[L_E1A], 0, L_E1A);
   conv_back(n, L_E1A, g[L_E1A], n->pool[0], nullptr, n->gpool[0], 0);
   pool_back(n, n->gpool[0], n->gup[0].p, g[L_E0B]);
-  conv_back(n, L_E0B, g[L_E0B], z[L_E0A], gm[L_E0A], g[L_E0A], 0);
-  conv_back(n, L_E0A, g[L_E0A], z[L_IN], gm[L_IN], g[L_IN], 0);
+  conv_back(n, L_E0B, g[L_E0B], z[L_E0A], gm[L_E0A], g[L_E0A], 0, L_E0A);
+  conv_back(n, L_E0A, g[L_E0A], z[L_IN], gm[L_IN], g[L_IN], 0, L_IN);
   conv_back(n, L_IN, g[L_IN], x0, nullptr, none, 0);
   FilmArgs a;
   int groups = 0;
@@ -850,7 +881,7 @@ lbm_status backward(sg_net* n) {
     a.part[l] = n->fpart[l];
     a.da[l] = n->grad + n->P.aoff[l];
     a.cout[l] = kLayers[l].cout;
-    a.S[l] = film_chunks(n->B, z[l].H * z[l].W);
+    a.S[l] = n->fchunks[l];
     groups += kLayers[l].cout / 32;
   }
   hipLaunchKernelGGL(k_film_grad_coef, dim3((unsigned)groups), dim3(RT), 0, n->stream, a,

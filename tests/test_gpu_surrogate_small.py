@@ -43,3 +43,23 @@ def test_small_gradients_match_direct(B, H, W, circular):
         n = np.linalg.norm(grads[1][k])
         err = np.linalg.norm(grads[0][k] - grads[1][k]) / max(n, 1e-30)
         assert err < 2 * TOL, (k, err)
+
+
+@gpu
+@pytest.mark.parametrize("H,W", [(512, 512), (512, 640)])
+def test_gain_gradients_of_large_images_match_direct(H, W):
+    # up to 1024 tiles per sample the convolution forms the gain gradient's
+    # chunk sums, beyond that a kernel of their own
+    torch = _torch()
+    x = _input(torch, 1, H, W, 3)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    t = x[:, :5] + 0.1 * torch.randn(1, 5, H, W, device="cuda", generator=g)
+    grads = []
+    for mode in (0, 1):
+        net = _net(1, H, W, 3, mode, train=True)
+        net.train_step(x, t, circular=False, lr=0.0)
+        grads.append(S.unpack_params(net.get_grads().double().cpu().numpy()))
+    for k in grads[0]:
+        n = np.linalg.norm(grads[1][k])
+        err = np.linalg.norm(grads[0][k] - grads[1][k]) / max(n, 1e-30)
+        assert err < 2 * TOL, (k, err)
