@@ -346,8 +346,9 @@ def rerank(lat, fields, run_steps, top=4):
     stepping alternates two buffers, and a run of n steps pays for the launch
     that takes the n mod T steps after the last full one.  Time the
     autotuner's choice and the blocked variants its launch timing ranks best
-    per step by stepping runs of the benchmark's own length (run_steps steps
-    per call, repeated up to RERANK_STEPS steps), keep the fastest, and
+    per step by stepping runs of the benchmark's own length (the full launches,
+    then the steps left, in calls of their own as in the timed region; repeated
+    up to RERANK_STEPS steps), keep the fastest, and
     re-initialise the lattice (state and step count as before)."""
     import torch
     per_step = sorted((lat.time_tblock_config(c["index"], 5) / c["steps"], c["index"])
@@ -358,11 +359,13 @@ def rerank(lat, fields, run_steps, top=4):
     for idx in cands:
         lat.init(*fields)
         lat.tblock_config = idx
+        T = lat.steps_per_launch
         lat.step(64)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(reps):
-            lat.step(run_steps)
+            lat.step(run_steps - run_steps % T)
+            lat.step(run_steps % T)
         e1.record()
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1)
