@@ -309,8 +309,8 @@ lbm_status lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t use_cache, int32_t* 
  * nearest launch shape; a tile variant takes them itself), or of the
  * single-step kernel for r = 1.  With launch times from lbm_autotune in
  * this process and r > 0, the last launches of T steps and those r steps are
- * divided into the launches whose times add up to least (not while the
- * stream is captured).  Row base
+ * divided into as many launches or fewer, whose times add up to least (not
+ * while the stream is captured).  Row base
  * addresses are 64-bit; only the byte offsets inside one row's 20 planes
  * ((19 plane strides + one row) * 4 B) must stay below 2^31, which fails
  * for the plane-major layout beyond about 28 M nodes and for rows of more

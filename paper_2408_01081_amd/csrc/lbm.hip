@@ -47,7 +47,7 @@ constexpr int RED_THREADS = 256;
 // Device kernels
 // ---------------------------------------------------------------------------
 
-template <int SRC>
+template <int SRC, bool NT>
 __global__ __launch_bounds__(256) void k_init(const double* __restrict__ v0,
                                               const double* __restrict__ s0,
                                               const double* __restrict__ grad,
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ v0,
                                               Force F) {
   int x, y;
   if (!field_node(g, x, y)) return;
-  init_node<SRC, double>(v0, s0, grad, dst, g, k, x, y, F);
+  init_node<SRC, NT, double>(v0, s0, grad, dst, g, k, x, y, F);
 }
 
 // U_num(t_n) of a node from its stored post-collision populations:
@@ -670,8 +670,11 @@ lbm_status lbm_lattice_constants(const lbm_ctx* c, double* kK, double* km, doubl
 static lbm_status init_from(lbm_ctx* c, const double* d_v0, const double* d_s0,
                             const double* d_grad, int src) {
   const InitConst k = init_const(c->kK, c->km, c->cK, c->cmu, c->p.rho, c->p.dx, c->p.bc);
-  hipLaunchKernelGGL(src == INIT_FROM_STRESS ? &k_init<INIT_FROM_STRESS>
-                                             : &k_init<INIT_FROM_GRADIENT>,
+  const bool nt = state_bytes(c->g) > INIT_NT_BYTES;
+  hipLaunchKernelGGL(src == INIT_FROM_STRESS
+                         ? (nt ? &k_init<INIT_FROM_STRESS, true> : &k_init<INIT_FROM_STRESS, false>)
+                         : (nt ? &k_init<INIT_FROM_GRADIENT, true>
+                               : &k_init<INIT_FROM_GRADIENT, false>),
                      dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream, d_v0, d_s0,
                      d_grad, c->buf[0], c->g, k, force_at(c, 0));
   lbm_status s = launch_check("k_init launch");

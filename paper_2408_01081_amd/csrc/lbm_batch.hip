@@ -210,7 +210,7 @@ constexpr int kNumBatchTB = (int)(sizeof(kBatchTB) / sizeof(kBatchTB[0]));
 
 // packed = 0: v0 [..][2][ny][nx] and s0 [..][3][ny][nx] separate arrays;
 // packed = 1: one array [..][5][ny][nx] = (v, sigma_bar) in s0's place (v0 unused).
-template <typename T>
+template <typename T, bool NT>
 __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
                                                    const T* __restrict__ s0, int packed,
                                                    float* __restrict__ pool,
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const T* v = packed ? s0 + 5 * d.node0 : v0 + 2 * d.node0;
     const T* s = packed ? s0 + 5 * d.node0 + 2 * ni : s0 + 3 * d.node0;
-    init_node<INIT_FROM_STRESS, T>(v, s, nullptr, pool + d.off, d.g, d.ic, x, y);
+    init_node<INIT_FROM_STRESS, NT, T>(v, s, nullptr, pool + d.off, d.g, d.ic, x, y);
   });
 }
 
@@ -778,13 +778,14 @@ static lbm_status batch_init_any(lbm_batch* b, const void* v0, const void* s0, i
                                  bool f32) {
   const int64_t total = b->L.total_nodes;
   const unsigned grid = (unsigned)((total + BT - 1) / BT);
+  const bool nt = (size_t)b->L.pool_floats * 4 > INIT_NT_BYTES;
   if (f32)
-    hipLaunchKernelGGL(k_batch_init<float>, dim3(grid), dim3(BT), 0, b->stream,
-                       (const float*)v0, (const float*)s0, packed, b->pool[0],
+    hipLaunchKernelGGL((nt ? &k_batch_init<float, true> : &k_batch_init<float, false>), dim3(grid),
+                       dim3(BT), 0, b->stream, (const float*)v0, (const float*)s0, packed, b->pool[0],
                        (const InstDesc*)b->d_desc, b->n);
   else
-    hipLaunchKernelGGL(k_batch_init<double>, dim3(grid), dim3(BT), 0, b->stream,
-                       (const double*)v0, (const double*)s0, packed, b->pool[0],
+    hipLaunchKernelGGL((nt ? &k_batch_init<double, true> : &k_batch_init<double, false>),
+                       dim3(grid), dim3(BT), 0, b->stream, (const double*)v0, (const double*)s0, packed, b->pool[0],
                        (const InstDesc*)b->d_desc, b->n);
   lbm_status s = launch_check("batch init launch");
   if (s) return s;

@@ -154,9 +154,23 @@ __device__ inline void body_hat0(const Force& F, int x, int y, double& bx, doubl
 // with FP64 divisions in the conversion of all five nodes and its loads behind
 // the branches of the boundary rule, it took 789 us on 4096 x 4096 and 92 us
 // on 2048 x 1024; in this form with plain stores 536 and 38 us, with
-// nontemporal ones (the state is not read back before the whole pass has
-// ended) 515 and 37 us (3.9 and 6.9 TB/s).
-template <int SRC, typename T>
+// nontemporal ones 515 and 37 us (3.9 and 6.9 TB/s).  NT is for states whose
+// two buffers the last-level cache cannot hold: it keeps smaller ones out of
+// it, also for the launches after the first (initialisation, 45 steps in 9
+// launches and moments of 1794 x 559, three lattices in turn: 550 us with
+// nontemporal stores, 54 a launch, 470 with plain ones; 900 x 1500, 33 steps
+// 440 and 427; 2048 x 1024, 336 MB, 20 steps 389 and 402).
+constexpr size_t INIT_NT_BYTES = (size_t)128 << 20;  // half of the cache
+
+template <bool NT>
+__device__ __forceinline__ void init_store(float v, float* p) {
+  if (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+template <int SRC, bool NT, typename T>
 __device__ inline void init_node(const T* __restrict__ v0, const T* __restrict__ s0,
                                  const double* __restrict__ grad, float* __restrict__ dst,
                                  const Grid& g, const InitConst& k, int x, int y,
@@ -211,10 +225,10 @@ __device__ inline void init_node(const T* __restrict__ v0, const T* __restrict__
     const double e = fma(0.125, Bh[c], 0.25 * U[c]);
     const double ex = fma(0.125, P[c], e), ey = fma(-0.125, P[c], e);
     const double ox = fma(0.125, UX[c], A[c]), oy = fma(0.125, UY[c], B[c]);
-    __builtin_nontemporal_store((float)(ex + ox), dst + pidx(g, 0 * NC + c, y, x));
-    __builtin_nontemporal_store((float)(ey + oy), dst + pidx(g, 1 * NC + c, y, x));
-    __builtin_nontemporal_store((float)(ex - ox), dst + pidx(g, 2 * NC + c, y, x));
-    __builtin_nontemporal_store((float)(ey - oy), dst + pidx(g, 3 * NC + c, y, x));
+    init_store<NT>((float)(ex + ox), dst + pidx(g, 0 * NC + c, y, x));
+    init_store<NT>((float)(ey + oy), dst + pidx(g, 1 * NC + c, y, x));
+    init_store<NT>((float)(ex - ox), dst + pidx(g, 2 * NC + c, y, x));
+    init_store<NT>((float)(ey - oy), dst + pidx(g, 3 * NC + c, y, x));
   }
 }
 
