@@ -57,11 +57,11 @@ lbm_status sg_destroy(sg_net* net);
 
 /* Convolution kernel family: 0 (default) stages input tiles in LDS, with the
  * weights in LDS too where a layer has many pixels and all input channels at
- * once where it has few, and applies pooling, skip sums and the output map in
- * the producing kernel; 1 uses the direct kernel (operands read from global
- * memory) for every layer; 2 stages input tiles of 64 pixels and reads the
- * weights from global memory.  All compute the same products and sums (FP32
- * accumulation order may differ); for comparisons and timing. */
+ * once where it has few (split 3), and applies pooling, skip sums and the
+ * output map in the producing kernel; 1 uses the direct kernel (operands read
+ * from global memory) for every layer; 2 stages input tiles of 64 pixels and
+ * reads the weights from global memory.  All compute the same products and
+ * sums (FP32 accumulation order may differ); for comparisons and timing. */
 lbm_status sg_set_conv_mode(sg_net* net, int32_t mode);
 
 /* Copy the parameter vector in (resets the Adam state) or out, device to

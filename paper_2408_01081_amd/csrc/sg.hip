@@ -470,12 +470,12 @@ void launch_conv_shape(int k, sg_net* n, const Tensor& x, const float* xscale,
   }
 }
 
-template <int SPLIT, int PB, int NB, int WT>
+template <int SPLIT, int PB, int NB, bool WL, int WT>
 void launch_convt(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
   constexpr int CT = PB * 16 * NB;
   dim3 grid((unsigned)((int64_t)n->B * x.H * x.W / 64), (unsigned)(cout / CT));
-  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WT>), grid, dim3(256), 0, n->stream,
+  hipLaunchKernelGGL((k_convt<SPLIT, PB, NB, WL, WT>), grid, dim3(256), 0, n->stream,
                      (const float*)x.p, xscale, wh, wl, z.p, x.H, x.W, cin, cout, n->circular,
                      accumulate);
 }
@@ -502,61 +502,72 @@ bool conv_wide(sg_net* n, const Tensor& x, const float* xscale, const unsigned s
   return true;
 }
 
-// k_convs for the layers with fewer pixels
-template <int SPLIT, int NG, int TR>
+// k_convs for the layers with fewer pixels (hi/lo operands)
+template <int NG, int TR>
 void launch_convs(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cout, int epi, const ConvEpi& E) {
-  auto fn = epi == EPI_POOL   ? &k_convs<SPLIT, NG, TR, EPI_POOL>
-            : epi == EPI_UP   ? &k_convs<SPLIT, NG, TR, EPI_UP>
-                              : &k_convs<SPLIT, NG, TR, EPI_NONE>;
+  auto fn = epi == EPI_POOL   ? &k_convs<3, NG, TR, EPI_POOL>
+            : epi == EPI_UP   ? &k_convs<3, NG, TR, EPI_UP>
+                              : &k_convs<3, NG, TR, EPI_NONE>;
   if constexpr (NG == 1)
-    if (epi == EPI_POST) fn = &k_convs<SPLIT, NG, TR, EPI_POST>;
+    if (epi == EPI_POST) fn = &k_convs<3, NG, TR, EPI_POST>;
   hipLaunchKernelGGL(fn, dim3((unsigned)((int64_t)n->B * x.H * x.W / (16 * TR) * (cout / 32))),
                      dim3(128 * NG), 0, n->stream, (const float*)x.p, xscale, wh, wl, z.p, x.H,
                      x.W, cout, n->circular, E);
 }
 
-template <int SPLIT>
 bool conv_small(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                 const unsigned short* wl, Tensor& z, int cin, int cout, int epi,
                 const ConvEpi& E) {
   if (x.W % 16 || x.H % 8) return false;
   const int64_t work = (int64_t)n->B * x.H * x.W / 64 * (cout / 32);
   switch (cin) {
-    case 32: launch_convs<SPLIT, 1, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
-    case 64: launch_convs<SPLIT, 2, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
+    case 32: launch_convs<1, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
+    case 64: launch_convs<2, 4>(n, x, xscale, wh, wl, z, cout, epi, E); return true;
     case 128:
       // (a workgroup fills its CU)
       if (work > 256)
-        launch_convs<SPLIT, 4, 8>(n, x, xscale, wh, wl, z, cout, epi, E);
+        launch_convs<4, 8>(n, x, xscale, wh, wl, z, cout, epi, E);
       else
-        launch_convs<SPLIT, 4, 4>(n, x, xscale, wh, wl, z, cout, epi, E);
+        launch_convs<4, 4>(n, x, xscale, wh, wl, z, cout, epi, E);
       return true;
   }
   return false;
 }
 
-// The tiled kernel of conv mode 2, where the row is a multiple of 64 pixels or
-// 32 or 16 pixels long and it gives at least 256 workgroups: 64 output
-// channels per workgroup (2 x 2 waves of 32 x 32) when that still gives 512
-// workgroups, else 32 (4 waves of 16 pixels x 32 channels), or 16 where 32
-// gives fewer than 256 workgroups.
+// The 64-pixel tiled kernel, where the row is a multiple of 64 pixels or 32 or
+// 16 pixels long and it gives at least 256 workgroups: 64 output channels per
+// workgroup (2 x 2 waves of 32 x 32) when that still gives 512 workgroups, else
+// 32 (4 waves of 16 pixels x 32 channels), or 16 where 32 gives fewer than 256
+// workgroups.  In mode 0 it serves plain BF16's layers with few pixels, with
+// the weights staged in LDS too (batch 1, 128 x 384: 161 us a forward call,
+// 193 with the weights from global memory).
 template <int SPLIT, int WT>
 void conv_tiled_w(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                   const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
   const int64_t tiles = (int64_t)n->B * x.H * x.W / 64;
+  const bool few = tiles * (cout / 32) < 256;
   if (cout % 64 == 0 && tiles * (cout / 64) >= 512)
-    launch_convt<SPLIT, 2, 2, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
-  else if (tiles * (cout / 32) < 256)
-    launch_convt<SPLIT, 1, 1, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+    return launch_convt<SPLIT, 2, 2, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+  if constexpr (SPLIT == 1) {
+    if (n->conv_mode == 0) {
+      if (few)
+        launch_convt<SPLIT, 1, 1, true, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+      else
+        launch_convt<SPLIT, 1, 2, true, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+      return;
+    }
+  }
+  if (few)
+    launch_convt<SPLIT, 1, 1, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
   else
-    launch_convt<SPLIT, 1, 2, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
+    launch_convt<SPLIT, 1, 2, false, WT>(n, x, xscale, wh, wl, z, cin, cout, accumulate);
 }
 
 template <int SPLIT>
 bool conv_tiled(sg_net* n, const Tensor& x, const float* xscale, const unsigned short* wh,
                 const unsigned short* wl, Tensor& z, int cin, int cout, int accumulate) {
-  if (n->conv_mode != 2 || cin % 32 || cout % 32 || ((int64_t)x.H * x.W) % 64) return false;
+  if (n->conv_mode == 1 || cin % 32 || cout % 32 || ((int64_t)x.H * x.W) % 64) return false;
   // too few workgroups to fill the chip even with 16 output channels per
   // workgroup: the direct kernel splits the reduction over waves instead
   if ((int64_t)n->B * x.H * x.W / 64 * (cout / 16) < 256) return false;
@@ -586,11 +597,10 @@ bool conv(sg_net* n, const Tensor& x, const float* xscale, int l, Tensor& z, boo
                               conv_wide<1, 16>(n, x, xscale, wh, wl, z, cin, cout, epi, E))
       return true;
     const int e = epi == EPI_FILM ? EPI_NONE : epi;
-    if (n->P.split == 3 ? conv_small<3>(n, x, xscale, wh, wl, z, cin, cout, e, E)
-                        : conv_small<1>(n, x, xscale, wh, wl, z, cin, cout, e, E))
-      return e == epi;
+    if (n->P.split == 3 && conv_small(n, x, xscale, wh, wl, z, cin, cout, e, E)) return e == epi;
   }
-  // modes 1 and 2; the tiled kernel splits its input tiles itself
+  // modes 1 and 2, and plain BF16's layers with few pixels, whose sums keep the
+  // order they have there; the tiled kernel splits its input tiles itself
   if (n->P.split == 3 ? conv_tiled<3>(n, x, xscale, wh, wl, z, cin, cout, accumulate)
                       : conv_tiled<1>(n, x, xscale, wh, wl, z, cin, cout, accumulate))
     return false;
@@ -621,9 +631,9 @@ void upadd(sg_net* n, const Tensor& coarse, const float* sc, const Tensor& skip,
 // one workgroup per sample for what k_stats forms
 bool conv_in(sg_net* n, const float* in, Tensor& z, const SampleStats& st) {
   const int64_t work = (int64_t)n->B * z.H * z.W / 256;
-  if (n->conv_mode != 0 || z.W % 32 || z.H % 8 || work < 256) return false;
-  hipLaunchKernelGGL(n->P.split == 3 ? &k_conv_in<3> : &k_conv_in<1>, 
-                     dim3((unsigned)(work + n->B)), dim3(256), 0, n->stream, in,
+  // (its products take 4 taps at a time, another order of sums: see k_convw)
+  if (n->conv_mode != 0 || n->P.split != 3 || z.W % 32 || z.H % 8 || work < 256) return false;
+  hipLaunchKernelGGL(k_conv_in<3>, dim3((unsigned)(work + n->B)), dim3(256), 0, n->stream, in,
                      (const unsigned short*)n->wfh + n->P.wq_off[L_IN],
                      (const unsigned short*)n->wfl + n->P.wq_off[L_IN], z.p, z.H, z.W,
                      n->circular, (int)work, st);

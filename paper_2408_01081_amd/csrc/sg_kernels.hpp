@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ X,
 // blocks), so the two give bitwise identical results.  Cin % 32 == 0,
 // Cout % CT == 0.
 // ---------------------------------------------------------------------------
-template <int SPLIT, int PB, int NB, int WT>
+template <int SPLIT, int PB, int NB, bool WL, int WT>
 __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
                                                const float* __restrict__ xscale,
                                                const unsigned short* __restrict__ Whi,
@@ -242,8 +242,12 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
   constexpr int TW = WT + 2;           // tile columns: WT pixels + one each side
   constexpr int PS = 20;               // dwords per tile pixel
   constexpr int NH = SPLIT == 3 ? 2 : 1;
-  __shared__ uint4 tile4[NH * TR * TW * PS / 4];
+  // WL: the chunk's weights of the workgroup's CT channels for all 9 taps
+  // are staged in LDS as well ([hi/lo][tap][channel], PS dwords per channel)
+  constexpr int WS = WL ? 9 * CT * PS : 0;
+  __shared__ uint4 tile4[NH * (TR * TW * PS + WS) / 4];
   uint32_t* tile = reinterpret_cast<uint32_t*>(tile4);
+  uint32_t* wtile = tile + NH * TR * TW * PS;
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = lane & 15, kq = lane >> 4;
@@ -263,16 +267,19 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[pb][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  // staging: thread t handles the items t, t + 256, ... of the tile; 256 is a
-  // multiple of 4, so its piece q of 8 channels is the same in every item.  A
-  // chunk's loads (input tile, gains) are all issued before the first is used,
-  // so their latencies overlap, and those of the next chunk are in flight
-  // during this chunk's products.
+  // staging: thread t handles the items t, t + 256, ... of the tile (and of
+  // the weights); 256 is a multiple of 4, so its piece q of 8 channels is
+  // the same in every item.  A chunk's loads (input tile, gains, weights)
+  // are all issued before the first is used, so their latencies overlap, and
+  // those of the next chunk are in flight during this chunk's products.
   constexpr int NTILE = TR * TW * 4, PER = (NTILE + 255) / 256;
+  constexpr int NWT = WL ? 9 * CT * 4 : 1, PERW = (NWT + 255) / 256;
   const int q = threadIdx.x & 3;
   float4 u0[PER], u1[PER];
   bool valid[PER];
   float sc[8];
+  // (dword arrays: arrays of uint4 were placed in scratch memory)
+  uint32_t wh[WL ? PERW : 1][4], wl[WL ? PERW : 1][4];
   auto issue = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -297,6 +304,24 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
       const float* sp = xscale + (int64_t)b * Cin + c0 + 8 * q;
 #pragma unroll
       for (int j = 0; j < 8; ++j) sc[j] = sp[j];
+    }
+    if (WL) {
+      // 9 taps x CT channels x 4 pieces of 8 input channels (from L2: every
+      // workgroup reads the same weights)
+#pragma unroll
+      for (int k = 0; k < PERW; ++k) {
+        const int i = threadIdx.x + 256 * k;
+        if (i < NWT) {
+          const int co = (i >> 2) % CT, t = (i >> 2) / CT;
+          const int64_t wo = ((int64_t)t * Cout + blockIdx.y * CT + co) * Cin + c0 + 8 * q;
+          const uint4 a = *reinterpret_cast<const uint4*>(Whi + wo);
+          wh[k][0] = a.x; wh[k][1] = a.y; wh[k][2] = a.z; wh[k][3] = a.w;
+          if (SPLIT == 3) {
+            const uint4 c = *reinterpret_cast<const uint4*>(Wlo + wo);
+            wl[k][0] = c.x; wl[k][1] = c.y; wl[k][2] = c.z; wl[k][3] = c.w;
+          }
+        }
+      }
     }
   };
   issue(0);
@@ -325,6 +350,19 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
       if (SPLIT == 3) *reinterpret_cast<uint4*>(tile + TR * TW * PS + d) = vl;
       }
     }
+    if (WL) {
+#pragma unroll
+      for (int k = 0; k < PERW; ++k) {
+        const int i = threadIdx.x + 256 * k;
+        if (i < NWT) {
+          const int co = (i >> 2) % CT, t = (i >> 2) / CT;
+          const int d = (t * CT + co) * PS + 4 * q;
+          *reinterpret_cast<uint4*>(wtile + d) = (uint4){wh[k][0], wh[k][1], wh[k][2], wh[k][3]};
+          if (SPLIT == 3)
+            *reinterpret_cast<uint4*>(wtile + WS + d) = (uint4){wl[k][0], wl[k][1], wl[k][2], wl[k][3]};
+        }
+      }
+    }
     if (c0 + 32 < Cin) issue(c0 + 32);
     __syncthreads();
 #pragma unroll
@@ -341,9 +379,15 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         bf16x8 bhi, blo;
-        const int64_t wo = ((int64_t)t * Cout + co0 + 16 * nb + m) * Cin + 8 * kq + c0;
-        bhi = *reinterpret_cast<const bf16x8*>(Whi + wo);
-        if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(Wlo + wo);
+        if (WL) {
+          const int d = (t * CT + cw + 16 * nb + m) * PS + 4 * kq;
+          bhi = *reinterpret_cast<const bf16x8*>(wtile + d);
+          if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(wtile + WS + d);
+        } else {
+          const int64_t wo = ((int64_t)t * Cout + co0 + 16 * nb + m) * Cin + 8 * kq + c0;
+          bhi = *reinterpret_cast<const bf16x8*>(Whi + wo);
+          if (SPLIT == 3) blo = *reinterpret_cast<const bf16x8*>(Wlo + wo);
+        }
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
           acc[pb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[pb], bhi, acc[pb][nb], 0, 0, 0);
@@ -778,34 +822,57 @@ __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
       if (stage_w) fetch_w(cbn, cn);
     }
     __syncthreads();
-    // tap column by tap column: the six row fragments under it serve the
-    // three tap rows of all four pixel rows
+    if constexpr (SPLIT == 1) {
+      // taps in k_conv's order: with plain BF16 operands the order of a
+      // layer's sums decides roundings in every layer after it
+      bf16x8 x[3][6];
 #pragma unroll
-    for (int dx = 0; dx < 3; ++dx) {
-      bf16x8 xh[6], xl[6];
+      for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-      for (int r = 0; r < 6; ++r) {
-        const int d = swz((wy + r) * TW + wx + dx + m, kq);
-        xh[r] = *reinterpret_cast<const bf16x8*>(tile + d);
-        if (SPLIT == 3) xl[r] = *reinterpret_cast<const bf16x8*>(tile + XS + d);
-      }
+        for (int r = 0; r < 6; ++r)
+          x[dx][r] = *reinterpret_cast<const bf16x8*>(
+              tile + swz((wy + r) * TW + wx + dx + m, kq));
 #pragma unroll
-      for (int dy = 0; dy < 3; ++dy) {
+      for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          const int d = swz((3 * dy + dx) * CT + 16 * nb + m, kq);
-          const bf16x8 ah = *reinterpret_cast<const bf16x8*>(wtile + d);
+          const bf16x8 ah =
+              *reinterpret_cast<const bf16x8*>(wtile + swz(t * CT + 16 * nb + m, kq));
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xh[r + dy], acc[r][nb], 0, 0, 0);
-          if (SPLIT == 3) {
-            const bf16x8 al = *reinterpret_cast<const bf16x8*>(wtile + WS + d);
+            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, x[t % 3][r + t / 3],
+                                                                 acc[r][nb], 0, 0, 0);
+        }
+    } else {
+      // tap column by tap column: the six row fragments under it serve the
+      // three tap rows of all four pixel rows
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        bf16x8 xh[6], xl[6];
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+          const int d = swz((wy + r) * TW + wx + dx + m, kq);
+          xh[r] = *reinterpret_cast<const bf16x8*>(tile + d);
+          xl[r] = *reinterpret_cast<const bf16x8*>(tile + XS + d);
+        }
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            const int d = swz((3 * dy + dx) * CT + 16 * nb + m, kq);
+            const bf16x8 ah = *reinterpret_cast<const bf16x8*>(wtile + d);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xl[r + dy], acc[r][nb], 0, 0, 0);
+              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xh[r + dy], acc[r][nb], 0, 0, 0);
+            if (SPLIT == 3) {
+              const bf16x8 al = *reinterpret_cast<const bf16x8*>(wtile + WS + d);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, xh[r + dy], acc[r][nb], 0, 0, 0);
+              for (int r = 0; r < 4; ++r)
+                acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, xl[r + dy], acc[r][nb], 0, 0, 0);
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, xh[r + dy], acc[r][nb], 0, 0, 0);
+            }
           }
         }
       }

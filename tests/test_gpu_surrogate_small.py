@@ -63,3 +63,17 @@ def test_gain_gradients_of_large_images_match_direct(H, W):
         n = np.linalg.norm(grads[1][k])
         err = np.linalg.norm(grads[0][k] - grads[1][k]) / max(n, 1e-30)
         assert err < 2 * TOL, (k, err)
+
+
+@gpu
+@pytest.mark.parametrize("B,H,W,circular", [(1, 256, 256, False), (5, 384, 128, True),
+                                            (33, 64, 128, False), (2, 64, 128, True)])
+def test_plain_bf16_sums_keep_their_order(B, H, W, circular):
+    # with plain BF16 operands the order of a layer's sums decides the
+    # roundings of all layers after it: the wide kernel adds its products as
+    # the 64-pixel kernel does (mode 2), and the fused epilogues do what their
+    # kernels did, so the two give the same bits
+    torch = _torch()
+    x = _input(torch, B, H, W, B)
+    outs = [_net(B, H, W, 1, mode).forward(x, circular=circular) for mode in (0, 2)]
+    assert torch.equal(outs[0], outs[1])
