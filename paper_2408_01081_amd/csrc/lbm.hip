@@ -847,7 +847,7 @@ const TBTables& tb_tables() {
 static_assert(kNumTBVariants <= 64, "tb_slots size");
 static_assert(kNumTBExtVariants * 3 <= 48, "tbf_slots size");
 static_assert(kNumTBSplitVariants <= 8, "tbs_slots size");
-
+static_assert(TB_MAX_STEPS <= PLAN_MAX_STEPS, "LaunchPlan size");
 
 // Sum the wall velocities of steps step0 .. step0 + n - 1 (n <= WALL_CHUNK)
 // into the context's table; no-op without wall data.
@@ -1287,7 +1287,7 @@ static int steps_variant(const lbm_ctx* c, int t) {
 
 // the launches of a run without load, displacement or error norms
 static LaunchPlan step_plan(const lbm_ctx* c, int64_t nsteps) {
-  if (c->tb_cfg < 0) return LaunchPlan{nsteps, 1, {}};
+  if (c->tb_cfg < 0) return LaunchPlan{nsteps, 1, 0, {}};
   const int T = kTBVariants[c->tb_cfg].steps, r = (int)(nsteps % T);
   double ms[TB_MAX_STEPS + 1] = {};
   // (a tile variant takes any smaller number of steps itself)
@@ -1327,15 +1327,13 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   // chunks of whole launches (at most WALL_CHUNK steps): the chunk's wall
   // velocities are summed first, then its launches run
   const LaunchPlan plan = step_plan(c, nsteps);
-  const int64_t launches = plan.head + (int64_t)plan.tail.size();
-  auto steps_of = [&](int64_t l) { return l < plan.head ? plan.T : plan.tail[l - plan.head]; };
-  for (int64_t l = 0, s0 = 0; l < launches;) {
+  for (int64_t l = 0, s0 = 0; l < plan.launches();) {
     int64_t end = l;
     int m = 0;
-    for (; end < launches && m + steps_of(end) <= WALL_CHUNK; ++end) m += steps_of(end);
+    for (; end < plan.launches() && m + plan.steps(end) <= WALL_CHUNK; ++end) m += plan.steps(end);
     eval_walls(c, c->nstep + s0, m);
     for (int k = 0; l < end; ++l) {
-      const int t = steps_of(l);
+      const int t = plan.steps(l);
       if (t == 1)
         hipLaunchKernelGGL(fn, dim3(sc.ntiles), dim3(cfg.threads), 0, c->stream,
                            (const float*)c->buf[c->cur], c->buf[c->cur ^ 1], g, sc, wall_at(c, k));

@@ -360,6 +360,7 @@ struct Layout {
 };
 
 constexpr int BATCH_TB_MAXT = 8;  // most steps of a blocked launch: rows of a wall table
+static_assert(BATCH_TB_MAXT <= PLAN_MAX_STEPS, "LaunchPlan size");
 
 // wave table of blocked variant `v`: (instance, strip + nstrips * segment)
 // (Dirichlet instances first, or all waves with the Dirichlet rule first: 326
@@ -531,8 +532,8 @@ int steps_variant(const lbm_batch* b, int t) {
 // Steps per launch for `steps` steps (plan_launches; without launch times T
 // per launch, then the r < T steps left as one launch of an r-step variant
 // (r >= 2) or one step).
-std::vector<int> launch_plan(const lbm_batch* b, int64_t steps) {
-  if (b->tb_cfg < 0) return std::vector<int>(steps, 1);
+LaunchPlan launch_plan(const lbm_batch* b, int64_t steps) {
+  if (b->tb_cfg < 0) return LaunchPlan{steps, 1, 0, {}};
   const int T = kBatchTB[b->tb_cfg].steps, r = (int)(steps % T);
   double ms[BATCH_TB_MAXT + 1] = {};
   if (r && b->step_ms > 0.0 && !capturing(b->stream)) {
@@ -542,10 +543,7 @@ std::vector<int> launch_plan(const lbm_batch* b, int64_t steps) {
       if (v >= 0) ms[t] = b->tb_ms[v];
     }
   }
-  const LaunchPlan p = plan_launches(steps, T, steps_variant(b, r) >= 0, ms, BATCH_TB_MAXT);
-  std::vector<int> out(p.head, T);
-  out.insert(out.end(), p.tail.begin(), p.tail.end());
-  return out;
+  return plan_launches(steps, T, steps_variant(b, r) >= 0, ms, BATCH_TB_MAXT);
 }
 
 // Launch parameters of one launch advancing `t` steps from step index `step`
@@ -639,7 +637,9 @@ lbm_status build_graph(lbm_batch* b, int64_t steps, int cur, int64_t step0,
   hipGraphNode_t prev = nullptr;
   int parity = cur;
   int64_t step = step0;
-  for (int t : launch_plan(b, steps)) {
+  const LaunchPlan plan = launch_plan(b, steps);
+  for (int64_t l = 0; l < plan.launches(); ++l) {
+    const int t = plan.steps(l);
     hipGraphNode_t node;
     if (t > 1 && b->any_wall) {
       WallEvalArgs w;
@@ -850,7 +850,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t nsteps) {
     hipGraphExecDestroy(exec);
   }
   if (s) return s;
-  b->cur ^= (int)(launch_plan(b, nsteps).size() & 1);
+  b->cur ^= (int)(launch_plan(b, nsteps).launches() & 1);
   b->nstep += nsteps;
   return LBM_OK;
 }
@@ -862,10 +862,11 @@ lbm_status lbm_batch_step_eager(lbm_batch* b, int64_t nsteps) {
   for (int i = 0; i < b->n; ++i)
     if (b->L.desc[i].rank > 0 && b->nstep + nsteps > b->wall_nsteps[i])
       return fail(LBM_E_ARG, "wall table too short for the requested steps");
-  for (int t : launch_plan(b, nsteps)) {
-    launch_direct(b, t, b->cur, b->nstep);
+  const LaunchPlan plan = launch_plan(b, nsteps);
+  for (int64_t l = 0; l < plan.launches(); ++l) {
+    launch_direct(b, plan.steps(l), b->cur, b->nstep);
     b->cur ^= 1;
-    b->nstep += t;
+    b->nstep += plan.steps(l);
   }
   return launch_check("batch step launch");
 }

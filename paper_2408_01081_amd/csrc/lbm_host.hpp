@@ -9,10 +9,10 @@
 #include <stdio.h>
 
 #include <string>
-#include <vector>
 
 #include "lbm.h"
 #include "lbm_kernels.hpp"
+#include "lbm_plan.hpp"
 
 namespace lbmh {
 
@@ -36,65 +36,6 @@ inline lbm_status hip_check(hipError_t e, const char* what) {
 inline lbm_status launch_check(const char* what) { return hip_check(hipGetLastError(), what); }
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
-
-// The launches of a run of n steps: `head` of T steps, then those of `tail`.
-struct LaunchPlan {
-  int64_t head;
-  int T;
-  std::vector<int> tail;
-};
-
-// Plan of a run of n steps with a variant of T steps.  ms[t], 1 <= t <= maxt:
-// time of a launch of t steps, as far as known (else <= 0); one_launch: the
-// n mod T steps left take one launch (else one each).  Where every time
-// needed is known, the last up to four launches of T steps and the steps left
-// are divided into the launches, no more than these, whose times add up to
-// least, if that saves more than the 1% by which such times scatter: a launch
-// of one or two steps costs as much as three or four more steps in a longer
-// one (1000 x 777, periodic: 7 steps 31 us, a single step 18.6;
-// initialisation, 50 steps and moments 262 us as 7 x 7 + 1, 251 as 6 x 7 + 8).
-// More launches of fewer steps can look cheaper than they are, since the
-// autotuner's launches all read one buffer, which a cache may hold (900 x
-// 1500, 33 steps: 425 to 436 us with eight shorter launches allowed, 418 as
-// 5 x 6 + 3).
-inline LaunchPlan plan_launches(int64_t n, int T, bool one_launch, const double* ms, int maxt) {
-  LaunchPlan p{n / T, T, {}};
-  const int r = (int)(n % T);
-  if (r == 0) return p;
-  if (one_launch)
-    p.tail.assign(1, r);
-  else
-    p.tail.assign(r, 1);
-  const double rest = one_launch ? ms[r] : r * ms[1];
-  if (ms[T] <= 0.0 || rest <= 0.0) return p;
-  const int q = (int)(p.head < 4 ? p.head : 4), K = q * T + r;
-  const int most = q + (int)p.tail.size();
-  // cost[l (K + 1) + k]: k steps in l launches, last[..]: the last one's steps
-  std::vector<double> cost((size_t)(most + 1) * (K + 1), 1e300);
-  std::vector<int> last(cost.size(), 0);
-  cost[0] = 0.0;
-  int best = 0;
-  for (int l = 1; l <= most; ++l) {
-    const double* c0 = &cost[(size_t)(l - 1) * (K + 1)];
-    double* c1 = &cost[(size_t)l * (K + 1)];
-    for (int k = 1; k <= K; ++k)
-      for (int t = 1; t <= maxt && t <= k; ++t)
-        if (ms[t] > 0.0 && c0[k - t] + ms[t] < c1[k]) {
-          c1[k] = c0[k - t] + ms[t];
-          last[(size_t)l * (K + 1) + k] = t;
-        }
-    if (c1[K] < cost[(size_t)best * (K + 1) + K]) best = l;
-  }
-  if (cost[(size_t)best * (K + 1) + K] >= 0.99 * (q * ms[T] + rest)) return p;
-  p.head -= q;
-  p.tail.clear();
-  for (int l = best, k = K; l > 0; --l) {
-    const int t = last[(size_t)l * (K + 1) + k];
-    p.tail.push_back(t);
-    k -= t;
-  }
-  return p;
-}
 
 // whether the stream is being captured (a captured run keeps the launches that
 // its step count alone determines)
