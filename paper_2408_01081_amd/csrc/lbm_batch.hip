@@ -482,13 +482,13 @@ struct lbm_batch {
   double tb_ms[kNumBatchTB];  // launch time of each variant the autotuner timed, -1: not timed
   double step_ms;             // and of the single-step kernel
   // (steps, parity, blocked variant) -> graph, built while no instance has walls
-  std::map<std::tuple<int64_t, int, int>, hipGraphExec_t> graphs;
+  std::map<std::tuple<int64_t, int, int>, RunGraph<hipGraphExec_t>> graphs;
 };
 
 namespace {
 
 void drop_graphs(lbm_batch* b) {
-  for (auto& kv : b->graphs) hipGraphExecDestroy(kv.second);
+  for (auto& kv : b->graphs) hipGraphExecDestroy(kv.second.exec);
   b->graphs.clear();
 }
 
@@ -630,7 +630,7 @@ void make_wall_eval(const lbm_batch* b, int t, int64_t step, WallEvalArgs* a) {
 // Build a graph of the launches for `steps` steps starting from buffer `cur`
 // at step index `step0`.
 lbm_status build_graph(lbm_batch* b, int64_t steps, int cur, int64_t step0,
-                       hipGraphExec_t* exec) {
+                       RunGraph<hipGraphExec_t>* out) {
   hipGraph_t graph;
   lbm_status s = hip_check(hipGraphCreate(&graph, 0), "graph create");
   if (s) return s;
@@ -659,8 +659,9 @@ lbm_status build_graph(lbm_batch* b, int64_t steps, int cur, int64_t step0,
     parity ^= 1;
     step += t;
   }
-  if (s == LBM_OK) s = hip_check(hipGraphInstantiate(exec, graph, nullptr, nullptr, 0),
+  if (s == LBM_OK) s = hip_check(hipGraphInstantiate(&out->exec, graph, nullptr, nullptr, 0),
                                  "graph instantiate");
+  out->launches = plan.launches();
   hipGraphDestroy(graph);
   return s;
 }
@@ -832,25 +833,25 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t nsteps) {
     if (b->L.desc[i].rank > 0 && b->nstep + nsteps > b->wall_nsteps[i])
       return fail(LBM_E_ARG, "wall table too short for the requested steps");
   lbm_status s;
+  RunGraph<hipGraphExec_t> run;
   if (!b->any_wall) {
     auto key = std::make_tuple(nsteps, b->cur, b->tb_cfg);
     auto it = b->graphs.find(key);
     if (it == b->graphs.end()) {
-      hipGraphExec_t exec;
-      s = build_graph(b, nsteps, b->cur, 0, &exec);
+      s = build_graph(b, nsteps, b->cur, 0, &run);
       if (s) return s;
-      it = b->graphs.emplace(key, exec).first;
+      it = b->graphs.emplace(key, run).first;
     }
-    s = hip_check(hipGraphLaunch(it->second, b->stream), "graph launch");
+    run = it->second;
+    s = hip_check(hipGraphLaunch(run.exec, b->stream), "graph launch");
   } else {
-    hipGraphExec_t exec;
-    s = build_graph(b, nsteps, b->cur, b->nstep, &exec);
+    s = build_graph(b, nsteps, b->cur, b->nstep, &run);
     if (s) return s;
-    s = hip_check(hipGraphLaunch(exec, b->stream), "graph launch");
-    hipGraphExecDestroy(exec);
+    s = hip_check(hipGraphLaunch(run.exec, b->stream), "graph launch");
+    hipGraphExecDestroy(run.exec);
   }
   if (s) return s;
-  b->cur ^= (int)(launch_plan(b, nsteps).launches() & 1);
+  b->cur = run.buffer_after(b->cur);
   b->nstep += nsteps;
   return LBM_OK;
 }
@@ -920,6 +921,11 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t reps, int32_t* h_index, doub
       wall_left = b->wall_nsteps[i] - b->nstep;
   int best = -1;
   double best_ms = 1e300;
+  // the selection and the launch times stay as they are if a launch or its
+  // timing fails: cached graphs belong to them
+  const int was = b->tb_cfg;
+  double tb_ms[kNumBatchTB], step_ms = b->step_ms;
+  memcpy(tb_ms, b->tb_ms, sizeof tb_ms);
   // timed launches read the current pool and write the spare one: the state
   // is not changed
   for (int v = -1; v < kNumBatchTB && s == LBM_OK; ++v) {
@@ -937,7 +943,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t reps, int32_t* h_index, doub
     float ms = 0.f;
     if (s == LBM_OK) s = hip_check(hipEventElapsedTime(&ms, e0, e1), "autotune timing");
     const double per = (double)ms / reps / t;
-    if (s == LBM_OK) (v >= 0 ? b->tb_ms[v] : b->step_ms) = (double)ms / reps;
+    if (s == LBM_OK) (v >= 0 ? tb_ms[v] : step_ms) = (double)ms / reps;
     if (s == LBM_OK && per < best_ms) {
       best_ms = per;
       best = v;
@@ -945,14 +951,14 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t reps, int32_t* h_index, doub
   }
   hipEventDestroy(e0);
   hipEventDestroy(e1);
+  if (s == LBM_OK) s = hip_check(hipStreamSynchronize(b->stream), "batch sync");
+  b->tb_cfg = s ? was : best;
   if (s) return s;
   // the launch times decide the launches for the last steps of a run: rebuild
   // cached graphs
-  s = hip_check(hipStreamSynchronize(b->stream), "batch sync");
-  if (s) return s;
   drop_graphs(b);
-  s = lbm_batch_set_tblock_config(b, best);
-  if (s) return s;
+  memcpy(b->tb_ms, tb_ms, sizeof tb_ms);
+  b->step_ms = step_ms;
   if (h_index) *h_index = best;
   if (h_ms) *h_ms = best_ms;
   return LBM_OK;

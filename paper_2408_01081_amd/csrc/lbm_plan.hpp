@@ -71,4 +71,15 @@ inline LaunchPlan plan_launches(int64_t n, int T, bool one_launch, const double*
   return p;
 }
 
+// A cached graph of a run.  The buffer that holds the state after it follows
+// from the launches it was built with: a plan made later can divide the same
+// run into another number (launch times measured since, or a stream now being
+// captured).
+template <class Exec>
+struct RunGraph {
+  Exec exec;
+  int64_t launches;
+  int buffer_after(int cur) const { return cur ^ (int)(launches & 1); }
+};
+
 }  // namespace lbmh

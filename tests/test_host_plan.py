@@ -29,6 +29,12 @@ int64_t plan(int64_t n, int T, int one, const double* ms, int maxt, int cap, int
   for (int64_t l = 0; l < p.launches() && l < cap; ++l) out[l] = p.steps(l);
   return p.launches();
 }
+// the buffer after a run from buffer `cur` with a graph built from one plan
+int buffer_after(int64_t n, int T, int one, const double* ms, int maxt, int cur) {
+  const lbmh::LaunchPlan p = lbmh::plan_launches(n, T, one != 0, ms, maxt);
+  const lbmh::RunGraph<int> g{0, p.launches()};
+  return g.buffer_after(cur);
+}
 }
 """
 
@@ -132,3 +138,31 @@ def test_plans_do_not_allocate(lib):
             for one in (True, False):
                 _plan(lib, n, T, one, ms, 10)
     assert lib.count_allocations() == before
+
+
+def test_buffer_after_a_cached_graph_is_that_of_its_own_launches(lib):
+    # 9 steps with a 4-step variant: 4 + 4 + 1 before launch times are known,
+    # 4 + 5 with them.  A graph of either plan decides the buffer it leaves the
+    # state in, whatever plan would be made when it is launched again.
+    before = [0.0] * 11
+    after = [0.0, 18.0, 19.0, 20.0, 21.0, 22.0] + [0.0] * 5
+    assert _plan(lib, 9, 4, True, before, 8) == [4, 4, 1]
+    assert sorted(_plan(lib, 9, 4, True, after, 8)) == [4, 5]
+    for cur in (0, 1):
+        for ms, launches in ((before, 3), (after, 2)):
+            a = (ctypes.c_double * 11)(*ms)
+            assert lib.buffer_after(ctypes.c_int64(9), 4, 1, a, 8, cur) == cur ^ (launches & 1)
+
+
+def test_batch_step_advances_by_its_graph():
+    # the launch count after a graph launch comes from the graph, and a failed
+    # autotune leaves selection and launch times (the graphs' own) as they were
+    text = open(os.path.join(CSRC, "lbm_batch.hip")).read()
+    step = text[text.index("lbm_status lbm_batch_step(lbm_batch* b"):
+                text.index("lbm_status lbm_batch_step_eager")]
+    assert "launch_plan" not in step and "buffer_after" in step
+    tune = text[text.index("lbm_status lbm_batch_autotune(lbm_batch* b"):
+                text.index("static lbm_status batch_moments")]
+    loop = tune[tune.index("for (int v = -1"):tune.index("hipEventDestroy(e0);\n  hipEventDestroy(e1);\n  if (s ==")]
+    assert "b->tb_ms" not in loop and "b->step_ms" not in loop
+    assert tune.index("drop_graphs(b)") < tune.index("memcpy(b->tb_ms")
