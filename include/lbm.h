@@ -300,7 +300,10 @@ lbm_status lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t use_cache, int32_t* 
  * x R rows in registers and advances all of them one step at a time (rows
  * meet in LDS), storing 64 - 2T columns x R - 2T rows; it takes any number
  * of steps up to T per launch, also with a body load of rank <= 32 and/or
- * the displacement state.  index -1 disables blocking; lbm_autotune
+ * the displacement state (there with T <= 5 where a load leaves it 16 rows, and
+ * on periodic lattices only up to 1024 tiles, 512 with load and displacement,
+ * 256 with a load of rank > 16: beyond, the sweeps with these extras run as for
+ * other selections).  index -1 disables blocking; lbm_autotune
  * selects a variant when it is faster per step than the best single-step
  * configuration.  With a variant of T steps enabled, lbm_step(n) runs the
  * steps T per launch; the r = n mod T
@@ -355,8 +358,9 @@ int32_t lbm_tblock_split_active(lbm_ctx* ctx, int32_t index);
  * win over one that is faster per step (4096^2: T = 10 for 20-step runs,
  * against T = 8 per step).  Without such launch times (no lbm_autotune, or
  * its choice read from the cache file) the selection is unchanged.
- * Applies to lbm_step without a body load, displacement state or error
- * tracking.  LBM_E_ARG for a NULL argument or nsteps < 1. */
+ * The times are those of launches without body load and displacement state; a
+ * run with either follows the selection only in taking tiles where a tile
+ * variant is selected and otherwise the sweep nearest to it.  LBM_E_ARG for a NULL argument or nsteps < 1. */
 lbm_status lbm_select_for_steps(lbm_ctx* ctx, int64_t nsteps, int32_t* h_index);
 /* The r-step blocked variant (r = 2 .. 10) lbm_step launches for r of the
  * last steps of a run when r is below the selected variant's T: the fastest

@@ -1121,8 +1121,8 @@ bool extra_usable(const lbm_ctx* c, int i, int m) {
 
 // the whole-run variant with extras m (0 load, 1 displacement, 2 both) for a
 // lattice whose blocked variant is tb_cfg: the same launch shape if there is
-// one, else the same T, else the first for its boundary type; -1 if none
-// applies
+// one, else the same T, else the first for its boundary type (of a tile, whose
+// T says nothing about sweeps, always that); -1 if none applies
 int extra_variant(const lbm_ctx* c, int m) {
   if (c->tb_cfg < 0 || c->force_rank > TB_MAXR || !tblock_fits(c->g)) return -1;
   const TBVariant& t = kTBVariants[c->tb_cfg];
@@ -1130,6 +1130,7 @@ int extra_variant(const lbm_ctx* c, int m) {
   for (int i = 0; i < kNumTBExtVariants; ++i) {
     const TBExtVariant& k = kTBExtVariants[i];
     if (!k.main || !extra_usable(c, i, m)) continue;
+    if (is_tile(c->tb_cfg)) return i;
     if (k.steps == t.steps && k.seg_rows == t.seg_rows && k.nt == t.nt && k.pf == t.pf) return i;
     if (k.steps == t.steps && same_t < 0) same_t = i;
     if (first < 0) first = i;
@@ -1247,10 +1248,26 @@ static lbm_status step_extra_blocked(lbm_ctx* c, int64_t nsteps, int vi, int m) 
   return launch_check("k_tblock launch (load / displacement)");
 }
 
-// whether steps with extras take tiles: a tile variant is selected and the
-// load's rank has a kernel
-static bool extra_tiles(const lbm_ctx* c) {
-  return c->tb_cfg >= 0 && is_tile(c->tb_cfg) && c->force_rank <= TB_MAXR && tblock_fits(c->g);
+// Whether steps with extras m take tiles: a tile variant is selected, the
+// load's rank has a kernel, and a launch has no more tiles than pay.  The
+// selection was timed without the load, and with it tiles are cut to 16 rows
+// and store 6 of them at T = 5, so on periodic lattices the sweeps with extras
+// catch up once the tiles no longer fit the CUs in a round or two (us per step,
+// tiles against those sweeps): load of rank 32, 256^2 (215 tiles) 3.0 / 4.8,
+// 100 x 1500 (500) 5.4 / 5.2, 448^2 (675) 7.2 / 5.2; of rank 16, 384^2 (512)
+// 3.3 / 4.4, 512^2 (860) 5.2 / 5.7, 600^2 (1200) 6.1 / 5.8; of rank 32 with the
+// displacement state, 384^2 (512) 5.5 / 6.2, 416^2 (560) 7.6 / 6.7; of rank 16
+// with it 4.1 / 5.1, 5.7 / 5.6.  The displacement state alone leaves the tiles
+// nearly as they were timed (384^2: 2.2 / 3.4), and with walls the sweeps are
+// slower everywhere (160^2 to 600^2, rank 32: 2.9 / 14.7 to 11.9 / 15.7; one
+// step per launch 6.3 to 15.2).
+static bool extra_tiles(const lbm_ctx* c, int m) {
+  if (c->tb_cfg < 0 || !is_tile(c->tb_cfg) || c->force_rank > TB_MAXR || !tblock_fits(c->g))
+    return false;
+  if (m == 1 || c->p.bc == LBM_DIRICHLET) return true;
+  const TBConst sc = tile_const(c, c->tb_cfg, m, tile_steps_of(c, c->tb_cfg, m));
+  const int most = m == 2 ? 512 : c->force_rank > 16 ? 256 : 1024;
+  return (int64_t)sc.nstrips * sc.nseg <= most;
 }
 
 // Steps with a body load and/or the displacement state (no error norms) in
@@ -1315,7 +1332,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
     return fail(LBM_E_ARG, "reference table too short for the requested steps");
   if ((c->force_rank > 0 || c->disp) && !c->err_on) {
     const int m = c->force_rank > 0 ? (c->disp ? 2 : 0) : 1;
-    if (extra_tiles(c)) return step_extra_tiles(c, nsteps, m);
+    if (extra_tiles(c, m)) return step_extra_tiles(c, nsteps, m);
     const int vi = extra_variant(c, m);
     if (vi >= 0) return step_extra_blocked(c, nsteps, vi, m);
   }
@@ -1600,7 +1617,7 @@ int32_t lbm_steps_per_launch(const lbm_ctx* c) {
   if (c->err_on) return 1;
   if (c->force_rank > 0 || c->disp) {
     const int m = c->force_rank > 0 ? (c->disp ? 2 : 0) : 1;
-    if (extra_tiles(c)) return tile_steps_of(c, c->tb_cfg, m);
+    if (extra_tiles(c, m)) return tile_steps_of(c, c->tb_cfg, m);
     const int vi = extra_variant(c, m);
     return vi >= 0 ? kTBExtVariants[vi].steps : 1;
   }
