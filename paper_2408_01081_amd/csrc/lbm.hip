@@ -74,10 +74,10 @@ __device__ inline void node_moment(const float f[NQ][NC], const Force& F, int x,
 // Displacement state after initialisation: D = u0 + dt/2 v_num(t_0)
 __global__ __launch_bounds__(256) void k_init_disp(const float* __restrict__ src,
                                                    const double* __restrict__ u0,
-                                                   double* __restrict__ D, Grid g, Force F,
-                                                   double half_dt) {
+                                                   double* __restrict__ D, Grid g, bool per_xcd,
+                                                   Force F, double half_dt) {
   int x, y;
-  if (!field_node(g, x, y)) return;
+  if (!flat_node(g, per_xcd, x, y)) return;
   const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC], U[NC];
   for (int q = 0; q < NQ; ++q)
@@ -89,10 +89,10 @@ __global__ __launch_bounds__(256) void k_init_disp(const float* __restrict__ src
 // Displacement output u(t_n) = D - dt/2 v_num(t_n) (D holds u(t_n) + dt/2 v_num(t_n))
 __global__ __launch_bounds__(256) void k_displacement(const float* __restrict__ src,
                                                       const double* __restrict__ D,
-                                                      float* __restrict__ out, Grid g, Force F,
-                                                      double half_dt) {
+                                                      float* __restrict__ out, Grid g,
+                                                      bool per_xcd, Force F, double half_dt) {
   int x, y;
-  if (!field_node(g, x, y)) return;
+  if (!flat_node(g, per_xcd, x, y)) return;
   const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC], U[NC];
   for (int q = 0; q < NQ; ++q)
@@ -104,9 +104,10 @@ __global__ __launch_bounds__(256) void k_displacement(const float* __restrict__ 
 // load pre-collision FP32 populations [4][5][ny][nx] and collide (FP32)
 __global__ __launch_bounds__(256) void k_set_populations(const float* __restrict__ fin,
                                                          float* __restrict__ dst, Grid g,
-                                                         float kK, float km, Force F) {
+                                                         bool per_xcd, float kK, float km,
+                                                         Force F) {
   int x, y;
-  if (!field_node(g, x, y)) return;
+  if (!flat_node(g, per_xcd, x, y)) return;
   const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC];
   for (int q = 0; q < NQ; ++q)
@@ -133,10 +134,10 @@ struct MomConst {
 };
 
 __global__ __launch_bounds__(256) void k_moments(const float* __restrict__ src,
-                                                 float* __restrict__ out, Grid g, MomConst m,
-                                                 Force F) {
+                                                 float* __restrict__ out, Grid g, bool per_xcd,
+                                                 MomConst m, Force F) {
   int x, y;
-  if (!field_node(g, x, y)) return;
+  if (!flat_node(g, per_xcd, x, y)) return;
   const int64_t n = (int64_t)g.nx * g.ny, id = (int64_t)y * g.nx + x;
   float f[NQ][NC];
   for (int q = 0; q < NQ; ++q)
@@ -667,6 +668,9 @@ lbm_status lbm_lattice_constants(const lbm_ctx* c, double* kK, double* km, doubl
   return LBM_OK;
 }
 
+// order of the passes without neighbours (flat_node)
+static bool per_xcd(const lbm_ctx* c) { return state_bytes(c->g) <= INIT_NT_BYTES; }
+
 static lbm_status init_from(lbm_ctx* c, const double* d_v0, const double* d_s0,
                             const double* d_grad, int src) {
   const InitConst k = init_const(c->kK, c->km, c->cK, c->cmu, c->p.rho, c->p.dx, c->p.bc);
@@ -719,9 +723,9 @@ lbm_status lbm_init_displacement(lbm_ctx* c, const double* d_u0) {
   if (!c->disp) return fail(LBM_E_STATE, "context created without LBM_F_DISPLACEMENT");
   if (!c->initialised || c->nstep != 0)
     return fail(LBM_E_STATE, "lbm_init_displacement needs a freshly initialised lattice");
-  hipLaunchKernelGGL(k_init_disp, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
-                     (const float*)c->buf[c->cur], d_u0, c->disp, c->g, force_at(c, 0),
-                     0.5 * c->p.dt);
+  hipLaunchKernelGGL(k_init_disp, dim3(flat_blocks(c->g)), dim3(256), 0, c->stream,
+                     (const float*)c->buf[c->cur], d_u0, c->disp, c->g, per_xcd(c),
+                     force_at(c, 0), 0.5 * c->p.dt);
   lbm_status s = launch_check("k_init_disp launch");
   if (s) return s;
   c->disp_ready = true;
@@ -732,8 +736,8 @@ lbm_status lbm_displacement(lbm_ctx* c, float* d_u) {
   if (!c || !d_u) return fail(LBM_E_ARG, "null argument");
   if (!c->disp || !c->disp_ready)
     return fail(LBM_E_STATE, "no displacement: LBM_F_DISPLACEMENT and lbm_init_displacement");
-  hipLaunchKernelGGL(k_displacement, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
-                     (const float*)c->buf[c->cur], (const double*)c->disp, d_u, c->g,
+  hipLaunchKernelGGL(k_displacement, dim3(flat_blocks(c->g)), dim3(256), 0, c->stream,
+                     (const float*)c->buf[c->cur], (const double*)c->disp, d_u, c->g, per_xcd(c),
                      force_at(c, c->nstep), 0.5 * c->p.dt);
   return launch_check("k_displacement launch");
 }
@@ -781,8 +785,8 @@ lbm_status lbm_error_sums(lbm_ctx* c, double* h_out) {
 
 lbm_status lbm_set_populations(lbm_ctx* c, const float* d_f) {
   if (!c || !d_f) return fail(LBM_E_ARG, "null argument");
-  hipLaunchKernelGGL(k_set_populations, dim3((unsigned)field_tiles(c->g)), dim3(256), 0,
-                     c->stream, d_f, c->buf[0], c->g, (float)c->kK, (float)c->km,
+  hipLaunchKernelGGL(k_set_populations, dim3(flat_blocks(c->g)), dim3(256), 0,
+                     c->stream, d_f, c->buf[0], c->g, per_xcd(c), (float)c->kK, (float)c->km,
                      force_at(c, 0));
   lbm_status s = launch_check("k_set_populations launch");
   if (s) return s;
@@ -1765,8 +1769,8 @@ static lbm_status moments_mode(lbm_ctx* c, float* out, int mode) {
   if (!c || !out) return fail(LBM_E_ARG, "null argument");
   if (!c->initialised) return fail(LBM_E_STATE, "not initialised");
   MomConst m{(float)c->cK, (float)c->cmu, (float)c->p.rho, (float)c->kK, (float)c->km, mode};
-  hipLaunchKernelGGL(k_moments, dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream,
-                     c->buf[c->cur], out, c->g, m, force_at(c, c->nstep));
+  hipLaunchKernelGGL(k_moments, dim3(flat_blocks(c->g)), dim3(256), 0, c->stream,
+                     c->buf[c->cur], out, c->g, per_xcd(c), m, force_at(c, c->nstep));
   return launch_check("k_moments launch");
 }
 
