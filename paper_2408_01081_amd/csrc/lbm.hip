@@ -47,15 +47,15 @@ constexpr int RED_THREADS = 256;
 // Device kernels
 // ---------------------------------------------------------------------------
 
-template <int SRC, bool NT>
+template <int SRC, int FORM>
 __global__ __launch_bounds__(256) void k_init(const double* __restrict__ v0,
                                               const double* __restrict__ s0,
                                               const double* __restrict__ grad,
                                               float* __restrict__ dst, Grid g, InitConst k,
                                               Force F) {
   int x, y;
-  if (!field_node(g, x, y)) return;
-  init_node<SRC, NT, double>(v0, s0, grad, dst, g, k, x, y, F);
+  if (!(FORM == INIT_FLAT ? flat_node(g, false, x, y) : field_node(g, x, y))) return;
+  init_node<SRC, FORM == INIT_NT, double>(v0, s0, grad, dst, g, k, x, y, F);
 }
 
 // U_num(t_n) of a node from its stored post-collision populations:
@@ -674,13 +674,17 @@ static bool per_xcd(const lbm_ctx* c) { return state_bytes(c->g) <= INIT_NT_BYTE
 static lbm_status init_from(lbm_ctx* c, const double* d_v0, const double* d_s0,
                             const double* d_grad, int src) {
   const InitConst k = init_const(c->kK, c->km, c->cK, c->cmu, c->p.rho, c->p.dx, c->p.bc);
-  const bool nt = state_bytes(c->g) > INIT_NT_BYTES;
-  hipLaunchKernelGGL(src == INIT_FROM_STRESS
-                         ? (nt ? &k_init<INIT_FROM_STRESS, true> : &k_init<INIT_FROM_STRESS, false>)
-                         : (nt ? &k_init<INIT_FROM_GRADIENT, true>
-                               : &k_init<INIT_FROM_GRADIENT, false>),
-                     dim3((unsigned)field_tiles(c->g)), dim3(256), 0, c->stream, d_v0, d_s0,
-                     d_grad, c->buf[0], c->g, k, force_at(c, 0));
+  typedef void (*InitFn)(const double*, const double*, const double*, float*, Grid, InitConst,
+                         Force);
+  static constexpr InitFn fns[2][3] = {
+      {&k_init<INIT_FROM_STRESS, INIT_NT>, &k_init<INIT_FROM_STRESS, INIT_PLAIN>,
+       &k_init<INIT_FROM_STRESS, INIT_FLAT>},
+      {&k_init<INIT_FROM_GRADIENT, INIT_NT>, &k_init<INIT_FROM_GRADIENT, INIT_PLAIN>,
+       &k_init<INIT_FROM_GRADIENT, INIT_FLAT>}};
+  const InitForm form = init_form(c->g.nx, state_bytes(c->g));
+  const unsigned blocks = form == INIT_FLAT ? flat_blocks(c->g) : (unsigned)field_tiles(c->g);
+  hipLaunchKernelGGL(fns[src == INIT_FROM_GRADIENT][form], dim3(blocks), dim3(256), 0, c->stream,
+                     d_v0, d_s0, d_grad, c->buf[0], c->g, k, force_at(c, 0));
   lbm_status s = launch_check("k_init launch");
   if (s) return s;
   c->cur = 0;

@@ -7,6 +7,7 @@
 
 #include "lbm.h"
 #include "lbm_kernels.hpp"
+#include "lbm_plan.hpp"
 #include "lbm_step.hpp"
 
 namespace lbmk {
@@ -154,13 +155,7 @@ __device__ inline void body_hat0(const Force& F, int x, int y, double& bx, doubl
 // with FP64 divisions in the conversion of all five nodes and its loads behind
 // the branches of the boundary rule, it took 789 us on 4096 x 4096 and 92 us
 // on 2048 x 1024; in this form with plain stores 536 and 38 us, with
-// nontemporal ones 515 and 37 us (3.9 and 6.9 TB/s).  NT is for states whose
-// two buffers the last-level cache cannot hold: it keeps smaller ones out of
-// it, also for the launches after the first (initialisation, 45 steps in 9
-// launches and moments of 1794 x 559, three lattices in turn: 550 us with
-// nontemporal stores, 54 a launch, 470 with plain ones; 900 x 1500, 33 steps
-// 440 and 427; 2048 x 1024, 336 MB, 20 steps 389 and 402).
-constexpr size_t INIT_NT_BYTES = (size_t)128 << 20;  // half of the cache
+// nontemporal ones 515 and 37 us (3.9 and 6.9 TB/s).
 
 template <bool NT>
 __device__ __forceinline__ void init_store(float v, float* p) {
@@ -256,7 +251,7 @@ __device__ inline bool field_node(const Grid& g, int& x, int& y) {
 // 256 consecutive nodes per workgroup, so every lane has a node whatever nx and
 // ny are.  per_xcd: each XCD a contiguous part of the lattice, whose lines two
 // XCDs then share nowhere but at its ends; for states whose two buffers the
-// last-level cache holds (as INIT_NT_BYTES).  Beyond, grid order, in which the
+// last-level cache holds (INIT_NT_BYTES).  Beyond, grid order, in which the
 // workgroups in flight read and write one stretch of memory.  Two lattices in
 // turn (initialisation, steps, moments), moments in grid order / a part per XCD
 // / in tiles with a part per XCD: 1000 x 777 15.7 / 14.4 / 15.0 us, 200000 x 6

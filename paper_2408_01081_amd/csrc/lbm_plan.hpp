@@ -1,7 +1,9 @@
-// The launches of a run of n steps.  Plain C++ without HIP and without
-// allocation: a run is planned inside entry points that must not throw.
+// Host-side rules: the launches of a run of n steps, the form of an
+// initialisation.  Plain C++ without HIP and without allocation: they run inside
+// entry points that must not throw.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 namespace lbmh {
@@ -81,5 +83,26 @@ struct RunGraph {
   int64_t launches;
   int buffer_after(int cur) const { return cur ^ (int)(launches & 1); }
 };
+
+// Form of an initialisation pass: tiles of 64 x 4 nodes with nontemporal or plain
+// stores, or consecutive nodes with plain stores.
+enum InitForm { INIT_NT, INIT_PLAIN, INIT_FLAT };
+
+// Nontemporal stores are for states whose two buffers the last-level cache
+// cannot hold: they keep smaller ones out of it, also for the launches after the
+// first (initialisation, 45 steps in 9 launches and moments of 1794 x 559, three
+// lattices in turn: 550 us with nontemporal stores, 54 a launch, 470 with plain
+// ones; 900 x 1500, 33 steps 440 and 427; 2048 x 1024, 336 MB, 20 steps 389 and
+// 402).
+constexpr size_t INIT_NT_BYTES = (size_t)128 << 20;  // half of the cache
+// They also need rows that fill cache lines, of 32 values: part of a line goes
+// to memory as a read and a write.  And such rows leave more than half of a
+// tile's lanes without a node.
+constexpr int INIT_FULL_ROW = 32;
+
+inline InitForm init_form(int nx, size_t state_bytes) {
+  if (nx < INIT_FULL_ROW) return INIT_FLAT;
+  return state_bytes > INIT_NT_BYTES ? INIT_NT : INIT_PLAIN;
+}
 
 }  // namespace lbmh

@@ -1,6 +1,7 @@
-"""The host-side launch plans of runs (csrc/lbm_plan.hpp), compiled with the
-host compiler: step sums, launch counts, unknown times, least predicted time,
-and no allocation (they run inside entry points that must not throw)."""
+"""The host-side rules of csrc/lbm_plan.hpp, compiled with the host compiler: the
+launch plans of runs (step sums, launch counts, unknown times, least predicted time
+and no allocation, since they run inside entry points that must not throw) and
+the form of an initialisation."""
 import ctypes
 import itertools
 import os
@@ -35,6 +36,7 @@ int buffer_after(int64_t n, int T, int one, const double* ms, int maxt, int cur)
   const lbmh::RunGraph<int> g{0, p.launches()};
   return g.buffer_after(cur);
 }
+int init_form(int nx, size_t bytes) { return lbmh::init_form(nx, bytes); }
 }
 """
 
@@ -166,3 +168,22 @@ def test_batch_step_advances_by_its_graph():
     loop = tune[tune.index("for (int v = -1"):tune.index("hipEventDestroy(e0);\n  hipEventDestroy(e1);\n  if (s ==")]
     assert "b->tb_ms" not in loop and "b->step_ms" not in loop
     assert tune.index("drop_graphs(b)") < tune.index("memcpy(b->tb_ms")
+
+
+def test_init_form(lib):
+    # (tiles with nontemporal stores, tiles with plain ones, consecutive nodes)
+    NT, PLAIN, FLAT = 0, 1, 2
+
+    def form(nx, ny):
+        state = 20 * 4 * ny * (-(-nx // 64) * 64)  # rows padded to 64 values
+        return lib.init_form(nx, ctypes.c_size_t(state))
+
+    # rows shorter than a cache line: no nontemporal stores of parts of lines,
+    # and no tiles that leave more than half of their lanes idle
+    for nx in range(1, 32):
+        for ny in (1, 50, 3000, 60000, 10 ** 6):
+            assert form(nx, ny) == FLAT
+    # up to 128 MiB of state plain, beyond nontemporal
+    assert [form(32, 26214), form(32, 26215)] == [PLAIN, NT]
+    assert [form(64, 64), form(1000, 777), form(2048, 1024), form(4096, 4096)] \
+        == [PLAIN, PLAIN, NT, NT]
