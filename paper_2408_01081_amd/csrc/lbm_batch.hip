@@ -348,6 +348,7 @@ struct Layout {
   std::vector<InstDesc> desc;
   std::vector<int> tile_inst, tile_count;
   int64_t pool_floats = 0, total_nodes = 0;
+  int64_t full_row_floats = 0;  // of the pool: instances whose rows fill cache lines
   int ntiles = 0;
   int tb_waves[kNumBatchTB];    // waves of each blocked variant
   int64_t tb_wave0[kNumBatchTB];  // its wave table's first entry in the tables' region
@@ -399,7 +400,9 @@ lbm_status plan(int32_t n, const lbm_params* params, Layout* L) {
     memset(&d, 0, sizeof d);
     d.g = make_grid(&params[i]);
     d.off = L->pool_floats;
-    L->pool_floats += round_up((int64_t)(state_bytes(d.g) / 4), 64);
+    const int64_t floats = round_up((int64_t)(state_bytes(d.g) / 4), 64);
+    L->pool_floats += floats;
+    if (d.g.nx >= INIT_FULL_ROW) L->full_row_floats += floats;
     d.node0 = L->total_nodes;
     L->total_nodes += (int64_t)d.g.nx * d.g.ny;
     d.tiles_x = (d.g.nx + BT - 1) / BT;
@@ -779,7 +782,7 @@ static lbm_status batch_init_any(lbm_batch* b, const void* v0, const void* s0, i
                                  bool f32) {
   const int64_t total = b->L.total_nodes;
   const unsigned grid = (unsigned)((total + BT - 1) / BT);
-  const bool nt = (size_t)b->L.pool_floats * 4 > INIT_NT_BYTES;
+  const bool nt = batch_init_nt((size_t)b->L.pool_floats * 4, (size_t)b->L.full_row_floats * 4);
   if (f32)
     hipLaunchKernelGGL((nt ? &k_batch_init<float, true> : &k_batch_init<float, false>), dim3(grid),
                        dim3(BT), 0, b->stream, (const float*)v0, (const float*)s0, packed, b->pool[0],

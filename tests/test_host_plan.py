@@ -37,6 +37,7 @@ int buffer_after(int64_t n, int T, int one, const double* ms, int maxt, int cur)
   return g.buffer_after(cur);
 }
 int init_form(int nx, size_t bytes) { return lbmh::init_form(nx, bytes); }
+int batch_init_nt(size_t pool, size_t full) { return lbmh::batch_init_nt(pool, full); }
 }
 """
 
@@ -187,3 +188,13 @@ def test_init_form(lib):
     assert [form(32, 26214), form(32, 26215)] == [PLAIN, NT]
     assert [form(64, 64), form(1000, 777), form(2048, 1024), form(4096, 4096)] \
         == [PLAIN, PLAIN, NT, NT]
+
+
+def test_batch_init_stores(lib):
+    def nt(pool, full):
+        return bool(lib.batch_init_nt(ctypes.c_size_t(pool), ctypes.c_size_t(full)))
+
+    mib = 1 << 20
+    assert not nt(128 * mib, 128 * mib) and nt(129 * mib, 129 * mib)
+    # narrow instances alone, half of the pool, most of it wide
+    assert not nt(640 * mib, 0) and not nt(640 * mib, 320 * mib) and nt(640 * mib, 321 * mib)
