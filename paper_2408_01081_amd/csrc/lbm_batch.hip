@@ -58,8 +58,8 @@ struct InstDesc {
   float* V;  // Dirichlet instances: [8][2 (nx + ny)][2] wall velocities of a blocked launch's steps
 };
 
-__device__ inline int find_instance(const InstDesc* __restrict__ d, int n, int64_t node) {
-  int lo = 0, hi = n - 1;
+// the instance of a node, one of lo .. hi
+__device__ inline int find_instance(const InstDesc* __restrict__ d, int lo, int hi, int64_t node) {
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (d[mid].node0 <= node)
@@ -70,24 +70,39 @@ __device__ inline int find_instance(const InstDesc* __restrict__ d, int n, int64
   return lo;
 }
 
-// fn(instance, x, y) for this thread's node of the packed node range: a block
-// of BT consecutive nodes lies in one instance, or in a run of them, which the
-// whole block walks together, so the descriptors come through scalar loads
-// and no thread searches for its own (128 instances of 128 rows, 3.3 M nodes:
-// FP64 initialisation 237 -> 81 us with the form of init_node above).
+// fn(instance, x, y) for this thread's node of the packed node range, of which
+// workgroup `block` takes BT consecutive nodes.  They lie in one instance or in
+// a run of a few, which the whole workgroup walks together, so the descriptors
+// come through scalar loads and no thread searches for its own (128 instances
+// of 128 rows, 3.3 M nodes: FP64 initialisation 237 -> 81 us with the form of
+// init_node above).  Of more than WALK instances each thread finds its own: the
+// walk is one instance's latency after another (4096 instances of 4 x 4, 16 per
+// workgroup: 25 us walking, 19 so; 1280 of 3 x 2 to 7 x 8: 23 and 18; 16384 of
+// 1 x 1: 209 and 22).
+constexpr int WALK = 4;
+
 template <typename FN>
-__device__ inline void for_block_instances(const InstDesc* __restrict__ descs, int n, FN fn) {
-  const int64_t first = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * BT;
-  const int64_t node = first + threadIdx.x;
-  for (int i = find_instance(descs, n, first); i < n; ++i) {
-    const InstDesc& d = descs[i];
-    if (d.node0 >= first + BT) break;
+__device__ inline void for_block_instances(const InstDesc* __restrict__ descs, int n, int block,
+                                           FN fn) {
+  const int64_t first = (int64_t)block * BT, node = first + threadIdx.x;
+  auto at = [&](const InstDesc& d) {
     const int64_t loc = node - d.node0;
-    if (loc < 0 || loc >= (int64_t)d.g.nx * d.g.ny) continue;
+    if (loc < 0 || loc >= (int64_t)d.g.nx * d.g.ny) return;
     // (instances whose node count fits 31 bits: a 32-bit division)
     const int y = (int64_t)d.g.nx * d.g.ny <= 0x7fffffff ? (int)((unsigned)loc / (unsigned)d.g.nx)
                                                           : (int)(loc / d.g.nx);
     fn(d, (int)(loc - (int64_t)y * d.g.nx), y);
+  };
+  int i = find_instance(descs, 0, n - 1, first);
+  const bool whole = descs[i].node0 + (int64_t)descs[i].g.nx * descs[i].g.ny >= first + BT;
+  if (!whole && i + WALK < n && descs[i + WALK].node0 < first + BT) {
+    at(descs[find_instance(descs, i, i + BT - 1 < n ? i + BT - 1 : n - 1, node)]);
+    return;
+  }
+  for (; i < n; ++i) {
+    const InstDesc& d = descs[i];
+    if (d.node0 >= first + BT) break;
+    at(d);
   }
 }
 
@@ -215,7 +230,8 @@ __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
                                                    const T* __restrict__ s0, int packed,
                                                    float* __restrict__ pool,
                                                    const InstDesc* __restrict__ descs, int n) {
-  for_block_instances(descs, n, [&](const InstDesc& d, int x, int y) {
+  const int block = xcd_tile(blockIdx.x, gridDim.x);
+  for_block_instances(descs, n, block, [&](const InstDesc& d, int x, int y) {
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const T* v = packed ? s0 + 5 * d.node0 : v0 + 2 * d.node0;
     const T* s = packed ? s0 + 5 * d.node0 + 2 * ni : s0 + 3 * d.node0;
@@ -228,7 +244,8 @@ __global__ __launch_bounds__(BT) void k_batch_moments(const float* __restrict__ 
                                                       float* __restrict__ out,
                                                       const InstDesc* __restrict__ descs, int n,
                                                       int mode) {
-  for_block_instances(descs, n, [&](const InstDesc& d, int x, int y) {
+  const int block = xcd_tile(blockIdx.x, gridDim.x);
+  for_block_instances(descs, n, block, [&](const InstDesc& d, int x, int y) {
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const float* src = pool + d.off;
     float f[NQ][NC], U[NC];
