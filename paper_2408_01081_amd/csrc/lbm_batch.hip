@@ -239,12 +239,15 @@ __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
   });
 }
 
-// mode 0: physical (v, sigma_bar); 1: U
+// mode 0: physical (v, sigma_bar); 1: U.  per_xcd: see flat_node; for pools
+// that the last-level cache holds twice (two batches in turn, grid order / a
+// part per XCD: 64 uneven instances, 430 MB, 88.5 / 93.6 us, 64 of 250 x 250
+// 72.4 / 75.9, 512 of 33 x 128 69.3 / 73.1; 256 of 33 x 33, 54 MB, 15.0 / 14.2).
 __global__ __launch_bounds__(BT) void k_batch_moments(const float* __restrict__ pool,
                                                       float* __restrict__ out,
                                                       const InstDesc* __restrict__ descs, int n,
-                                                      int mode) {
-  const int block = xcd_tile(blockIdx.x, gridDim.x);
+                                                      bool per_xcd, int mode) {
+  const int block = per_xcd ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   for_block_instances(descs, n, block, [&](const InstDesc& d, int x, int y) {
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const float* src = pool + d.off;
@@ -990,7 +993,7 @@ static lbm_status batch_moments(lbm_batch* b, float* out, int mode) {
   const int64_t total = b->L.total_nodes;
   hipLaunchKernelGGL(k_batch_moments, dim3((unsigned)((total + BT - 1) / BT)), dim3(BT), 0,
                      b->stream, (const float*)b->pool[b->cur], out, (const InstDesc*)b->d_desc,
-                     b->n, mode);
+                     b->n, (size_t)b->L.pool_floats * 4 <= INIT_NT_BYTES, mode);
   return launch_check("batch moments launch");
 }
 
