@@ -350,11 +350,10 @@ lbm_status lbm_set_tblock_split(lbm_ctx* ctx, int32_t mode);
  * configured now, 0 if not, -1 for a NULL context or a bad index. */
 int32_t lbm_tblock_split_active(lbm_ctx* ctx, int32_t index);
 /* Select the launch configuration that makes runs of nsteps steps cheapest:
- * for every blocked variant (and for single steps) the predicted time of such
- * a run from the launch times the last lbm_autotune of this shape in this
- * process measured, floor(nsteps / T) full launches plus the launch lbm_step
- * takes for the nsteps mod T steps left; the cheapest becomes the selected
- * variant (*h_index, -1: single steps).  A variant that divides nsteps can
+ * for every blocked variant (and for single steps) the predicted time of the
+ * launches that lbm_step makes for such a run (outside stream capture), from the
+ * launch times the last lbm_autotune of this shape in this process measured;
+ * the cheapest becomes the selected variant (*h_index, -1: single steps).  A variant that divides nsteps can
  * win over one that is faster per step (4096^2: T = 10 for 20-step runs,
  * against T = 8 per step).  Without such launch times (no lbm_autotune, or
  * its choice read from the cache file) the selection is unchanged.

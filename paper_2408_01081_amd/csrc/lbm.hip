@@ -376,6 +376,17 @@ __global__ __launch_bounds__(256) void k_copy(const float4* __restrict__ src,
 
 }  // namespace
 
+// launch times (ms; -1: not timed): every blocked variant, a tile variant's
+// launches of fewer steps, and the best single-step configuration
+struct LaunchTimes {
+  double tb[kNumTBVariants], tile[kNumTBTiles][TB_MAX_STEPS + 1], step;
+  LaunchTimes() : step(-1.0) {
+    for (double& t : tb) t = -1.0;
+    for (auto& row : tile)
+      for (double& t : row) t = -1.0;
+  }
+};
+
 struct lbm_ctx {
   lbm_params p;
   Grid g;
@@ -398,10 +409,7 @@ struct lbm_ctx {
   int tb_slots[64];   // resident waves of a blocked variant on this device (0: not known)
   int tbf_slots[48];  // the same for the variants with a load / displacement (3 per variant)
   int tb_rem[TB_MAX_STEPS + 1];  // variant for the last r = 2 .. 10 steps of a run (-1: nearest shape)
-  // launch times the autotuner measured for this shape (ms; -1: not timed):
-  // every blocked variant, and the best single-step configuration
-  double tb_launch_ms[kNumTBVariants];
-  double step_launch_ms;
+  LaunchTimes times;  // as the autotuner measured them for this shape
   // split Dirichlet blocked launches (mode -1, the default, or 1: wherever a
   // split kernel exists and the lattice allows; 0: never): the wall band
   // with the Dirichlet rule and the interior with the periodic kernel's
@@ -648,8 +656,7 @@ lbm_status lbm_create(const lbm_params* p, void* d_ws, size_t ws_size, void* hip
   c->tb_cfg = -1;
   for (int r = 0; r <= TB_MAX_STEPS; ++r) c->tb_rem[r] = -1;
   c->tb_split = -1;
-  for (int i = 0; i < kNumTBVariants; ++i) c->tb_launch_ms[i] = -1.0;
-  c->step_launch_ms = -1.0;
+  c->times = LaunchTimes();
   *out = c;
   g_err.clear();
   return LBM_OK;
@@ -1302,28 +1309,40 @@ static lbm_status step_extra_tiles(lbm_ctx* c, int64_t nsteps, int m) {
   return launch_check("k_tile launch (load / displacement)");
 }
 
-// the variant of a launch of t >= 2 steps: the selected one for its own number
-// of steps, remainder_variant's below it, above it the fastest the autotuner timed
-static int steps_variant(const lbm_ctx* c, int t) {
-  const int T = kTBVariants[c->tb_cfg].steps;
-  if (t == T) return c->tb_cfg;
-  return t < T ? remainder_variant(c, t, c->tb_cfg) : c->tb_rem[t];
+// the variant of a launch of t >= 2 steps in a run with variant v: v for its own
+// number of steps, remainder_variant's below it, above it the fastest the
+// autotuner timed
+static int steps_variant(const lbm_ctx* c, int v, int t) {
+  const int T = kTBVariants[v].steps;
+  if (t == T) return v;
+  return t < T ? remainder_variant(c, t, v) : c->tb_rem[t];
 }
 
-// the launches of a run without load, displacement or error norms
-static LaunchPlan step_plan(const lbm_ctx* c, int64_t nsteps) {
-  if (c->tb_cfg < 0) return LaunchPlan{nsteps, 1, 0, {}};
-  const int T = kTBVariants[c->tb_cfg].steps, r = (int)(nsteps % T);
+// ms[t]: time of a launch of t steps in a run with variant v, as the autotuner
+// measured it (<= 0: it did not)
+static void launch_times(const lbm_ctx* c, int v, double ms[TB_MAX_STEPS + 1]) {
+  ms[0] = 0.0;
+  ms[1] = c->times.step;
+  for (int t = 2; t <= TB_MAX_STEPS; ++t) {
+    const int k = steps_variant(c, v, t);
+    if (k < 0)
+      ms[t] = -1.0;
+    else if (t < kTBVariants[k].steps)  // a tile
+      ms[t] = c->times.tile[k - kNumTBSweeps][t];
+    else
+      ms[t] = c->times.tb[k];
+  }
+}
+
+// the launches of a run with variant v (-1: single steps) without load,
+// displacement or error norms; times: divided by the launch times, where known
+static LaunchPlan run_plan(const lbm_ctx* c, int v, int64_t nsteps, bool times) {
+  if (v < 0) return LaunchPlan{nsteps, 1, 0, {}};
+  const int T = kTBVariants[v].steps, r = (int)(nsteps % T);
   double ms[TB_MAX_STEPS + 1] = {};
   // (a tile variant takes any smaller number of steps itself)
-  if (r && !is_tile(c->tb_cfg) && c->step_launch_ms > 0.0 && !capturing(c->stream)) {
-    ms[1] = c->step_launch_ms;
-    for (int t = 2; t <= TB_MAX_STEPS; ++t) {
-      const int v = steps_variant(c, t);
-      if (v >= 0) ms[t] = c->tb_launch_ms[v];
-    }
-  }
-  return plan_launches(nsteps, T, remainder_variant(c, r, c->tb_cfg) >= 0, ms, TB_MAX_STEPS);
+  if (r && !is_tile(v) && times) launch_times(c, v, ms);
+  return plan_launches(nsteps, T, remainder_variant(c, r, v) >= 0, ms, TB_MAX_STEPS);
 }
 
 lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
@@ -1351,7 +1370,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   const StepFn fn = cfg.fn[c->p.bc];
   // chunks of whole launches (at most WALL_CHUNK steps): the chunk's wall
   // velocities are summed first, then its launches run
-  const LaunchPlan plan = step_plan(c, nsteps);
+  const LaunchPlan plan = run_plan(c, c->tb_cfg, nsteps, !capturing(c->stream));
   for (int64_t l = 0, s0 = 0; l < plan.launches();) {
     int64_t end = l;
     int m = 0;
@@ -1363,7 +1382,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
         hipLaunchKernelGGL(fn, dim3(sc.ntiles), dim3(cfg.threads), 0, c->stream,
                            (const float*)c->buf[c->cur], c->buf[c->cur ^ 1], g, sc, wall_at(c, k));
       else
-        launch_tb(c, steps_variant(c, t), c->buf[c->cur], c->buf[c->cur ^ 1],
+        launch_tb(c, steps_variant(c, c->tb_cfg, t), c->buf[c->cur], c->buf[c->cur ^ 1],
                   walls_from(c, k, true), t);
       c->cur ^= 1;
       k += t;
@@ -1392,17 +1411,15 @@ struct TuneKey {
 struct TuneVal {
   int cfg, cfg2;
   int rem[TB_MAX_STEPS + 1];
-  double launch_ms[kNumTBVariants];  // in this process only (-1: not timed)
-  double step_ms;
+  LaunchTimes times;  // in this process only
 };
 
-TuneVal tune_val(int cfg, int cfg2, const int* rem, const lbm_ctx* timed = nullptr) {
+TuneVal tune_val(int cfg, int cfg2, const int* rem, const LaunchTimes& times = LaunchTimes()) {
   TuneVal v;
   v.cfg = cfg;
   v.cfg2 = cfg2;
   for (int r = 0; r <= TB_MAX_STEPS; ++r) v.rem[r] = rem ? rem[r] : -1;
-  for (int i = 0; i < kNumTBVariants; ++i) v.launch_ms[i] = timed ? timed->tb_launch_ms[i] : -1.0;
-  v.step_ms = timed ? timed->step_launch_ms : -1.0;
+  v.times = times;
   return v;
 }
 
@@ -1510,8 +1527,7 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t reps, int32_t use_cache, int32_t* h_
       c->step_cfg = it->second.cfg;
       c->tb_cfg = it->second.cfg2 < kNumTBVariants && tblock_fits(c->g) ? it->second.cfg2 : -1;
       for (int r = 0; r <= TB_MAX_STEPS; ++r) c->tb_rem[r] = c->tb_cfg >= 0 ? it->second.rem[r] : -1;
-      for (int i = 0; i < kNumTBVariants; ++i) c->tb_launch_ms[i] = it->second.launch_ms[i];
-      c->step_launch_ms = it->second.step_ms;
+      c->times = it->second.times;
       if (h_index) *h_index = it->second.cfg;
       if (h_ms) *h_ms = -1.0;
       return LBM_OK;
@@ -1560,31 +1576,51 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t reps, int32_t use_cache, int32_t* h_
     rem[r] = -1;
     rem_ms[r] = 1e300;
   }
-  for (int i = 0; i < kNumTBVariants && s == LBM_OK && tblock_fits(c->g); ++i) {
-    // grids of many tiles are the sweep's: its overlap is smaller
-    if (is_tile(i)) {
-      const TBConst sc = tile_const(c, i, 3, kTBVariants[i].steps);
-      if ((int64_t)sc.nstrips * sc.nseg > TILE_TUNE) continue;
-    }
+  LaunchTimes times;
+  times.step = best_ms;
+  // average time of launches of variant i with `steps` steps
+  auto time_launches = [&](int i, int steps) {
     for (int r = 0; r < reps + 2; ++r) {
       if (r == 2) hipEventRecord(e0, c->stream);
-      launch_tb(c, i, c->buf[c->cur], c->buf[c->cur ^ 1], ws);
+      launch_tb(c, i, c->buf[c->cur], c->buf[c->cur ^ 1], ws, steps);
     }
     hipEventRecord(e1, c->stream);
     s = hip_check(hipEventSynchronize(e1), "autotune sync");
     float ms = 0.f;
     if (s == LBM_OK) s = hip_check(hipEventElapsedTime(&ms, e0, e1), "autotune timing");
+    return (double)ms / reps;
+  };
+  for (int i = 0; i < kNumTBVariants && s == LBM_OK && tblock_fits(c->g); ++i) {
     const int steps = kTBVariants[i].steps;
-    const double per = (double)ms / reps / steps;
-    if (s == LBM_OK) c->tb_launch_ms[i] = (double)ms / reps;
-    if (s == LBM_OK && per < best2_ms) {
-      best2_ms = per;
+    // grids of many tiles are the sweep's: its overlap is smaller
+    if (is_tile(i)) {
+      const TBConst sc = tile_const(c, i, 3, steps);
+      if ((int64_t)sc.nstrips * sc.nseg > TILE_TUNE) continue;
+    }
+    const double ms = time_launches(i, steps);
+    if (s) break;
+    times.tb[i] = ms;
+    if (ms / steps < best2_ms) {
+      best2_ms = ms / steps;
       best2 = i;
     }
     // the fastest launch of each step count, for the last steps of a run
-    if (s == LBM_OK && (double)ms / reps < rem_ms[steps]) {
-      rem_ms[steps] = (double)ms / reps;
+    if (ms < rem_ms[steps]) {
+      rem_ms[steps] = ms;
       rem[steps] = i;
+    }
+  }
+  // where a tile is the fastest, also tiles' launches of fewer steps (the last of
+  // a run): no formula gives them, since tiles of fewer steps store more and can
+  // need a round less (384 x 384, 24 rows: 6 steps 11.9 us, 7 18.5, 8 19.7);
+  // variants of the same rows share them
+  for (int i = kNumTBSweeps; i < kNumTBVariants && best2 >= 0 && is_tile(best2); ++i) {
+    for (int t = 2; t < kTBVariants[i].steps && s == LBM_OK; ++t) {
+      double& at = times.tile[i - kNumTBSweeps][t];
+      for (int j = kNumTBSweeps; j < i && at < 0.0; ++j)
+        if (kTBVariants[j].seg_rows == kTBVariants[i].seg_rows && t <= kTBVariants[j].steps)
+          at = t == kTBVariants[j].steps ? times.tb[j] : times.tile[j - kNumTBSweeps][t];
+      if (at < 0.0) at = time_launches(i, t);
     }
   }
   hipEventDestroy(e0);
@@ -1592,14 +1628,14 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t reps, int32_t use_cache, int32_t* h_
   if (s) return s;
   if (best < 0) return fail(LBM_E_ARG, "no valid launch configuration");
   c->step_cfg = best;
-  c->step_launch_ms = best_ms;
+  c->times = times;
   c->tb_cfg = best2_ms < best_ms ? best2 : -1;
   for (int r = 0; r <= TB_MAX_STEPS; ++r) c->tb_rem[r] = rem[r];
   const double per_step = best2_ms < best_ms ? best2_ms : best_ms;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     load_tune_file();
-    g_tune_cache[key] = tune_val(best, c->tb_cfg, rem, c);
+    g_tune_cache[key] = tune_val(best, c->tb_cfg, rem, times);
     append_tune_file(key, g_tune_cache[key], per_step);
   }
   if (h_index) *h_index = best;
@@ -1650,32 +1686,24 @@ lbm_status lbm_set_tblock_config(lbm_ctx* c, int32_t index) {
 lbm_status lbm_select_for_steps(lbm_ctx* c, int64_t nsteps, int32_t* h_index) {
   if (!c || !h_index || nsteps < 1) return fail(LBM_E_ARG, "null argument or no steps");
   *h_index = c->tb_cfg;
-  if (c->step_launch_ms <= 0.0) return LBM_OK;  // no launch times: selection unchanged
-  // predicted time of a run of nsteps steps with variant v (-1: single steps):
-  // its full launches, then the launch lbm_step takes for the steps left
-  auto cost = [&](int v) {
-    const int T = v >= 0 ? kTBVariants[v].steps : 1;
-    const double full = v >= 0 ? c->tb_launch_ms[v] : c->step_launch_ms;
-    if (full <= 0.0) return 1e300;
-    const int r = (int)(nsteps % T);
-    double rest = 0.0;
-    if (r == 1) {
-      rest = c->step_launch_ms;
-    } else if (r > 1 && v >= 0 && is_tile(v)) {
-      // the same tile with fewer steps: a launch costs about two steps beside them
-      rest = full * (r + 2) / (T + 2);
-    } else if (r > 1) {
-      const int ri = remainder_variant(c, r, v);
-      rest = ri >= 0 && c->tb_launch_ms[ri] > 0.0 ? c->tb_launch_ms[ri] : r * c->step_launch_ms;
-    }
-    return (double)(nsteps / T) * full + rest;
-  };
+  if (c->times.step <= 0.0) return LBM_OK;  // no launch times: selection unchanged
+  // the predicted time of the launches lbm_step makes for such a run.  A run whose
+  // last launches are divided counts 3% more: it is the least of many sums, several
+  // variants may make the same launches, and variants' predicted and real times
+  // differ by that much, since the autotuner's launches all read one buffer
+  // (640 x 500, 50 steps: predicted 148.3 us of T = 7 and 148.7 of T = 8 run 156
+  // and 162; 512 x 512, 29 steps: with 1%, runs of 101 to 113 us, with 3% 97 to 100;
+  // 4096^2, 20 steps: 10 + 10 by T = 8 or 10)
   int best = -1;
-  double best_cost = cost(-1);
+  double best_ms = (double)nsteps * c->times.step;
   for (int v = 0; v < kNumTBVariants; ++v) {
-    const double cv = cost(v);
-    if (cv < best_cost) {
-      best_cost = cv;
+    if (c->times.tb[v] <= 0.0) continue;
+    const LaunchPlan plan = run_plan(c, v, nsteps, true);
+    double ms[TB_MAX_STEPS + 1];
+    launch_times(c, v, ms);
+    const double run = plan_ms(plan, ms) * (plan.head < nsteps / plan.T ? 1.03 : 1.0);
+    if (run < best_ms) {
+      best_ms = run;
       best = v;
     }
   }

@@ -73,6 +73,15 @@ inline LaunchPlan plan_launches(int64_t n, int T, bool one_launch, const double*
   return p;
 }
 
+// Time of a plan's launches, ms[t] for one of t steps; of an unknown one (<= 0)
+// that of t single steps.
+inline double plan_ms(const LaunchPlan& p, const double* ms) {
+  auto launch = [&](int t) { return ms[t] > 0.0 ? ms[t] : t * ms[1]; };
+  double sum = p.head ? (double)p.head * launch(p.T) : 0.0;
+  for (int l = 0; l < p.ntail; ++l) sum += launch(p.tail[l]);
+  return sum;
+}
+
 // A cached graph of a run.  The buffer that holds the state after it follows
 // from the launches it was built with: a plan made later can divide the same
 // run into another number (launch times measured since, or a stream now being

@@ -48,6 +48,7 @@ constexpr int tb_num_sweeps() {
 }
 // the sweep kernels' variants come first, then the tiles
 constexpr int kNumTBSweeps = tb_num_sweeps();
+constexpr int kNumTBTiles = kNumTBVariants - kNumTBSweeps;
 constexpr bool tb_steps_in_range() {
   for (const TBVariant& v : kTBVariants)
     if (v.steps < 2 || v.steps > TB_MAX_STEPS) return false;

@@ -36,6 +36,10 @@ int buffer_after(int64_t n, int T, int one, const double* ms, int maxt, int cur)
   const lbmh::RunGraph<int> g{0, p.launches()};
   return g.buffer_after(cur);
 }
+// the predicted time of a run's launches
+double plan_ms(int64_t n, int T, int one, const double* ms, int maxt) {
+  return lbmh::plan_ms(lbmh::plan_launches(n, T, one != 0, ms, maxt), ms);
+}
 int init_form(int nx, size_t bytes) { return lbmh::init_form(nx, bytes); }
 int batch_init_nt(size_t pool, size_t full) { return lbmh::batch_init_nt(pool, full); }
 }
@@ -198,3 +202,26 @@ def test_batch_init_stores(lib):
     assert not nt(128 * mib, 128 * mib) and nt(129 * mib, 129 * mib)
     # narrow instances alone, half of the pool, most of it wide
     assert not nt(640 * mib, 0) and not nt(640 * mib, 320 * mib) and nt(640 * mib, 321 * mib)
+
+
+def test_predicted_time_is_that_of_the_launches_made(lib):
+    lib.plan_ms.restype = ctypes.c_double
+
+    def predicted(n, T, ms):
+        return lib.plan_ms(ctypes.c_int64(n), T, 1, (ctypes.c_double * 11)(*ms), 10)
+
+    # 50 steps: 7 x 7 + 1 would be 235.6, the run made is 6 x 7 + 8
+    ms = [0.0, 18.6, 19.5, 21.0, 23.0, 25.0, 28.0, 31.0, 34.0, 0.0, 0.0]
+    assert predicted(50, 7, ms) == pytest.approx(6 * 31.0 + 34.0)
+    # runs that variants of fewer and more steps make alike cost the same: 20 steps
+    # of an 8-step variant as 10 + 10
+    ms = [0.0, 440.0, 450.0, 460.0, 470.0, 480.0, 490.0, 510.0, 530.0, 650.0, 690.0]
+    assert predicted(20, 10, ms) == predicted(20, 8, ms) == 2 * 690.0
+    for T in range(2, 11):
+        for n in range(1, 60):
+            steps = _plan(lib, n, T, True, ms, 10)
+            assert predicted(n, T, ms) == pytest.approx(sum(ms[t] for t in steps))
+    # a launch that was not timed counts as its single steps
+    ms[4] = -1.0
+    assert _plan(lib, 20, 8, True, ms, 10) == [8, 8, 4]
+    assert predicted(20, 8, ms) == pytest.approx(2 * 530.0 + 4 * 440.0)
