@@ -1628,6 +1628,9 @@ __global__ __launch_bounds__(256, 2) void k_wgradw(const float* __restrict__ G,
     bf16x8 gh[4][2], gl[4][2];  // [step][half of the output channels]
 #pragma unroll
     for (int r = 0; r < 6; ++r) {  // input row 4 kh + r of the tile
+      // (plain BF16: without the barrier the fragments of all rows are read ahead of
+      // the products, 256 registers and 36 B of scratch per lane; 216 and none with it)
+      if (SPLIT == 1) __builtin_amdgcn_sched_barrier(0);
       if (r < 4) {
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
