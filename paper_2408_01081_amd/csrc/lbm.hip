@@ -860,6 +860,7 @@ const TBTables& tb_tables() {
 }
 
 static_assert(kNumTBVariants <= 64, "tb_slots size");
+static_assert(tb_tile_rows() == TILE_MAX_ROWS, "tile kernels are built for the largest tile");
 static_assert(kNumTBExtVariants * 3 <= 48, "tbf_slots size");
 static_assert(kNumTBSplitVariants <= 8, "tbs_slots size");
 static_assert(TB_MAX_STEPS <= PLAN_MAX_STEPS, "LaunchPlan size");

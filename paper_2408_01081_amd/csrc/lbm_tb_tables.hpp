@@ -49,6 +49,13 @@ constexpr int tb_num_sweeps() {
 // the sweep kernels' variants come first, then the tiles
 constexpr int kNumTBSweeps = tb_num_sweeps();
 constexpr int kNumTBTiles = kNumTBVariants - kNumTBSweeps;
+// rows of the largest tile
+constexpr int tb_tile_rows() {
+  int rows = 0;
+  for (const TBVariant& v : kTBVariants)
+    if (v.seg_rows < TB_SEG_TILE && TB_SEG_TILE - v.seg_rows > rows) rows = TB_SEG_TILE - v.seg_rows;
+  return rows;
+}
 constexpr bool tb_steps_in_range() {
   for (const TBVariant& v : kTBVariants)
     if (v.steps < 2 || v.steps > TB_MAX_STEPS) return false;

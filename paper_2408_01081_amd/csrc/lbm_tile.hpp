@@ -16,7 +16,7 @@
 // results are bitwise those of single steps.
 //
 // Bound by vector instructions at two or three waves per SIMD (0.14 to 0.18 us
-// per row update of a wave; R / 8 of them per SIMD and step) and by 3.4 to 5
+// per row update of a wave; R / 4 of them per SIMD and step) and by 3.4 to 5
 // us per launch (dispatch, loads, stores).  Which shape pays depends on the
 // grid and is the autotuner's choice; per step, the fastest tile against the
 // fastest other variant: 160 x 160 with walls 1.49 us (T = 5, 16 rows) against
@@ -33,6 +33,7 @@
 namespace lbmk {
 
 constexpr int TILE_K = 2;  // rows per wave
+constexpr int TILE_MAX_ROWS = 24;  // rows of the largest tile variant
 
 // the body load and displacement state of a launch (TBExtra; the row factors
 // Y[r][y] T_{n+l}[r] are formed in LDS at the start of the launch)
@@ -201,11 +202,14 @@ typedef void (*TileFn)(const float*, float*, Grid, TBConst, WallSeq, TileExtra, 
 struct TileTable {
   TileFn fn[4][2][2];
 };
-// most waves of a kernel: its registers per wave are 512 / (waves per SIMD).
-// (With a load, 12 waves left the wall code 80 to 150 B of scratch per lane:
-// 160 x 160 with load and displacement 3.1 us per step; 8 waves 2.7.)
+// most waves of a kernel: those of the largest tile, fewer with a load.  They set
+// its LDS and the registers a wave may use, 512 / (waves per SIMD).  (With a load,
+// 12 waves left the wall code 80 to 150 B of scratch per lane: 160 x 160 with load
+// and displacement 3.1 us per step; 8 waves 2.7.  With walls, ranks above 16 and
+// the displacement state 8 waves leave 44 B: 3.0 us per step, where one launch per
+// step takes 6.5 and the sweep, with 92 B, 15.5.)
 constexpr int tile_max_waves(int extras) {
-  return extras == 3 ? 16 : extras == 1 ? 12 : 8;
+  return extras == 3 || extras == 1 ? TILE_MAX_ROWS / TILE_K : 8;
 }
 void tile_fill(TileTable& t);  // lbm_tile.hip
 

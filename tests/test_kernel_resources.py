@@ -63,3 +63,17 @@ def _named(kernels, name):
 def test_surrogate_kernels_do_not_spill(kernels, name):
     for k, v in _named(kernels, name).items():
         assert v["scratch"] == 0, (k, v)
+
+
+def test_tile_kernels_are_built_for_the_largest_tile(kernels):
+    # template arguments: boundary type, load, displacement, ranks, most waves.
+    # Without extras the LDS is that of the 12 waves of a 24-row tile; only the
+    # kernel with walls, ranks above 16 and the displacement state spills.
+    tiles = _named(kernels, "k_tile")
+    assert len(tiles) == 12
+    for k, v in tiles.items():
+        bc, load, disp, ranks = re.search(r"k_tileILi(\d)ELb(\d)ELb(\d)ELi(\d+)E", k).groups()
+        if load == "0":
+            assert v["lds"] <= 2 * 12 * 10 * 64 * 4 + 16, (k, v)
+        if (bc, load, disp, ranks) != ("1", "1", "1", "32"):
+            assert v["scratch"] == 0, (k, v)
