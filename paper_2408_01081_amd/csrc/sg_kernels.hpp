@@ -412,28 +412,7 @@ __global__ __launch_bounds__(256) void k_convt(const float* __restrict__ X,
       }
 }
 
-// ---------------------------------------------------------------------------
-// The same convolution for layers with many pixels: a workgroup computes RW x
-// WT = 256 pixels x CT = 32 output channels, each of its 4 waves 4 rows of 16
-// pixels x all CT channels, so that a weight fragment read from LDS feeds 64
-// pixels and a pixel fragment CT channels of up to three taps.  Input tile
-// and weights of a 32-channel chunk (9 taps x CT channels) are both in LDS,
-// 16 dwords per pixel and per channel row, whose 16-byte pieces are rotated
-// by the row (swz) so that fragment reads meet no bank conflicts without
-// padding: 80 KB, so two workgroups share a CU and one's staging runs beside
-// the other's products.  Workgroups run through their tiles (tile, chunk) by
-// (tile, chunk): the next chunk's or tile's loads are in registers while this
-// one's products run, and with one chunk and Cout = CT the weights are staged
-// once per workgroup.  The weights are the A operand, so a lane ends up with
-// 4 consecutive channels of a pixel and stores 16 bytes.  Cin % 32 == 0,
-// Cout % CT == 0, H % RW == 0, W % WT == 0.
-// Bound by the matrix cores: a layer of 29 GFLOP in three passes (batch 32,
-// 128 x 128: 32 channels at full, 64 at half, 128 at quarter resolution)
-// takes 33.7 us, 860 TFLOP/s; k_convt took 58, 52 and 77.  Measured on the
-// way: one workgroup of 4 waves x 64 channels per CU 37.5 us (its waves stage,
-// wait and multiply one after the other), 8 waves on 512 pixels 39.5 us.
-// ---------------------------------------------------------------------------
-// dword of 16-byte piece q of staged row p
+// dword of 16-byte piece q of staged row p (k_convw, k_convs)
 __device__ __forceinline__ int swz(int p, int q) { return 16 * p + 4 * (q ^ ((p >> 1) & 3)); }
 
 struct Mat {
@@ -663,6 +642,27 @@ __device__ __forceinline__ void conv_epilogue(const f32x4 (&acc)[4][NB], float* 
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same convolution for layers with many pixels: a workgroup computes RW x
+// WT = 256 pixels x CT = 32 output channels, each of its 4 waves 4 rows of 16
+// pixels x all CT channels, so that a weight fragment read from LDS feeds 64
+// pixels and a pixel fragment CT channels of up to three taps.  Input tile
+// and weights of a 32-channel chunk (9 taps x CT channels) are both in LDS,
+// 16 dwords per pixel and per channel row, whose 16-byte pieces are rotated
+// by the row (swz) so that fragment reads meet no bank conflicts without
+// padding: 80 KB, so two workgroups share a CU and one's staging runs beside
+// the other's products.  Workgroups run through their tiles (tile, chunk) by
+// (tile, chunk): the next chunk's or tile's loads are in registers while this
+// one's products run, and with one chunk and Cout = CT the weights are staged
+// once per workgroup.  The weights are the A operand, so a lane ends up with
+// 4 consecutive channels of a pixel and stores 16 bytes.  Cin % 32 == 0,
+// Cout % CT == 0, H % RW == 0, W % WT == 0.
+// Bound by the matrix cores: a layer of 29 GFLOP in three passes (batch 32,
+// 128 x 128: 32 channels at full, 64 at half, 128 at quarter resolution)
+// takes 33.7 us, 860 TFLOP/s; k_convt took 58, 52 and 77.  Measured on the
+// way: one workgroup of 4 waves x 64 channels per CU 37.5 us (its waves stage,
+// wait and multiply one after the other), 8 waves on 512 pixels 39.5 us.
+// ---------------------------------------------------------------------------
 template <int SPLIT, int WT, int EPI>
 __global__ __launch_bounds__(256, 2) void k_convw(const float* __restrict__ X,
                                                   const float* __restrict__ xscale,
