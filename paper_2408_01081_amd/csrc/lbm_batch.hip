@@ -75,13 +75,15 @@ __device__ inline int find_instance(const InstDesc* __restrict__ d, int lo, int 
 // a run of a few, which the whole workgroup walks together, so the descriptors
 // come through scalar loads and no thread searches for its own (128 instances
 // of 128 rows, 3.3 M nodes: FP64 initialisation 237 -> 81 us with the form of
-// init_node above).  Of more than WALK instances each thread finds its own: the
-// walk is one instance's latency after another (4096 instances of 4 x 4, 16 per
-// workgroup: 25 us walking, 19 so; 1280 of 3 x 2 to 7 x 8: 23 and 18; 16384 of
-// 1 x 1: 209 and 22).
+// init_node above).  MANY: in workgroups of more than WALK instances each thread
+// finds its own, since the walk is one instance's latency after another (4096
+// instances of 4 x 4, 16 per workgroup: 25 us walking, 18 so; 1280 of 3 x 2 to
+// 7 x 8: 23 and 18; 16384 of 1 x 1: 209 and 21); for batches with such workgroups
+// only, as the second copy of fn takes registers (32 of 128 x 128, FP32
+// initialisation 12.3 us without it, 14.1 with it).
 constexpr int WALK = 4;
 
-template <typename FN>
+template <bool MANY, typename FN>
 __device__ inline void for_block_instances(const InstDesc* __restrict__ descs, int n, int block,
                                            FN fn) {
   const int64_t first = (int64_t)block * BT, node = first + threadIdx.x;
@@ -94,8 +96,7 @@ __device__ inline void for_block_instances(const InstDesc* __restrict__ descs, i
     fn(d, (int)(loc - (int64_t)y * d.g.nx), y);
   };
   int i = find_instance(descs, 0, n - 1, first);
-  const bool whole = descs[i].node0 + (int64_t)descs[i].g.nx * descs[i].g.ny >= first + BT;
-  if (!whole && i + WALK < n && descs[i + WALK].node0 < first + BT) {
+  if (MANY && i + WALK < n && descs[i + WALK].node0 < first + BT) {
     at(descs[find_instance(descs, i, i + BT - 1 < n ? i + BT - 1 : n - 1, node)]);
     return;
   }
@@ -104,6 +105,13 @@ __device__ inline void for_block_instances(const InstDesc* __restrict__ descs, i
     if (d.node0 >= first + BT) break;
     at(d);
   }
+}
+
+// whether a workgroup of for_block_instances holds more than WALK instances
+bool many_instances(const std::vector<InstDesc>& d) {
+  for (size_t i = 0; i + WALK < d.size(); ++i)
+    if (d[i + WALK].node0 / BT == (d[i + 1].node0 - 1) / BT) return true;
+  return false;
 }
 
 template <int THREADS>
@@ -225,13 +233,13 @@ constexpr int kNumBatchTB = (int)(sizeof(kBatchTB) / sizeof(kBatchTB[0]));
 
 // packed = 0: v0 [..][2][ny][nx] and s0 [..][3][ny][nx] separate arrays;
 // packed = 1: one array [..][5][ny][nx] = (v, sigma_bar) in s0's place (v0 unused).
-template <typename T, bool NT>
+template <typename T, bool NT, bool MANY>
 __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
                                                    const T* __restrict__ s0, int packed,
                                                    float* __restrict__ pool,
                                                    const InstDesc* __restrict__ descs, int n) {
   const int block = xcd_tile(blockIdx.x, gridDim.x);
-  for_block_instances(descs, n, block, [&](const InstDesc& d, int x, int y) {
+  for_block_instances<MANY>(descs, n, block, [&](const InstDesc& d, int x, int y) {
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const T* v = packed ? s0 + 5 * d.node0 : v0 + 2 * d.node0;
     const T* s = packed ? s0 + 5 * d.node0 + 2 * ni : s0 + 3 * d.node0;
@@ -243,12 +251,13 @@ __global__ __launch_bounds__(BT) void k_batch_init(const T* __restrict__ v0,
 // that the last-level cache holds twice (two batches in turn, grid order / a
 // part per XCD: 64 uneven instances, 430 MB, 88.5 / 93.6 us, 64 of 250 x 250
 // 72.4 / 75.9, 512 of 33 x 128 69.3 / 73.1; 256 of 33 x 33, 54 MB, 15.0 / 14.2).
+template <bool MANY>
 __global__ __launch_bounds__(BT) void k_batch_moments(const float* __restrict__ pool,
                                                       float* __restrict__ out,
                                                       const InstDesc* __restrict__ descs, int n,
                                                       bool per_xcd, int mode) {
   const int block = per_xcd ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  for_block_instances(descs, n, block, [&](const InstDesc& d, int x, int y) {
+  for_block_instances<MANY>(descs, n, block, [&](const InstDesc& d, int x, int y) {
     const int64_t ni = (int64_t)d.g.nx * d.g.ny;
     const float* src = pool + d.off;
     float f[NQ][NC], U[NC];
@@ -369,6 +378,7 @@ struct Layout {
   std::vector<int> tile_inst, tile_count;
   int64_t pool_floats = 0, total_nodes = 0;
   int64_t full_row_floats = 0;  // of the pool: instances whose rows fill cache lines
+  bool many = false;            // many_instances
   int ntiles = 0;
   int tb_waves[kNumBatchTB];    // waves of each blocked variant
   int64_t tb_wave0[kNumBatchTB];  // its wave table's first entry in the tables' region
@@ -446,6 +456,7 @@ lbm_status plan(int32_t n, const lbm_params* params, Layout* L) {
       if (links > L->max_links) L->max_links = links;
     }
   }
+  L->many = many_instances(L->desc);
   for (int v = 0; v < kNumBatchTB; ++v) {
     const int valid = TB_LANES - 2 * kBatchTB[v].steps;
     int64_t w = 0;
@@ -803,14 +814,18 @@ static lbm_status batch_init_any(lbm_batch* b, const void* v0, const void* s0, i
   const int64_t total = b->L.total_nodes;
   const unsigned grid = (unsigned)((total + BT - 1) / BT);
   const bool nt = batch_init_nt((size_t)b->L.pool_floats * 4, (size_t)b->L.full_row_floats * 4);
-  if (f32)
-    hipLaunchKernelGGL((nt ? &k_batch_init<float, true> : &k_batch_init<float, false>), dim3(grid),
-                       dim3(BT), 0, b->stream, (const float*)v0, (const float*)s0, packed, b->pool[0],
-                       (const InstDesc*)b->d_desc, b->n);
-  else
-    hipLaunchKernelGGL((nt ? &k_batch_init<double, true> : &k_batch_init<double, false>),
-                       dim3(grid), dim3(BT), 0, b->stream, (const double*)v0, (const double*)s0, packed, b->pool[0],
-                       (const InstDesc*)b->d_desc, b->n);
+  const bool many = b->L.many;
+  if (f32) {
+    auto fn = many ? (nt ? &k_batch_init<float, true, true> : &k_batch_init<float, false, true>)
+                   : (nt ? &k_batch_init<float, true, false> : &k_batch_init<float, false, false>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(BT), 0, b->stream, (const float*)v0, (const float*)s0,
+                       packed, b->pool[0], (const InstDesc*)b->d_desc, b->n);
+  } else {
+    auto fn = many ? (nt ? &k_batch_init<double, true, true> : &k_batch_init<double, false, true>)
+                   : (nt ? &k_batch_init<double, true, false> : &k_batch_init<double, false, false>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(BT), 0, b->stream, (const double*)v0,
+                       (const double*)s0, packed, b->pool[0], (const InstDesc*)b->d_desc, b->n);
+  }
   lbm_status s = launch_check("batch init launch");
   if (s) return s;
   b->cur = 0;
@@ -991,8 +1006,8 @@ static lbm_status batch_moments(lbm_batch* b, float* out, int mode) {
   if (!b || !out) return fail(LBM_E_ARG, "null argument");
   if (!b->initialised) return fail(LBM_E_STATE, "not initialised");
   const int64_t total = b->L.total_nodes;
-  hipLaunchKernelGGL(k_batch_moments, dim3((unsigned)((total + BT - 1) / BT)), dim3(BT), 0,
-                     b->stream, (const float*)b->pool[b->cur], out, (const InstDesc*)b->d_desc,
+  hipLaunchKernelGGL(b->L.many ? &k_batch_moments<true> : &k_batch_moments<false>,
+                     dim3((unsigned)((total + BT - 1) / BT)), dim3(BT), 0, b->stream, (const float*)b->pool[b->cur], out, (const InstDesc*)b->d_desc,
                      b->n, (size_t)b->L.pool_floats * 4 <= INIT_NT_BYTES, mode);
   return launch_check("batch moments launch");
 }
