@@ -155,7 +155,8 @@ __device__ inline void body_hat0(const Force& F, int x, int y, double& bx, doubl
 // with FP64 divisions in the conversion of all five nodes and its loads behind
 // the branches of the boundary rule, it took 789 us on 4096 x 4096 and 92 us
 // on 2048 x 1024; in this form with plain stores 536 and 38 us, with
-// nontemporal ones 515 and 37 us (3.9 and 6.9 TB/s).
+// nontemporal ones 515 and 37 us, the pass repeated alone (3.9 and 6.9 TB/s);
+// between the steps and outputs of a run 526 and 70.
 
 template <bool NT>
 __device__ __forceinline__ void init_store(float v, float* p) {

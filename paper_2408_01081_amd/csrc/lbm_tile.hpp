@@ -23,7 +23,8 @@
 // 2.90; 256 x 256 with walls 1.61 against 2.94, periodic 1.56 (T = 8, 24
 // rows) against 1.97; 384 x 384 1.99 against 2.13; 512 x 512 3.07 against 2.84
 // (walls: 3.63 against 3.79); 724 x 724 5.07 against 3.60.  160 x 160 with a
-// load of rank 16 and the displacement state: 2.7 us, one launch per step 4.9.
+// load of rank 16 and the displacement state: 2.3 us (2.7 in a trace), one launch
+// per step 4.9.
 // 3 or 4 rows per wave: equal or slower (fewer waves; the wall code needs the
 // registers); tiles of 32 rows: slower.
 #pragma once
