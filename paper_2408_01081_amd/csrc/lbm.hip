@@ -1336,13 +1336,15 @@ static void launch_times(const lbm_ctx* c, int v, double ms[TB_MAX_STEPS + 1]) {
 }
 
 // the launches of a run with variant v (-1: single steps) without load,
-// displacement or error norms; times: divided by the launch times, where known
-static LaunchPlan run_plan(const lbm_ctx* c, int v, int64_t nsteps, bool times) {
+// displacement or error norms, divided by the launch times where they are known;
+// now: for the stream as it is, by the step count alone while it is captured
+static LaunchPlan run_plan(const lbm_ctx* c, int v, int64_t nsteps, bool now) {
   if (v < 0) return LaunchPlan{nsteps, 1, 0, {}};
   const int T = kTBVariants[v].steps, r = (int)(nsteps % T);
   double ms[TB_MAX_STEPS + 1] = {};
   // (a tile variant takes any smaller number of steps itself)
-  if (r && !is_tile(v) && times) launch_times(c, v, ms);
+  if (r && !is_tile(v) && c->times.step > 0.0 && !(now && capturing(c->stream)))
+    launch_times(c, v, ms);
   return plan_launches(nsteps, T, remainder_variant(c, r, v) >= 0, ms, TB_MAX_STEPS);
 }
 
@@ -1371,7 +1373,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   const StepFn fn = cfg.fn[c->p.bc];
   // chunks of whole launches (at most WALL_CHUNK steps): the chunk's wall
   // velocities are summed first, then its launches run
-  const LaunchPlan plan = run_plan(c, c->tb_cfg, nsteps, !capturing(c->stream));
+  const LaunchPlan plan = run_plan(c, c->tb_cfg, nsteps, true);
   for (int64_t l = 0, s0 = 0; l < plan.launches();) {
     int64_t end = l;
     int m = 0;
@@ -1699,7 +1701,7 @@ lbm_status lbm_select_for_steps(lbm_ctx* c, int64_t nsteps, int32_t* h_index) {
   double best_ms = (double)nsteps * c->times.step;
   for (int v = 0; v < kNumTBVariants; ++v) {
     if (c->times.tb[v] <= 0.0) continue;
-    const LaunchPlan plan = run_plan(c, v, nsteps, true);
+    const LaunchPlan plan = run_plan(c, v, nsteps, false);
     double ms[TB_MAX_STEPS + 1];
     launch_times(c, v, ms);
     const double run = plan_ms(plan, ms) * (plan.head < nsteps / plan.T ? 1.03 : 1.0);
