@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIBNAME = "liblbm_hip.so"
 SOURCES = ["lbm.hip", "lbm_tb_pa.hip", "lbm_tb_pb.hip", "lbm_tb_da.hip", "lbm_tb_db.hip",
            "lbm_tb_xa.hip", "lbm_tb_xb.hip", "lbm_tb_sp.hip", "lbm_tile.hip", "lbm_batch.hip",
-           "lbm_wop.hip", "sg.hip"]
+           "lbm_batch_many.hip", "lbm_wop.hip", "sg.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
