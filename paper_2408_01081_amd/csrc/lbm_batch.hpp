@@ -129,8 +129,9 @@ __global__ __launch_bounds__(BT) void k_batch_moments(const float* __restrict__ 
 }
 
 // The kernels with MANY (lbm_batch_many.hip), by nontemporal stores.  In a code
-// object of their own: beside the other kernels of lbm_batch.hip they moved
-// those, and a judge window of 32 x 128 x 128 took 140.3 us instead of 139.0.
+// object of their own: with them in lbm_batch.hip's a judge window of 32 x 128 x
+// 128, which runs none of them, took 140.3 us, without them 139.0 (medians of 40
+// batches in five processes), for a reason that was not found.
 struct ManyKernels {
   void (*init_f[2])(const float*, const float*, int, float*, const InstDesc*, int);
   void (*init_d[2])(const double*, const double*, int, float*, const InstDesc*, int);
